@@ -73,10 +73,41 @@ __device__ inline uint4 stream16(const void *p) {
 // their maximum), lgkmcnt(0); and the cache-policy operand of a direct-to-LDS
 // load that marks it non-temporal
 constexpr int kWaitVm0 = 0x0F70;
+constexpr int wait_vm(int n) { return kWaitVm0 | n; }   // all but the newest n (< 16) vector memory operations
 constexpr int kWaitLgkm0 = 0xC07F;
 constexpr int kCpolNT = 2;
 typedef const __attribute__((address_space(1))) void global_cvoid_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
+
+// LDS reads of a stage that direct-to-LDS loads fill, with their own wait.  As
+// builtins or plain loads the compiler makes every such read wait for all
+// direct-to-LDS loads in flight (s_waitcnt vmcnt(0)), also for those of the
+// next page, which cost the decode kernels a second memory latency per page;
+// here the caller waits for the loads it needs (wait_vm) first.
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+__device__ inline uint32_t lds_addr(const void *p) {
+    return (uint32_t)(size_t)(__attribute__((address_space(3))) const char *)p;
+}
+__device__ inline void lds_read16(uint32_t a0, uint32_t a1, u32x4_t &x0, u32x4_t &x1) {
+    __asm__ volatile(
+        "ds_read_b128 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(x0), "=&v"(x1) : "v"(a0), "v"(a1) : "memory");
+}
+__device__ inline void lds_read16(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x4_t &x0, u32x4_t &x1,
+                                  u32x4_t &x2, u32x4_t &x3) {
+    __asm__ volatile(
+        "ds_read_b128 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b128 %2, %6\n\tds_read_b128 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
+// four transposed 16-bit reads (ds_read_b64_tr_b16)
+__device__ inline void lds_read_tr(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2_t &x0, u32x2_t &x1,
+                                   u32x2_t &x2, u32x2_t &x3) {
+    __asm__ volatile(
+        "ds_read_b64_tr_b16 %0, %4\n\tds_read_b64_tr_b16 %1, %5\n\tds_read_b64_tr_b16 %2, %6\n\t"
+        "ds_read_b64_tr_b16 %3, %7\n\ts_waitcnt lgkmcnt(0)"
+        : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
 
 // The request's view of one step: resident tokens m, pages P (clamped to the
 // table), whether the step's new token goes in (room: a token is given and the
@@ -751,11 +782,16 @@ __global__ __launch_bounds__(64 * kDecodeWaves) __attribute__((amdgpu_waves_per_
         const int phys_next = pn < page_end ? s_ids[pn - page_begin] : -1;
         if (phys >= 0) {                              // wave-uniform
             __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            __builtin_amdgcn_s_waitcnt(wait_vm(KLD));     // the keys; the values, requested after them, may be on their way
             __builtin_amdgcn_sched_barrier(0);
+            u32x4_t kx[KK];
+            uint32_t ka[KK];
 #pragma unroll
-            for (int kk = 0; kk < KK; ++kk) kb[kk] = kstage[n * UPR + ((4 * kk + kg) ^ (n % UPR))];
-            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
+            for (int kk = 0; kk < KK; ++kk) ka[kk] = lds_addr(kstage + n * UPR + ((4 * kk + kg) ^ (n % UPR)));
+            if constexpr (KK == 4) lds_read16(ka[0], ka[1], ka[2], ka[3], kx[0], kx[1], kx[2], kx[3]);
+            else lds_read16(ka[0], ka[1], kx[0], kx[1]);
+#pragma unroll
+            for (int kk = 0; kk < KK; ++kk) kb[kk] = __builtin_bit_cast(uint4, kx[kk]);
             __builtin_amdgcn_sched_barrier(0);
         }
         if (phys_next >= 0) load_k_only(phys_next);
@@ -813,24 +849,34 @@ __global__ __launch_bounds__(64 * kDecodeWaves) __attribute__((amdgpu_waves_per_
             // token may hold anything (0 x inf would reach o), so they read as
             // zero; the step's new token comes from LDS.
             const int R = 4 * kg + n / 4, qd = n % 4, fv = 2 * (R % (UPR / 2));
-            const char *vrow = reinterpret_cast<const char *>(vstage + R * UPR) + (qd & 1) * 8;
-#pragma unroll
-            for (int t = 0; t < DT; ++t) {
-                bf16x4v_t vt = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-                    (__attribute__((address_space(3))) bf16x4v_t *)(vrow + ((2 * t + qd / 2) ^ fv) * 16));
-                if (ntok < kPage) {                   // wave-uniform
-#pragma unroll
-                    for (int e = 0; e < 4; ++e)
-                        if (4 * kg + e >= ntok) vt[e] = 0;
-                }
-                if constexpr (STEP) {
-                    if (p == p_new && kg == slot_new / 4) vt[slot_new % 4] = (short)s_new[1][16 * t + n];
-                }
-                ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t], 0, 0, 0);
-                ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t], 0, 0, 0);
-            }
-            __builtin_amdgcn_s_waitcnt(kWaitLgkm0);   // the values' stage is read
+            const uint32_t vrow = lds_addr(vstage + R * UPR) + (qd & 1) * 8;
+            // the values have landed: only the next page's keys were requested after them
             __builtin_amdgcn_sched_barrier(0);
+            if (phys_next >= 0) __builtin_amdgcn_s_waitcnt(wait_vm(KLD));
+            else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int t0 = 0; t0 < DT; t0 += 4) {
+                u32x2_t vx[4];
+                auto at = [&](int t) { return vrow + ((2 * t + qd / 2) ^ fv) * 16; };
+                lds_read_tr(at(t0), at(t0 + 1), at(t0 + 2), at(t0 + 3), vx[0], vx[1], vx[2], vx[3]);
+#pragma unroll
+                for (int k = 0; k < 4; ++k) {
+                    const int t = t0 + k;
+                    bf16x4v_t vt = __builtin_bit_cast(bf16x4v_t, vx[k]);
+                    if (ntok < kPage) {               // wave-uniform
+#pragma unroll
+                        for (int e = 0; e < 4; ++e)
+                            if (4 * kg + e >= ntok) vt[e] = 0;
+                    }
+                    if constexpr (STEP) {
+                        if (p == p_new && kg == slot_new / 4) vt[slot_new % 4] = (short)s_new[1][16 * t + n];
+                    }
+                    ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t], 0, 0, 0);
+                    ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t], 0, 0, 0);
+                }
+            }
+            __builtin_amdgcn_sched_barrier(0);            // the values' stage is read
         }
         if (phys_next >= 0) load_v_only(phys_next);
         phys = phys_next;
