@@ -205,7 +205,11 @@ gp_status_t gp_update_summaries(const void *q_pre, gp_dtype_t dtype, int32_t num
  * table.  fp32 accumulation; output in the KV dtype.  A request with m_r == 0
  * gets a zero output; a held request (seq_lens[r] < 0) gets none (its rows of
  * out are not written, and gp_decode_step leaves its summaries alone).  Page slots at or beyond m_r are never used, whatever
- * they hold.  out: [num_reqs][num_q_heads][head_dim]. */
+ * they hold.  The work is split over the pages of the whole batch, so the
+ * float32 sums of a request run in an order that depends on the lengths of the
+ * others (held ones count with their length): its output is the same to
+ * float32 rounding in any batch, bit for bit only in batches of the same
+ * lengths.  out: [num_reqs][num_q_heads][head_dim]. */
 gp_status_t gp_decode_attention(const gp_kv_layer_t *kv, const gp_page_state_t *ps,
                                 const void *q_post, int32_t num_q_heads, float scale,
                                 void *out, void *ws, size_t ws_bytes, hipStream_t stream);
@@ -264,7 +268,7 @@ gp_status_t gp_decode_attention_noalloc(const gp_kv_layer_t *kv, const gp_page_s
 /* gp_decode_attention in its two launches, for a caller that orders other
  * work after the first (Sec. 3.1, same outputs):
  *   GP_DECODE_CHUNKS  reads q_post and the cache through the page table: the
- *                     outputs of requests that fit in one chunk, partial
+ *                     outputs of requests that one workgroup covers, partial
  *                     (max, sum, o) of the others into ws;
  *   GP_DECODE_MERGE   folds those partials into the remaining outputs: reads
  *                     ws (which also records each request's length), never

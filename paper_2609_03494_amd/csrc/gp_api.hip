@@ -13,7 +13,6 @@ using namespace gp;
 // the decode partials live in this array, one copy per device, held until the
 // process ends.  In host code `scratch` only names the symbol; its device
 // address comes from hipGetSymbolAddress (scratch_address below).
-constexpr size_t kScratchBytes = size_t(8) << 20;
 static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 
 namespace {
@@ -100,7 +99,7 @@ size_t gp_workspace_bytes(int32_t op, int32_t num_reqs, int32_t num_bnd, int32_t
         return 0;
     switch (op) {
         case GP_OP_DECODE:
-            return decode_ws(num_reqs, num_q_heads, num_kv_heads, head_dim, max_pages).total;
+            return decode_ws(num_reqs, num_q_heads, num_kv_heads, head_dim, max_pages, decode_waves(elem_bytes(dtype), head_dim)).total;
         case GP_OP_SCORE: return score_ws(num_bnd, num_q_heads, num_kv_heads, max_pages).total;
         case GP_OP_APPLY:
             return apply_ws(num_bnd, num_kv_heads, head_dim, elem_bytes(dtype), max_pages, n_layers).total;
@@ -168,15 +167,17 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
     if (sum && (!sum->q_pre || !sum->slot_ids || !sum->init || !sum->qstate)) return GP_ERR_INVALID;
     if (sum && (!sum->k_new != !sum->v_new)) return GP_ERR_INVALID;
     if (sum && sum->k_new && sum->advance && !sum->positions) return GP_ERR_INVALID;
-    const DecodeWs w = decode_ws(ps->num_reqs, num_q_heads, kv->num_kv_heads, kv->head_dim, ps->max_pages);
-    if (ps->num_reqs > 65535 || w.max_chunks > kMaxDecodeChunks || w.chunk_pages > kMaxChunkPages)
-        return GP_ERR_UNSUPPORTED;
+    if (ps->num_reqs > 65535 || ps->max_pages > kMaxDecodePages) return GP_ERR_UNSUPPORTED;
+    const DecodeWs w = decode_ws(ps->num_reqs, num_q_heads, kv->num_kv_heads, kv->head_dim, ps->max_pages,
+                                 decode_waves(elem_bytes(kv->dtype), kv->head_dim));
     if (noalloc) {
-        if (w.total > kScratchBytes) return GP_ERR_SCRATCH;
+        if (decode_chunked_bytes(ps->num_reqs, num_q_heads, kv->head_dim, ps->max_pages) > kScratchBytes ||
+            w.plain > kScratchBytes)
+            return GP_ERR_SCRATCH;
         if ((st = scratch_address(stream, &ws)) != GP_OK) return st;
-        ws_bytes = kScratchBytes;
+    } else if (ws_bytes < w.total) {
+        return GP_ERR_WORKSPACE;
     }
-    if (ws_bytes < w.total) return GP_ERR_WORKSPACE;
     DecodeArgs a = {};
     if (num_groups < 0 || num_groups > kMaxPrefixGroups || (num_groups > 0 && !groups)) return GP_ERR_INVALID;
     if (num_groups > 0 && kv->dtype != GP_BF16) return GP_ERR_UNSUPPORTED;
@@ -195,6 +196,8 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
             a.g_num[g] = gr.num_reqs;
             a.g_pages[g] = gr.prefix_pages;
             a.g_blk0[g] = blk;
+            a.g_slots[g] = cdiv(gr.prefix_pages, kPrefixSlotPages);
+            if (a.g_slots[g] > w.pslots) a.g_slots[g] = w.pslots;
             blk += cdiv(gr.num_reqs, rpb);
         }
         a.g_blk0[num_groups] = blk;
@@ -224,13 +227,15 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
     a.advance = sum && sum->k_new ? (sum->advance != 0) : 0;
     a.partial = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + w.partial);
     a.lens = reinterpret_cast<int32_t *>(static_cast<unsigned char *>(ws) + w.lens);
+    a.prefix = reinterpret_cast<float *>(static_cast<unsigned char *>(ws) + w.prefix);
     a.R = ps->num_reqs;
     a.Hkv = kv->num_kv_heads;
     a.max_pages = ps->max_pages;
     a.pool_pages = kv->pool_pages;
-    a.max_chunks = w.max_chunks;
+    a.W = w.W;
+    a.min_run = kDecodeMinRun;
     a.slots = w.slots;
-    a.chunk_pages = w.chunk_pages;
+    a.pslots = w.pslots;
     a.qscale = scale * 1.4426950408889634f;
     return from_hip(launch_decode(kv->dtype, kv->head_dim, num_q_heads / kv->num_kv_heads, a, stages, stream));
 }

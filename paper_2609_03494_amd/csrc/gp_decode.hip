@@ -1,28 +1,32 @@
 // Paged GQA decode attention (Sec. 3.1, attention-output equation), split over
-// the sequence.
+// the resident pages of the whole batch.
 //
-// Work item = (KV head h, chunk of the request's pages, request r): one
-// workgroup serves the whole GQA group of h (G query heads), so every K/V byte
-// is read from HBM once per step.  A request of m tokens has cdiv(m, chunk
-// tokens) chunks, chunk tokens being about kDecodeChunkPages pages sized so
-// that a request of max_pages pages splits evenly; its pages are then divided
-// into that many nearly equal chunks, which keeps workgroup durations even.
-// A request that
-// spans several chunks leaves one (o, max, sum) partial per chunk, which a
-// second, small kernel merges; a request of a single chunk gets its output
-// from the first kernel.  Consecutive workgroups are the KV heads of one
-// chunk, so the head slices of the same pages are read at about the same
-// time.
+// Work split.  Per KV head the batch is one flat list of pages: the pages of
+// request 0, then of request 1, and so on (U pages, read off the lengths by
+// every wave itself).  The waves of a.W workgroups take equal runs of L =
+// max(kMinRun, ceil(U / waves)) consecutive pages of it, whatever requests they
+// belong to, so every workgroup of the grid has the same amount of work and
+// none is empty as long as there are pages; the next page's keys and values are
+// on their way across request boundaries too.  A wave that meets the end of a
+// request writes that request's result (or its partial, if the request began
+// before the wave's run) and goes on with the next; at the end the workgroup
+// merges the runs its waves left open, and requests that span workgroups are
+// folded by merge_kernel from one (o, max, sum) partial per workgroup, at slot
+// (workgroup + request) of the KV head (the pair only ever grows along the
+// list, so slots are distinct).
+// Why: with a (KV head, 64-page chunk, request) grid most of the workgroups of
+// a batch with mixed lengths were empty (28 k of 35 k at 256 requests, table
+// width 1028), a request's chunks set the workgroups' durations, and one
+// request gave 48 workgroups to 256 CUs.
 //
-// fp32 (vector ALUs): lane l holds dims [c*EPL, c*EPL+EPL) of token
-// j*TPL + l/LPT for each of the LPP loads of a page, c = l % LPT; dot products
-// finish with cross-lane sums over the LPT lanes of a token.  Four waves take
-// pages round-robin, two pages in flight per wave.
-//
-// bf16: see decode_split_kernel.
+// A workgroup serves the whole GQA group of its KV head (G query heads), so
+// every K/V byte is read from HBM once per step.  The KV head is the fastest
+// grid index: the eight heads of a page are read at about the same time.
 //
 // Bound: HBM.  Algorithmic bytes per resident token and KV head:
-// 2 * d * sizeof(elem) (K and V), plus the page-table entries, q and out.
+// 2 * d * sizeof(elem) (K and V), plus the page-table entries, q and out.  A
+// copy of the kernel's loads without arithmetic (equal runs, 4 KiB head slices
+// of randomly placed pages) reads 6.5-6.9 TB/s; a plain streaming read 7.04.
 #include "gp_internal.h"
 
 namespace gp {
@@ -34,47 +38,33 @@ struct Traits;
 
 template <>
 struct Traits<uint16_t> {
-    static constexpr int EPL = 8;  // bf16 elements per 16-byte load
-    __device__ static inline void unpack(const uint4 &u, float *f) {
-        f[0] = bf16_lo(u.x); f[1] = bf16_hi(u.x);
-        f[2] = bf16_lo(u.y); f[3] = bf16_hi(u.y);
-        f[4] = bf16_lo(u.z); f[5] = bf16_hi(u.z);
-        f[6] = bf16_lo(u.w); f[7] = bf16_hi(u.w);
-    }
     __device__ static inline void store(uint16_t *p, float x) { *p = f32_to_bf16(x); }
     __device__ static inline float load(const uint16_t *p) { return bf16_to_f32(*p); }
 };
 
 template <>
 struct Traits<float> {
-    static constexpr int EPL = 4;
-    __device__ static inline void unpack(const uint4 &u, float *f) {
-        f[0] = __uint_as_float(u.x); f[1] = __uint_as_float(u.y);
-        f[2] = __uint_as_float(u.z); f[3] = __uint_as_float(u.w);
-    }
     __device__ static inline void store(float *p, float x) { *p = x; }
     __device__ static inline float load(const float *p) { return *p; }
 };
 
 constexpr float kNegInf = -__builtin_huge_valf();
 
-// K and V are read exactly once per step, so their loads carry the
-// non-temporal hint: the caches do not keep them at the expense of data that
-// is reused (page tables, partials, and the workspaces of the boundary
-// kernels that run beside decode attention).  On MI355X this also raised the
-// decode call's own bandwidth (0.123 -> 0.115 ms at the Qwen3-8B layer shape).
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
-__device__ inline uint4 stream16(const void *p) {
-    const u32x4_t x = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(p));
-    return make_uint4(x[0], x[1], x[2], x[3]);
-}
+typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
+typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
+typedef __attribute__((ext_vector_type(4))) float f32x4_t;
+typedef short bf16x4s_t __attribute__((ext_vector_type(4)));
 
 // s_waitcnt immediates: vmcnt(0) (vmcnt in bits 3:0 and 15:14, the others at
-// their maximum), lgkmcnt(0); and the cache-policy operand of a direct-to-LDS
-// load that marks it non-temporal
+// their maximum); and the cache-policy operand of a direct-to-LDS load that
+// marks it non-temporal: K and V are read exactly once per step, so the caches
+// do not keep them at the expense of data that is reused (page tables,
+// partials, the workspaces of boundary kernels beside decode); it also raises
+// the read rate itself (6.0 against 6.8 TB/s in the copy without arithmetic).
 constexpr int kWaitVm0 = 0x0F70;
-constexpr int wait_vm(int n) { return kWaitVm0 | n; }   // all but the newest n (< 16) vector memory operations
-constexpr int kWaitLgkm0 = 0xC07F;
+// all but the newest n (< 64) vector memory operations
+constexpr int wait_vm(int n) { return kWaitVm0 | (n & 15) | (n >> 4) << 14; }
 constexpr int kCpolNT = 2;
 typedef const __attribute__((address_space(1))) void global_cvoid_t;
 typedef __attribute__((address_space(3))) void lds_void_t;
@@ -84,7 +74,6 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 // direct-to-LDS loads in flight (s_waitcnt vmcnt(0)), also for those of the
 // next page, which cost the decode kernels a second memory latency per page;
 // here the caller waits for the loads it needs (wait_vm) first.
-typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 __device__ inline uint32_t lds_addr(const void *p) {
     return (uint32_t)(size_t)(__attribute__((address_space(3))) const char *)p;
 }
@@ -109,1056 +98,722 @@ __device__ inline void lds_read_tr(uint32_t a0, uint32_t a1, uint32_t a2, uint32
         : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
 }
 
-// The request's view of one step: resident tokens m, pages P (clamped to the
-// table), whether the step's new token goes in (room: a token is given and the
-// last page has a free slot, Sec. 3.1 paged cache) and the tokens attended.
-struct StepView {
-    int m, P, m_attn;
-    bool room;
+// ------------------------------------------------------------ lane helpers --
+// wave-uniform value, in a scalar register
+__device__ inline int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
+// x of lane i's partners in the other three rows of 16 lanes (lanes i ^ 16,
+// i ^ 32, i ^ 48) folded in: v_permlane16_swap and v_permlane32_swap exchange
+// rows in the vector ALU, where a shuffle would go through LDS.
+__device__ inline float cross_max(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+    auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+__device__ inline float cross_sum(float x) {
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float y = __uint_as_float(r[0]) + __uint_as_float(r[1]);
+    auto q = __builtin_amdgcn_permlane32_swap(__float_as_uint(y), __float_as_uint(y), false, false);
+    return __uint_as_float(q[0]) + __uint_as_float(q[1]);
+}
+
+// element i (wave-uniform) of an array that nothing writes during the kernel,
+// by a scalar load: it is counted apart from the pages in flight, so waiting for
+// it does not drain them
+__device__ inline int scalar_load(const int32_t *p, int64_t i) {
+    return ((const __attribute__((address_space(4))) int32_t *)p)[i];
+}
+
+// inclusive prefix sum over the wave (DPP row shifts and row broadcasts)
+__device__ inline int wave_scan(int x) {
+    x += __builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false);
+    x += __builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false);
+    return x;
+}
+
+// ------------------------------------------------------------ request view --
+// What the pass covers of one request: its resident tokens m, whether the
+// step's new token goes in (room: a token is given and the last page has a
+// free slot, Sec. 3.1 paged cache), the tokens attended, the pages before the
+// covered range (base) and the pages covered (n).  A held request keeps its
+// place in the flat list (m = -seq_len - 1), so that a request's output does not
+// depend on which others are held; its pages are passed over.
+struct ReqView {
+    int m, m_attn, base, n;
+    bool held, room;
 };
-__device__ inline StepView step_view(const DecodeArgs &a, int r, int m) {
-    StepView v;
-    int P = a.num_pages[r];
-    v.P = P < 0 ? 0 : (P > a.max_pages ? a.max_pages : P);
-    v.m = m > v.P * kPage ? v.P * kPage : m;
-    v.room = a.k_new != nullptr && v.m < v.P * kPage;
+
+template <bool STEP, bool PREFIX>
+__device__ inline ReqView req_view(const DecodeArgs &a, int r, int m_in, int P_in) {
+    ReqView v;
+    const int P = min(max(P_in, 0), a.max_pages);
+    v.held = m_in < 0;
+    v.m = min(v.held ? -m_in - 1 : m_in, P * kPage);
+    v.room = STEP && !v.held && v.m < P * kPage;
     v.m_attn = v.m + (v.room ? 1 : 0);
+    v.base = 0;
+    if constexpr (PREFIX) {
+        // The shared pages come from the prefix pass if the request is not
+        // held, holds the prefix's pages and tokens and more, and has the
+        // leader's page ids on all prefix pages.  The split goes by the first
+        // and the last of them (a compaction replaces every shared page); the
+        // wave that begins the request compares them all, and takes the prefix
+        // pages itself if they differ.
+        int pp = 0, first = 0;
+        for (int g = 0; g < a.ngroups; ++g)
+            if (r >= a.g_first[g] && r < a.g_first[g] + a.g_num[g]) {
+                pp = a.g_pages[g];
+                first = a.g_first[g];
+            }
+        const int32_t *row = a.page_table + (size_t)r * a.max_pages, *lead = a.page_table + (size_t)first * a.max_pages;
+        const int last = max(pp - 1, 0);
+        const bool same = (row[0] == lead[0]) & (row[last] == lead[last]);
+        if (same && pp > 0 && m_in > pp * kPage && P_in > pp && P_in <= a.max_pages && m_in <= P_in * kPage) v.base = pp;
+    }
+    v.n = cdiv(v.m_attn, kPage) - v.base;
     return v;
 }
+template <bool STEP, bool PREFIX>
+__device__ inline ReqView req_view(const DecodeArgs &a, int r) {
+    return req_view<STEP, PREFIX>(a, r, a.seq_lens[r], a.num_pages[r]);
+}
 
-// For the merge pass: the tokens attended (-1: held), whether a token went in
-// and how many partial slots the merge folds (0: the output is written by the
-// chunk pass), written once per request by the workgroup of (KV head 0,
-// chunk 0).
-__device__ inline void record_step(const DecodeArgs &a, int r, int h, int chunk, int m_attn, bool room,
-                                   int merge_slots) {
-    if (h == 0 && chunk == 0 && threadIdx.x == 0) {
-        a.lens[r] = m_attn;
-        a.lens[a.R + r] = room ? 1 : 0;
-        a.lens[2 * a.R + r] = merge_slots;
+// The page of K or V that one wave has in flight, by element type: how it is
+// laid out in LDS, and the two products on it.
+//
+// Both products run on the matrix cores, with the scores computed transposed:
+// S^T = K.Q^T (16 tokens x 16 columns, the G query heads and 16 - G zero
+// ones) leaves tokens 4 kg + e of head n in lane (n, kg) = (lane % 16, lane /
+// 16), which is the layout P^T needs as the B operand of O^T += V^T.P^T; every
+// lane then owns output dims of one head, so the softmax rescale needs no lane
+// exchange, and the cost does not depend on G.
+template <typename T, int D>
+struct Page;
+
+// bfloat16: S^T on v_mfma_f32_16x16x32_bf16; P split into two bfloat16 terms
+// (hi + lo carry its float32 value to about 2^-17) and O^T on
+// v_mfma_f32_16x16x16bf16_1k with V^T by transposed LDS reads
+// (ds_read_b64_tr_b16).  Keys are XOR-swizzled on the way in: unit u (16
+// bytes) of row R sits at R UPR + (u ^ R % UPR), so that the 16 rows of a
+// score-layout read fall on distinct banks; values at u ^ 2 (R % (UPR / 2)),
+// so that the transposed reads of 4 rows x 2 units do.
+template <int D>
+struct Page<uint16_t, D> {
+    static constexpr int UPR = D / 8;                 // 16-byte units per row
+    static constexpr int BYTES = kPage * D * 2;       // keys or values of one page and head
+    static constexpr int LOADS = BYTES / 1024;        // load instructions (64 lanes x 16 bytes) per page
+    static constexpr int WAVES = decode_waves(2, D);  // per workgroup: 64 KiB of pages at most
+    static constexpr int RPI = 64 / UPR;              // rows per load instruction
+    static constexpr int KK = D / 32;                 // product steps over the head dims
+    static constexpr int DT = D / 16;                 // O^T tiles of 16 dims
+
+    // byte offset of this lane's unit in load instruction q of keys or values,
+    // less 1024 q (the instruction's immediate): row R = q RPI + lane / UPR, unit
+    // (lane % UPR) swizzled by R, which splits into a part of the lane and one of
+    // q (their bits are disjoint)
+    __device__ static inline uint32_t koff(int lane) {
+        return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (lane / UPR))) * 16;
     }
-}
-
-// gp_decode_attention_shared: whether request r (not held, at least pp pages
-// and pp * page_size tokens, within its table) may read a prefix pass of pp
-// pages; the prefix pass and the tail pass also require the leader's page ids
-// on every prefix page.  Both passes evaluate this on their own.
-__device__ inline bool prefix_reader(const DecodeArgs &a, int r, int pp) {
-    const int m = a.seq_lens[r], P = a.num_pages[r];
-    return m >= pp * kPage && P >= pp && P <= a.max_pages && m <= P * kPage;
-}
-
-// gp_decode_step: the summary update of query heads [h G, h G + G) of request
-// r, done by the workgroup of the pair's first chunk (Sec. 4.1 folds the
-// update into the attention kernel).  Same arithmetic as the update kernel.
-template <typename T, int D, int G>
-__device__ inline void fold_summaries(const DecodeArgs &a, int r, int h) {
-    if (!a.qstate) return;
-    const int slot = a.slot_ids[r];
-    if (slot < 0 || slot >= a.M) return;
-    const int Hq = a.Hkv * G;
-    const bool ini = a.init[r] != 0;
-    const T *q = reinterpret_cast<const T *>(a.q_pre) + ((size_t)r * Hq + (size_t)h * G) * D;
-    float *S = a.qstate + (size_t)slot * 2 * Hq * D + (size_t)h * G * D;
-    float *L = S + (size_t)Hq * D;
-    const double cs = 1.0 - a.beta_s, cl = 1.0 - a.beta_l;
-    for (int i = threadIdx.x; i < G * D; i += blockDim.x) {
-        const float x = Traits<T>::load(q + i);
-        if (ini) {
-            S[i] = x;
-            L[i] = x;
-        } else {
-            S[i] = ema_step(S[i], x, a.beta_s, cs);
-            L[i] = ema_step(L[i], x, a.beta_l, cl);
+    static constexpr uint32_t kflip(int q) { return q * RPI % UPR * 16; }
+    __device__ static inline uint32_t voff(int lane) {
+        return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (2 * (lane / UPR % (UPR / 2))))) * 16;
+    }
+    static constexpr uint32_t vflip(int q) { return 2 * (q * RPI % (UPR / 2)) * 16; }
+    // LDS offsets of this lane's reads, to be xored with 64 kk (key operand kk) or
+    // 32 t (transposed values of tile t)
+    __device__ static inline uint32_t kread(int n, int kg) { return (n * UPR + (kg ^ (n % UPR))) * 16; }
+    __device__ static inline uint32_t vread(int n, int kg) {
+        // V^T tile t as the A operand by transposed reads: lane j of group kg
+        // names row R = 4 kg + j / 4, dims 16 t + 4 (j % 4); lane n receives
+        // tokens 4 kg .. + 3 at dim 16 t + n
+        const int R = 4 * kg + n / 4, qd = n % 4;
+        return (R * UPR + ((qd / 2) ^ (2 * (R % (UPR / 2))))) * 16 + (qd & 1) * 8;
+    }
+    // Q of head n as the B operand: unit kk of lane (n, kg) is head dims 32 kk + 8 kg .. + 7
+    static constexpr int QREGS = KK;
+    __device__ static inline int qdim(int j, int kg) { return 32 * j + 8 * kg; }
+    __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
+        u32x4_t kx[KK];
+        if constexpr (KK == 4) lds_read16(ka, ka ^ 64, ka ^ 128, ka ^ 192, kx[0], kx[1], kx[2], kx[3]);
+        else lds_read16(ka, ka ^ 64, kx[0], kx[1]);
+        f32x4_t st = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int kk = 0; kk < KK; ++kk) {
+            st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kx[kk]),
+                                                         __builtin_bit_cast(bf16x8_t, q[kk]), st, 0, 0, 0);
+        }
+        return st;
+    }
+    // O^T += V^T.P^T; ntok: tokens of the page (slots past the last may hold
+    // anything: 0 x inf would reach o, so they read as zero)
+    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&ot)[DT], int kg) {
+        bf16x4s_t phi, plo;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            const __bf16 hb = (__bf16)p[e];               // round to nearest even
+            phi[e] = __builtin_bit_cast(short, hb);
+            plo[e] = __builtin_bit_cast(short, (__bf16)(p[e] - (float)hb));   // p - hi is exact in float32
+        }
+#pragma unroll
+        for (int t0 = 0; t0 < DT; t0 += 4) {
+            u32x2_t vx[4];
+            lds_read_tr(va ^ 32 * t0, va ^ 32 * (t0 + 1), va ^ 32 * (t0 + 2), va ^ 32 * (t0 + 3), vx[0], vx[1], vx[2], vx[3]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                bf16x4s_t vt = __builtin_bit_cast(bf16x4s_t, vx[k]);
+                if (ntok < kPage) {                       // wave-uniform
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (4 * kg + e >= ntok) vt[e] = 0;
+                }
+                ot[t0 + k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t0 + k], 0, 0, 0);
+                ot[t0 + k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t0 + k], 0, 0, 0);
+            }
         }
     }
-}
+    // group j of four consecutive dims that the lane owns: its first dim and values
+    static constexpr int GROUPS = DT;
+    __device__ static inline int group_dim(int j, int kg) { return 16 * j + 4 * kg; }
+    __device__ static inline f32x4_t group(const f32x4_t (&ot)[DT], int j) { return ot[j]; }
+};
 
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256) void decode_kernel(DecodeArgs a) {
-    using Tr = Traits<T>;
-    constexpr int EPL = Tr::EPL;
-    constexpr int LPT = D / EPL;          // lanes per token
-    constexpr int TPL = 64 / LPT;         // tokens per wave load
-    constexpr int LPP = kPage / TPL;      // loads per page
-    constexpr int NW = 4;                 // waves per workgroup
-    const int CHUNK = a.chunk_pages * kPage;
-    static_assert(LPT >= 1 && LPT <= 64 && TPL * LPP == kPage, "layout");
+// float32: both products on v_mfma_f32_16x16x4f32 (float32 products and sums).
+// The contraction takes the head dims of a 16-byte key unit one by one, unit
+// 4 j + kg in lane group kg; P.V takes tokens 4 kg + e in step e, so P is in
+// place, and the value units of a row as they lie: row n of O^T tile 4 j + c is
+// dim 64 j + 4 n + c.  Keys are swizzled (u ^ R % 16); a value read is one
+// 256-byte run per row.
+template <int D>
+struct Page<float, D> {
+    static constexpr int UPR = D / 4;
+    static constexpr int BYTES = kPage * D * 4;
+    static constexpr int LOADS = BYTES / 1024;
+    static constexpr int WAVES = decode_waves(4, D);
+    static constexpr int RPI = 64 / UPR;
+    static constexpr int NJ = D / 16;                 // key units per lane
+    static constexpr int DT = D / 16;
 
-    __shared__ float s_m[NW][G], s_l[NW][G];
-    __shared__ float s_o[NW][G][D];
-
-    __shared__ float s_new[2][D];             // the step's new token (K, V) of head h
-
-    const int h = blockIdx.x, chunk = blockIdx.y, r = blockIdx.z;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int Hkv = a.Hkv;
-    const int Hq = Hkv * G;
-    const int m_in = a.seq_lens[r];
-    if (m_in < 0) {                           // held: not in this step's batch
-        record_step(a, r, h, chunk, -1, false, 0);
-        return;
+    __device__ static inline uint32_t koff(int lane) {
+        return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (lane / UPR))) * 16;
     }
-    const StepView sv = step_view(a, r, m_in);
-    // with a new token, only the requests that take it update their summaries
-    if (chunk == 0 && (a.k_new == nullptr || sv.room)) fold_summaries<T, D, G>(a, r, h);
-    const int m = sv.m_attn;
-    const int nchunks = cdiv(m, CHUNK);
-    record_step(a, r, h, chunk, sv.m_attn, sv.room, nchunks > 1 ? nchunks : 0);
-    T *out = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-    if (m == 0) {
-        if (chunk == 0)
-            for (int i = threadIdx.x; i < G * D; i += blockDim.x) Tr::store(out + i, 0.0f);
-        return;
-    }
-    if (chunk >= nchunks) return;
-
-    // the request's pages split into nchunks nearly equal chunks (the chunk
-    // count is the merge's; equal lengths keep the workgroups' durations even)
-    const int npg = cdiv(m, kPage), cs = cdiv(npg, nchunks);
-    const int page_begin = min(npg, chunk * cs), page_end = min(npg, page_begin + cs);
-
-    // the new token: the workgroup whose pages hold slot m_in writes it into
-    // the cache and takes its K and V from LDS (the cache slot is not read back)
-    const int p_new = sv.room ? sv.m / kPage : -1, slot_new = sv.m % kPage;
-    const bool owns_new = p_new >= page_begin && p_new < page_end;
-    if (owns_new) {
-        const T *kn = reinterpret_cast<const T *>(a.k_new) + ((size_t)r * Hkv + h) * D;
-        const T *vn = reinterpret_cast<const T *>(a.v_new) + ((size_t)r * Hkv + h) * D;
-        const int pid = a.page_table[(size_t)r * a.max_pages + p_new];
-        const bool okp = pid >= 0 && pid < a.pool_pages;
-        const size_t dst = (((size_t)(okp ? pid : 0) * Hkv + h) * kPage + slot_new) * D;
-        for (int i = threadIdx.x; i < 2 * D; i += blockDim.x) {
-            const int kvsel = i / D, dd = i % D;
-            const T x = kvsel ? vn[dd] : kn[dd];
-            s_new[kvsel][dd] = Tr::load(&x);
-            if (okp) (kvsel ? reinterpret_cast<T *>(a.v_w) : reinterpret_cast<T *>(a.k_w))[dst + dd] = x;
+    static constexpr uint32_t kflip(int q) { return q * RPI * 16; }
+    __device__ static inline uint32_t voff(int lane) { return lane * 16; }
+    static constexpr uint32_t vflip(int) { return 0; }
+    // key operand j: xor 64 j; values of token 4 kg + e, unit n + 16 j: plus (e UPR + 16 j) 16
+    __device__ static inline uint32_t kread(int n, int kg) { return (n * UPR + (kg ^ n)) * 16; }
+    __device__ static inline uint32_t vread(int n, int kg) { return (4 * kg * UPR + n) * 16; }
+    static constexpr int QREGS = NJ;
+    __device__ static inline int qdim(int j, int kg) { return 16 * j + 4 * kg; }
+    __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
+        f32x4_t st[4];                                // (four short sums per score, added at the end)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) st[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j0 = 0; j0 < NJ; j0 += 4) {
+            u32x4_t kx[4];
+            lds_read16(ka ^ 64 * j0, ka ^ 64 * (j0 + 1), ka ^ 64 * (j0 + 2), ka ^ 64 * (j0 + 3), kx[0], kx[1], kx[2], kx[3]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    st[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[k][e]), __uint_as_float(q[j0 + k][e]),
+                                                                 st[e], 0, 0, 0);
+            }
         }
+        return (st[0] + st[1]) + (st[2] + st[3]);
     }
-    __syncthreads();
-
-    const int c = lane % LPT, row = lane / LPT;
-    const T *qp = reinterpret_cast<const T *>(a.q) + ((size_t)r * Hq + (size_t)h * G) * D + c * EPL;
-    float q[G][EPL];
+    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&ot)[DT], int kg) {
+        f32x4_t pv[DT];                               // (the page's own sum, then added to the run's)
 #pragma unroll
-    for (int g = 0; g < G; ++g)
+        for (int t = 0; t < DT; ++t) pv[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) q[g][e] = Tr::load(qp + (size_t)g * D + e) * a.qscale;
-
-    float mrun[G], l[G], o[G][EPL];
+        for (int e0 = 0; e0 < 4; e0 += 8 / (D / 32)) {    // four reads at a time
+            constexpr int NE = 8 / (D / 32), NU = D / 64; // tokens and units per token of one batch
+            u32x4_t vx[4];
+            auto at = [&](int k) { return va + ((e0 + k / NU) * UPR + 16 * (k % NU)) * 16; };
+            lds_read16(at(0), at(1), at(2), at(3), vx[0], vx[1], vx[2], vx[3]);
 #pragma unroll
-    for (int g = 0; g < G; ++g) {
-        mrun[g] = kNegInf;
-        l[g] = 0.0f;
+            for (int k = 0; k < 4; ++k) {
+                const int e = e0 + k / NU, j = k % NU;
+                const bool in = 4 * kg + e < ntok;
 #pragma unroll
-        for (int e = 0; e < EPL; ++e) o[g][e] = 0.0f;
-    }
-
-    const int32_t *table = a.page_table + (size_t)r * a.max_pages;
-    const T *kpool = reinterpret_cast<const T *>(a.k);
-    const T *vpool = reinterpret_cast<const T *>(a.v);
-    const size_t head_off = (size_t)h * kPage * D;
-    const size_t page_elems = (size_t)Hkv * kPage * D;
-    const int lane_off = row * D + c * EPL;
-
-    for (int p0 = page_begin + wave; p0 < page_end; p0 += 2 * NW) {
-        uint4 kr[2][LPP], vr[2][LPP];
-        int ntok[2];
-        bool ok[2];
-#pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            const int p = p0 + u * NW;
-            int phys = p < page_end ? table[p] : -1;
-            ok[u] = phys >= 0 && phys < a.pool_pages;
-            ntok[u] = ok[u] ? min(kPage, m - p * kPage) : 0;
-            const size_t base = (size_t)(ok[u] ? phys : 0) * page_elems + head_off + lane_off;
-            if (ok[u]) {
-#pragma unroll
-                for (int j = 0; j < LPP; ++j) {
-                    kr[u][j] = stream16(kpool + base + (size_t)j * TPL * D);
-                    vr[u][j] = stream16(vpool + base + (size_t)j * TPL * D);
+                for (int c = 0; c < 4; ++c) {
+                    const float v = in ? __uint_as_float(vx[k][c]) : 0.0f;
+                    pv[4 * j + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p[e], pv[4 * j + c], 0, 0, 0);
                 }
             }
+            static_assert(NE * NU == 4, "four reads per batch");
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-            if (!ok[u]) continue;   // wave-uniform
-            float s[LPP][G];
-            const bool patch = p0 + u * NW == p_new;     // wave-uniform
-#pragma unroll
-            for (int j = 0; j < LPP; ++j) {
-                float kf[EPL];
-                Tr::unpack(kr[u][j], kf);
-                if (patch && j * TPL + row == slot_new) {
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) kf[e] = s_new[0][c * EPL + e];
-                }
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    float acc = 0.0f;
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) acc = fmaf(q[g][e], kf[e], acc);
-                    s[j][g] = acc;
-                }
-            }
-#pragma unroll
-            for (int off = LPT / 2; off >= 1; off >>= 1)
-#pragma unroll
-                for (int j = 0; j < LPP; ++j)
-#pragma unroll
-                    for (int g = 0; g < G; ++g) s[j][g] += __shfl_xor(s[j][g], off, 64);
-            const bool full = ntok[u] == kPage;
-            float pmax[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) pmax[g] = kNegInf;
-#pragma unroll
-            for (int j = 0; j < LPP; ++j) {
-                const bool valid = full || (j * TPL + row) < ntok[u];
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    s[j][g] = valid ? s[j][g] : kNegInf;
-                    pmax[g] = fmaxf(pmax[g], s[j][g]);
-                }
-            }
-#pragma unroll
-            for (int off = LPT; off < 64; off <<= 1)
-#pragma unroll
-                for (int g = 0; g < G; ++g) pmax[g] = fmaxf(pmax[g], __shfl_xor(pmax[g], off, 64));
-            float alpha[G];
-#pragma unroll
-            for (int g = 0; g < G; ++g) {
-                const float mn = fmaxf(mrun[g], pmax[g]);
-                alpha[g] = exp2f(mrun[g] - mn);
-                mrun[g] = mn;
-                l[g] *= alpha[g];
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) o[g][e] *= alpha[g];
-            }
-#pragma unroll
-            for (int j = 0; j < LPP; ++j) {
-                const bool valid = full || (j * TPL + row) < ntok[u];
-                float vf[EPL];
-                Tr::unpack(vr[u][j], vf);
-                if (patch && j * TPL + row == slot_new) {
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) vf[e] = s_new[1][c * EPL + e];
-                }
-#pragma unroll
-                for (int e = 0; e < EPL; ++e) vf[e] = valid ? vf[e] : 0.0f;
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float pw = exp2f(s[j][g] - mrun[g]);
-                    l[g] += pw;
-#pragma unroll
-                    for (int e = 0; e < EPL; ++e) o[g][e] = fmaf(pw, vf[e], o[g][e]);
-                }
-            }
-        }
+        for (int t = 0; t < DT; ++t) ot[t] += pv[t];
     }
-
-    // sum over the token rows of the wave (all rows share the running max)
-#pragma unroll
-    for (int off = LPT; off < 64; off <<= 1)
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            l[g] += __shfl_xor(l[g], off, 64);
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) o[g][e] += __shfl_xor(o[g][e], off, 64);
-        }
-    if (row == 0) {
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-#pragma unroll
-            for (int e = 0; e < EPL; ++e) s_o[wave][g][c * EPL + e] = o[g][e];
-            if (c == 0) {
-                s_m[wave][g] = mrun[g];
-                s_l[wave][g] = l[g];
-            }
-        }
+    static constexpr int GROUPS = DT;
+    __device__ static inline int group_dim(int j, int kg) { return 64 * (j / 4) + 16 * kg + 4 * (j % 4); }
+    __device__ static inline f32x4_t group(const f32x4_t (&ot)[DT], int j) {
+        const int t = 4 * (j / 4), e = j % 4;
+        return f32x4_t{ot[t][e], ot[t + 1][e], ot[t + 2][e], ot[t + 3][e]};
     }
-    __syncthreads();
+};
 
-    // merge the waves: thread -> (g, dim) pairs
-    const bool single = nchunks == 1;
-    float *part = a.partial + (((size_t)r * Hkv + h) * a.slots + chunk) * G * (D + 2);
-    for (int i = threadIdx.x; i < G * D; i += blockDim.x) {
-        const int g = i / D, dd = i % D;
-        float M = kNegInf;
+// One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
+// stage + 1024 q (the immediate offset moves source and destination).
+template <int LOADS, typename At>
+__device__ inline void load_page(At at, char *stage) {
 #pragma unroll
-        for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][g]);
-        float Ls = 0.0f, Os = 0.0f;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const float f = s_m[w][g] == kNegInf ? 0.0f : exp2f(s_m[w][g] - M);
-            Ls += s_l[w][g] * f;
-            Os += s_o[w][g][dd] * f;
-        }
-        if (single) {
-            Tr::store(out + (size_t)g * D + dd, Os / Ls);
-        } else {
-            part[(size_t)g * (D + 2) + dd] = Os;
-            if (dd == 0) {
-                part[(size_t)g * (D + 2) + D] = M;
-                part[(size_t)g * (D + 2) + D + 1] = Ls;
-            }
+    for (int q = 0; q < LOADS; q += 4) {
+        lds_void_t *const to = (lds_void_t *)(stage + q * 1024);
+        __builtin_amdgcn_global_load_lds((global_cvoid_t *)at(q), to, 16, 0, kCpolNT);
+        __builtin_amdgcn_global_load_lds((global_cvoid_t *)at(q + 1), to, 16, 1024, kCpolNT);
+        if constexpr (LOADS > 2) {
+            __builtin_amdgcn_global_load_lds((global_cvoid_t *)at(q + 2), to, 16, 2048, kCpolNT);
+            __builtin_amdgcn_global_load_lds((global_cvoid_t *)at(q + 3), to, 16, 3072, kCpolNT);
         }
     }
 }
 
-// ---------------------------------------------------------------------------
-// bf16 path: Q.K^T on the matrix cores.  For one page, v_mfma_f32_16x16x32_bf16
-// computes S^T = Q (16 rows: the G query heads, rest zero) x K^T (16 tokens)
-// in D/32 steps.  In step kk, lane l supplies token l%16 and head dimensions
-// [32 kk + 8 (l/16), +8), so one load instruction reads 64 contiguous bytes of
-// each of the page's 16 key rows; Q is laid out with the same assignment.  The
-// result leaves head 4*(l/16)+i of token l%16 in register i of lane l, so the
-// per-page max and the row sums are 16-lane DPP reductions and every score is
-// exponentiated once.  P.V stays on the vector ALUs in fp32, with the weights
-// exchanged through LDS.
-// ---------------------------------------------------------------------------
-typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
-typedef __attribute__((ext_vector_type(4))) float f32x4_t;
-
-template <int N>
-__device__ inline float dpp_ror(float x) {
-    return __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, x), 0x120 + N, 0xf, 0xf, false));
+// four consecutive outputs o / l (l > 0)
+__device__ inline void store_out(uint16_t *p, const f32x4_t &o, float l) {
+    const float inv = 1.0f / l;                       // (far below the bfloat16 rounding that follows)
+    typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    bf16x4_t x;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) x[e] = (__bf16)(o[e] * inv);
+    *reinterpret_cast<bf16x4_t *>(p) = x;
 }
-// 16-byte load of streamed K data (non-temporal, see stream16).
-__device__ inline uint4 ld16(const uint16_t *p) { return stream16(p); }
-
-// LDS traffic between lanes of one wave: wait for the wave's LDS operations
-// and keep the compiler from moving memory accesses across this point.
-__device__ inline void wave_lds_sync() { __asm__ volatile("s_waitcnt lgkmcnt(0)" ::: "memory"); }
-
-__device__ inline float row_max16(float x) {
-    x = fmaxf(x, dpp_ror<8>(x));
-    x = fmaxf(x, dpp_ror<4>(x));
-    x = fmaxf(x, dpp_ror<2>(x));
-    return fmaxf(x, dpp_ror<1>(x));
-}
-__device__ inline float row_sum16(float x) {
-    x += dpp_ror<8>(x);
-    x += dpp_ror<4>(x);
-    x += dpp_ror<2>(x);
-    return x + dpp_ror<1>(x);
+__device__ inline void store_out(float *p, const f32x4_t &o, float l) {
+    *reinterpret_cast<f32x4_t *>(p) = f32x4_t{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
 }
 
-// Split decode (bf16): one workgroup of kDecodeWaves waves per (KV head,
-// chunk, request); the waves take the chunk's pages round-robin.  Each wave
-// owns one LDS page of keys and one of values, filled by direct-to-LDS loads;
-// as soon as a stage has been read out, the wave requests the same part of its
-// next page, so a page is on its way while softmax and P.V run.  Q waits in
-// LDS.  For G >= kDecodePvmMinG, P.V runs on the matrix cores (S^T = K.Q^T
-// puts P in the B layout; V^T comes by transposed LDS reads); for smaller G on
-// the vector ALUs, each lane owning D/64 head dimensions for all 16 tokens of
-// the page (accumulators G * D / 64 registers).  The waves merge through LDS
-// at the end.
-// MODE 0: decode attention; 1: gp_decode_step with the step's new token (its
-// summary update is in the merge pass); 2: the private tails of gp_decode_attention_shared (a request
-// that reads its group's shared prefix pass covers the pages after the prefix
-// only, and its partials follow the prefix's).
-template <int D, int G, int MODE>
-__global__ __launch_bounds__(64 * kDecodeWaves) __attribute__((amdgpu_waves_per_eu(4))) void decode_split_kernel(
+// MODE 0: decode attention; 1: gp_decode_step with the step's new token (the
+// summary update is in the merge pass); 2: the private tails of
+// gp_decode_attention_shared.
+//
+// Per wave one LDS page of keys and one of values, filled by direct-to-LDS
+// loads, each instruction one contiguous 1 KiB of the head's slice; the keys
+// are refilled as soon as the scores are formed, the values once P.V has read
+// them, and each wait is for exactly the loads it needs.  Sixteen waves per CU
+// (bf16, d = 128) keep the memory busy while some of them compute: the copy of
+// the loads reads 6.7-6.8 TB/s whether or not a wave pauses for 1000 cycles
+// between a page's arrival and its refill; eight waves with two pages each read
+// 6.9 TB/s without the pause and 6.2-6.4 with it.
+template <typename T, int D, int G, int MODE>
+__global__ __launch_bounds__((64 * Page<T, D>::WAVES)) __attribute__((amdgpu_waves_per_eu(Page<T, D>::WAVES >= 8 ? 4 : 2))) void
+decode_kernel(
     DecodeArgs a) {
     constexpr bool STEP = MODE == 1, PREFIX = MODE == 2;
-    constexpr bool PVM = G >= kDecodePvmMinG;   // P.V on the matrix cores (see the page step)
-    constexpr int KK = D / 32;            // MFMA steps per page
-    constexpr int DPL = D / 64;           // head dims per lane in P.V (2 or 1)
-    constexpr int HR = (G + 3) / 4;       // lane rows that carry real heads
-    constexpr int GI = G < 4 ? G : 4;     // heads per lane row
-    constexpr int NW = kDecodeWaves;
+    using Pg = Page<T, D>;
+    constexpr int NW = Page<T, D>::WAVES;
     constexpr int NT = 64 * NW;
-    constexpr int UPP = kPage * D / 8;                // 16-byte units of one page of one head (keys or values)
-    constexpr int STAGE_BYTES = NW * 2 * UPP * 16, MERGE_BYTES = NW * G * D * 4;
-    __shared__ float s_m[NW][G], s_l[NW][G];
-    __shared__ float s_p[NW][kPage][G];
-    __shared__ float s_alpha[NW][G];
-    __shared__ bf16x8_t s_q[KK][4][G];
-    __shared__ int s_ids[kMaxChunkPages];
-    __shared__ __attribute__((aligned(16))) uint16_t s_new[STEP ? 2 : 1][STEP ? D : 8];   // new token K, V
-    // per wave one page of keys and one of values while the pages are read,
-    // then the waves' o for the merge
-    __shared__ __attribute__((aligned(16))) char s_big[STAGE_BYTES > MERGE_BYTES ? STAGE_BYTES : MERGE_BYTES];
-    auto s_o = reinterpret_cast<float (*)[G][D]>(s_big);
+    constexpr int LOADS = Pg::LOADS, DT = Pg::DT;
+    // per wave its pages (keys, values); when they are read, the wave's o goes
+    // where the first keys were
+    constexpr int STAGE = 2 * Pg::BYTES;
+    static_assert(G * D * 4 <= STAGE, "merge buffer");
+    __shared__ __attribute__((aligned(1024))) char s_wave[NW][STAGE];
+    __shared__ float s_ml[NW][G][2];                  // (max, sum) of each wave's open part
+    __shared__ int s_open[NW][3];                     // its request, first (1) and last (2) page flags; request written
 
-    const int h = blockIdx.x, chunk = blockIdx.y, r = blockIdx.z;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int Hkv = a.Hkv, Hq = Hkv * G;
-    const int m_in = a.seq_lens[r];
-    // PREFIX: a request whose prefix pages the prefix pass read starts after
-    // them, in the partial slots after the prefix chunks' (the pass wrote
-    // matched[r] for every request of a group)
-    int base_page = 0, slot0 = 0;
-    bool pmatch = false;
-    int spec_n = 0, spec_pid = -1;                    // PREFIX: page ids requested ahead
-    bool spec_hit = false;
-    if constexpr (PREFIX) {
-        int gsel = -1;
-        for (int g = 0; g < a.ngroups; ++g)
-            if (r >= a.g_first[g] && r < a.g_first[g] + a.g_num[g]) gsel = g;
-        if (gsel >= 0) {                                  // uniform
-            // the prefix pass's test for this request, evaluated here as well
-            const int pp = a.g_pages[gsel];
-            const bool reader = prefix_reader(a, r, pp);
-            const int32_t *row = a.page_table + (size_t)r * a.max_pages;
-            const int32_t *lrow = a.page_table + (size_t)a.g_first[gsel] * a.max_pages;
-            // while the table rows are compared, the page ids of this chunk's
-            // range as it is when the rows match (the usual case) are already
-            // requested: one memory round trip less before the pages
-            if (reader) {
-                const int mt_s = m_in - pp * kPage, nch_s = cdiv(mt_s, a.chunk_pages * kPage);
-                if (mt_s > 0 && chunk < nch_s) {
-                    const int npg_s = cdiv(mt_s, kPage), cs_s = cdiv(npg_s, nch_s);
-                    const int pb = pp + min(npg_s, chunk * cs_s), pe = pp + min(npg_s, chunk * cs_s + cs_s);
-                    spec_n = pe - pb;
-                    if (spec_n <= (int)blockDim.x && tid < spec_n) spec_pid = row[pb + tid];
-                }
-            }
-            bool ok = reader;
-            for (int j = tid; j < pp; j += blockDim.x) ok = ok && row[j] == lrow[j];
-            pmatch = __syncthreads_and(ok);
-            if (pmatch) {
-                base_page = pp;
-                slot0 = cdiv(pp, a.chunk_pages);
-            }
-            spec_hit = pmatch && spec_n > 0 && spec_n <= (int)blockDim.x;
-        }
-    }
-    if (m_in < 0) {                           // held: not in this step's batch
-        record_step(a, r, h, chunk, -1, false, 0);
-        return;
-    }
-    const StepView sv = step_view(a, r, m_in);
-    const int CHUNK = a.chunk_pages * kPage;
+    const int h = blockIdx.x, wg = blockIdx.y;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = uni(tid >> 6);
+    const int n = lane & 15, kg = lane >> 4;
+    const int Hkv = a.Hkv, Hq = Hkv * G, R = a.R;
 
-    const int m = sv.m_attn;
-    const int mt = m - base_page * kPage;         // tokens this pass covers
-    const int nchunks = cdiv(mt, CHUNK);
-    record_step(a, r, h, chunk, m, sv.room, (pmatch || nchunks > 1) ? slot0 + nchunks : 0);
-    uint16_t *out = reinterpret_cast<uint16_t *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-    if (mt == 0) {
-        if (chunk == 0 && !pmatch)
-            for (int i = tid; i < G * D; i += blockDim.x) out[i] = 0;
-        return;
-    }
-    if (chunk >= nchunks) return;
-    // the request's pages split into nchunks nearly equal chunks (the chunk
-    // count is the merge's; equal lengths keep the workgroups' durations even)
-    const int npg = cdiv(mt, kPage), cs = cdiv(npg, nchunks);
-    const int page_begin = base_page + min(npg, chunk * cs);
-    const int page_end = base_page + min(npg, chunk * cs + cs);
-
-    const int n = lane & 15, kg = lane >> 4;          // score layout: token n, key slice kg
-    const int v_off = lane * DPL;                     // P.V: lane owns dims [lane * DPL, +DPL)
-
-    // page ids and Q (MFMA A layout, rows < G) into LDS
-    const int32_t *table = a.page_table + (size_t)r * a.max_pages;
-    if (PREFIX && spec_hit) {
-        // (the same range: the prefix pages matched, as the request assumed)
-        if (tid < page_end - page_begin) s_ids[tid] = spec_pid >= 0 && spec_pid < a.pool_pages ? spec_pid : -1;
-    } else {
-        for (int k = tid; k < page_end - page_begin; k += blockDim.x) {
-            const int pid = table[page_begin + k];
-            s_ids[k] = pid >= 0 && pid < a.pool_pages ? pid : -1;
-        }
-    }
-    const uint16_t *qg = reinterpret_cast<const uint16_t *>(a.q) + ((size_t)r * Hq + (size_t)h * G) * D;
-    if (tid < KK * 4 * G) {
-        const int kk = tid / (4 * G), rem = tid % (4 * G), q_kg = rem / G, q_n = rem % G;
-        s_q[kk][q_kg][q_n] = *reinterpret_cast<const bf16x8_t *>(qg + (size_t)q_n * D + kk * 32 + q_kg * 8);
-    }
-    // gp_decode_step with a new token: the workgroup whose pages hold slot
-    // m_in stages the token's K and V of head h in LDS (its waves take them
-    // from there, not from the cache) and writes them into the cache
-    const int p_new = STEP && sv.room ? sv.m / kPage : -1, slot_new = sv.m % kPage;
-    const bool owns_new = STEP && p_new >= page_begin && p_new < page_end;
-    constexpr int NU16 = D / 8;                       // 16-byte units of one row
-    uint4 nv = make_uint4(0u, 0u, 0u, 0u);
-    if constexpr (STEP) {
-        if (owns_new && tid < 2 * NU16) {
-            const int kvsel = tid / NU16, u = tid % NU16;
-            const uint16_t *src = reinterpret_cast<const uint16_t *>(kvsel ? a.v_new : a.k_new) +
-                                  ((size_t)r * Hkv + h) * D + u * 8;
-            nv = *reinterpret_cast<const uint4 *>(src);
-            *reinterpret_cast<uint4 *>(&s_new[kvsel][u * 8]) = nv;
-        }
-    }
-    __syncthreads();
-    if constexpr (STEP) {
-        if (owns_new && tid < 2 * NU16) {
-            const int kvsel = tid / NU16, u = tid % NU16;
-            const int phys = s_ids[p_new - page_begin];
-            if (phys >= 0) {
-                uint16_t *dst = reinterpret_cast<uint16_t *>(kvsel ? a.v_w : a.k_w) +
-                                (((size_t)phys * Hkv + h) * kPage + slot_new) * D + u * 8;
-                *reinterpret_cast<uint4 *>(dst) = nv;
-            }
-        }
-    }
-
-    float mrun[GI], lrun[GI], o[G][DPL];
-#pragma unroll
-    for (int i = 0; i < GI; ++i) {
-        mrun[i] = kNegInf;
-        lrun[i] = 0.0f;
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g)
-#pragma unroll
-        for (int e = 0; e < DPL; ++e) o[g][e] = 0.0f;
-
-    const uint16_t *kpool = reinterpret_cast<const uint16_t *>(a.k);
-    const uint16_t *vpool = reinterpret_cast<const uint16_t *>(a.v);
-    const size_t head_off = (size_t)h * kPage * D;
-    const size_t page_elems = (size_t)Hkv * kPage * D;
-    uint4 kb[KK];
-    // Keys and values go straight to the wave's two LDS pages (no registers
-    // in flight, so the request for the next page can go out as soon as this
-    // one has been read out), each load instruction one contiguous 64 x
-    // 16-byte run of the page (RPI whole rows).  Keys are swizzled: lane l of
-    // instruction q takes row R = q RPI + l / UPR, unit (l % UPR) ^ (R % UPR),
-    // so that unit u of row R sits at R UPR + (u ^ (R % UPR)) and the 16 rows
-    // a score-layout read touches fall on distinct banks; values keep the row
-    // layout (a P.V read is one whole row).  (Loading the keys in the score
-    // layout itself, sixteen rows of 64 bytes per instruction, reads paged
-    // keys about 7 % slower.)
-    constexpr int UPR = D / 8;                        // 16-byte units per row
-    constexpr int RPI = 64 / UPR;                     // rows per load instruction
-    constexpr int KLD = kPage / RPI;                  // load instructions per page (keys or values)
-    uint4 *kstage = reinterpret_cast<uint4 *>(s_big) + (size_t)wave * 2 * UPP;
-    uint4 *vstage = kstage + UPP;
-    auto load_kv = [&](int phys) {
-        const size_t off = (size_t)phys * page_elems + head_off;
-#pragma unroll
-        for (int q = 0; q < KLD; ++q) {
-            const int R = q * RPI + lane / UPR, u = (lane % UPR) ^ (R % UPR);
-            __builtin_amdgcn_global_load_lds((global_cvoid_t *)(kpool + off + R * D + u * 8),
-                                             (lds_void_t *)(kstage + q * 64), 16, 0, kCpolNT);
-        }
-#pragma unroll
-        for (int q = 0; q < KLD; ++q) {
-            // PVM: values swizzled by fv(R) = 2 (R % (UPR / 2)) for the
-            // transposed reads; otherwise the plain row layout
-            const int R = q * RPI + lane / UPR, u = PVM ? (lane % UPR) ^ (2 * (R % (UPR / 2))) : lane % UPR;
-            __builtin_amdgcn_global_load_lds((global_cvoid_t *)(vpool + off + R * D + u * 8),
-                                             (lds_void_t *)(vstage + q * 64), 16, 0, kCpolNT);
-        }
-    };
-    // once the page has landed: the score-layout key operand of step kk (unit
-    // 4 kk + kg of row n) and this lane's dims of every value row; the stages
-    // are free again when the reads are done
-    auto read_kv = [&](uint32_t (&vw)[kPage]) {
-        __builtin_amdgcn_sched_barrier(0);
-        __builtin_amdgcn_s_waitcnt(kWaitVm0);
-        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-        for (int kk = 0; kk < KK; ++kk) kb[kk] = kstage[n * UPR + ((4 * kk + kg) ^ (n % UPR))];
-#pragma unroll
-        for (int t = 0; t < kPage; ++t) {
-            if constexpr (DPL == 2)
-                vw[t] = reinterpret_cast<const uint32_t *>(vstage)[t * (D / 2) + lane];
-            else
-                vw[t] = reinterpret_cast<const uint16_t *>(vstage)[t * D + lane];
-        }
-        __builtin_amdgcn_s_waitcnt(kWaitLgkm0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-    // One page of the wave: Q.K^T on the matrix cores, then the keys and
-    // values of the wave's next page are requested together (the values into
-    // the other buffer), then softmax and P.V on this page's values.
-    auto page = [&](int p, int &phys) {
-        const int ntok = phys >= 0 ? min(kPage, m - p * kPage) : 0;
-        uint32_t vw[kPage];                          // this lane's dims of the page's value rows
-        if (phys >= 0) {                             // wave-uniform
-            read_kv(vw);
-        } else {
-#pragma unroll
-            for (int t = 0; t < kPage; ++t) vw[t] = 0u;
-        }
-        if constexpr (STEP) {
-            if (p == p_new) {     // wave-uniform: the new token's slot comes from LDS
-                if (n == slot_new) {
-#pragma unroll
-                    for (int kk = 0; kk < KK; ++kk) kb[kk] = *reinterpret_cast<const uint4 *>(&s_new[0][kk * 32 + kg * 8]);
-                }
-                const uint32_t nvv = DPL == 2 ? *reinterpret_cast<const uint32_t *>(&s_new[1][v_off])
-                                              : (uint32_t)s_new[1][v_off];
-#pragma unroll
-                for (int t = 0; t < kPage; ++t) vw[t] = t == slot_new ? nvv : vw[t];
-            }
-        }
-        f32x4_t acc = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (ntok > 0) {
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                bf16x8_t qa = {};
-                if (n < G) qa = s_q[kk][kg][n];
-                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(qa, __builtin_bit_cast(bf16x8_t, kb[kk]), acc, 0, 0, 0);
-            }
-        }
-        const int pn = p + NW;
-        const int phys_next = pn < page_end ? s_ids[pn - page_begin] : -1;
-        if (phys_next >= 0) load_kv(phys_next);
-        const bool valid = n < ntok;
-        float sc[GI], alpha[GI];
-#pragma unroll
-        for (int i = 0; i < GI; ++i) {
-            sc[i] = valid ? acc[i] * a.qscale : kNegInf;
-            const float pm = row_max16(sc[i]);
-            const float mn = fmaxf(mrun[i], pm);
-            alpha[i] = mn == kNegInf ? 1.0f : exp2f(mrun[i] - mn);
-            mrun[i] = mn;
-            sc[i] = mn == kNegInf ? 0.0f : exp2f(sc[i] - mn);
-            lrun[i] = lrun[i] * alpha[i] + sc[i];
-        }
-        // hand the weights and the rescale factors to the P.V layout
-        if (kg < HR) {
-#pragma unroll
-            for (int i = 0; i < GI; ++i) {
-                s_p[wave][n][kg * 4 + i] = sc[i];
-                if (n == 0) s_alpha[wave][kg * 4 + i] = alpha[i];
-            }
-        }
-        wave_lds_sync();
-#pragma unroll
-        for (int g = 0; g < G; ++g) {
-            const float al = s_alpha[wave][g];
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) o[g][e] *= al;
-        }
-#pragma unroll
-        for (int t = 0; t < kPage; ++t) {
-            if (t < ntok) {      // wave-uniform; slots past the last token may hold anything
-                const float v0 = bf16_lo(vw[t]);
-                const float v1 = DPL == 2 ? bf16_hi(vw[t]) : 0.0f;
-#pragma unroll
-                for (int g = 0; g < G; ++g) {
-                    const float pw = s_p[wave][t][g];
-                    o[g][0] = fmaf(pw, v0, o[g][0]);
-                    if constexpr (DPL == 2) o[g][DPL - 1] = fmaf(pw, v1, o[g][DPL - 1]);
-                }
-            }
-        }
-        wave_lds_sync();
-        phys = phys_next;
-    };
-    // PVM (G >= kDecodePvmMinG): S^T = K.Q^T, so that lane (n, kg) holds
-    // tokens 4 kg + e of head n -- the B layout of the P.V product -- and
-    // O^T += V^T.P^T on v_mfma_f32_16x16x16bf16_1k, V^T by transposed LDS
-    // reads, P in two bfloat16 terms (hi + lo carry 16 significant bits): the
-    // per-page P.V costs the matrix cores what it costs at any G, where the
-    // vector-ALU form grows with G.  Heads n >= G of the 16 columns carry zero
-    // queries and are never written.
-    constexpr int DT = D / 16;                        // O^T tiles of 16 dims
-    f32x4_t ot[PVM ? DT : 1];
-    float pm_run = kNegInf, pl_run = 0.0f;            // head n: running max, this lane's share of the sum
-#pragma unroll
-    for (int t = 0; t < (PVM ? DT : 1); ++t) ot[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
-    typedef short bf16x4v_t __attribute__((ext_vector_type(4)));
-    // keys and values of a page go out as two requests here, so that the
-    // keys' stage is refilled as soon as its operands are read and the
-    // values' once P.V has read them
-    auto load_k_only = [&](int phys) {
-        const size_t off = (size_t)phys * page_elems + head_off;
-#pragma unroll
-        for (int q = 0; q < KLD; ++q) {
-            const int R = q * RPI + lane / UPR, u = (lane % UPR) ^ (R % UPR);
-            __builtin_amdgcn_global_load_lds((global_cvoid_t *)(kpool + off + R * D + u * 8),
-                                             (lds_void_t *)(kstage + q * 64), 16, 0, kCpolNT);
-        }
-    };
-    auto load_v_only = [&](int phys) {
-        const size_t off = (size_t)phys * page_elems + head_off;
-#pragma unroll
-        for (int q = 0; q < KLD; ++q) {
-            const int R = q * RPI + lane / UPR, u = (lane % UPR) ^ (2 * (R % (UPR / 2)));
-            __builtin_amdgcn_global_load_lds((global_cvoid_t *)(vpool + off + R * D + u * 8),
-                                             (lds_void_t *)(vstage + q * 64), 16, 0, kCpolNT);
-        }
-    };
-    auto page_pvm = [&](int p, int &phys) {
-        const int ntok = phys >= 0 ? min(kPage, m - p * kPage) : 0;
-        const int pn = p + NW;
-        const int phys_next = pn < page_end ? s_ids[pn - page_begin] : -1;
-        if (phys >= 0) {                              // wave-uniform
-            __builtin_amdgcn_sched_barrier(0);
-            __builtin_amdgcn_s_waitcnt(wait_vm(KLD));     // the keys; the values, requested after them, may be on their way
-            __builtin_amdgcn_sched_barrier(0);
-            u32x4_t kx[KK];
-            uint32_t ka[KK];
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) ka[kk] = lds_addr(kstage + n * UPR + ((4 * kk + kg) ^ (n % UPR)));
-            if constexpr (KK == 4) lds_read16(ka[0], ka[1], ka[2], ka[3], kx[0], kx[1], kx[2], kx[3]);
-            else lds_read16(ka[0], ka[1], kx[0], kx[1]);
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) kb[kk] = __builtin_bit_cast(uint4, kx[kk]);
-            __builtin_amdgcn_sched_barrier(0);
-        }
-        if (phys_next >= 0) load_k_only(phys_next);
-        if constexpr (STEP) {
-            if (p == p_new && n == slot_new) {        // the new token's key comes from LDS
-#pragma unroll
-                for (int kk = 0; kk < KK; ++kk) kb[kk] = *reinterpret_cast<const uint4 *>(&s_new[0][kk * 32 + kg * 8]);
-            }
-        }
-        f32x4_t st = {0.0f, 0.0f, 0.0f, 0.0f};
-        if (ntok > 0) {
-#pragma unroll
-            for (int kk = 0; kk < KK; ++kk) {
-                bf16x8_t qb = {};
-                if (n < G) qb = s_q[kk][kg][n];
-                st = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, kb[kk]), qb, st, 0, 0, 0);
-            }
-        }
-        // online softmax of head n over tokens 4 kg + e
-        float sc[4], ml = kNegInf;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sc[e] = 4 * kg + e < ntok ? st[e] * a.qscale : kNegInf;
-            ml = fmaxf(ml, sc[e]);
-        }
-        ml = fmaxf(ml, __shfl_xor(ml, 16, 64));
-        ml = fmaxf(ml, __shfl_xor(ml, 32, 64));
-        const float mn = fmaxf(pm_run, ml);
-        const float alpha = mn == kNegInf ? 1.0f : exp2f(pm_run - mn);
-        float psum = 0.0f;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            sc[e] = mn == kNegInf ? 0.0f : exp2f(sc[e] - mn);
-            psum += sc[e];
-        }
-        pl_run = pl_run * alpha + psum;
-        pm_run = mn;
-        if (__any(alpha != 1.0f)) {                   // skip while no head's max has moved
-#pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) ot[t][e] *= alpha;
-        }
-        bf16x4v_t phi, plo;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            const __bf16 hb = (__bf16)sc[e];              // round to nearest even
-            phi[e] = __builtin_bit_cast(short, hb);
-            plo[e] = __builtin_bit_cast(short, (__bf16)(sc[e] - (float)hb));   // p - hi is exact in float32
-        }
-        if (ntok > 0) {
-            // V^T tile t as the A operand by transposed reads: lane j of group
-            // kg names row R = 4 kg + j / 4, dims 16 t + 4 (j % 4); lane n
-            // receives tokens 4 kg .. + 3 at dim 16 t + n.  Slots past the last
-            // token may hold anything (0 x inf would reach o), so they read as
-            // zero; the step's new token comes from LDS.
-            const int R = 4 * kg + n / 4, qd = n % 4, fv = 2 * (R % (UPR / 2));
-            const uint32_t vrow = lds_addr(vstage + R * UPR) + (qd & 1) * 8;
-            // the values have landed: only the next page's keys were requested after them
-            __builtin_amdgcn_sched_barrier(0);
-            if (phys_next >= 0) __builtin_amdgcn_s_waitcnt(wait_vm(KLD));
-            else __builtin_amdgcn_s_waitcnt(kWaitVm0);
-            __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-            for (int t0 = 0; t0 < DT; t0 += 4) {
-                u32x2_t vx[4];
-                auto at = [&](int t) { return vrow + ((2 * t + qd / 2) ^ fv) * 16; };
-                lds_read_tr(at(t0), at(t0 + 1), at(t0 + 2), at(t0 + 3), vx[0], vx[1], vx[2], vx[3]);
-#pragma unroll
-                for (int k = 0; k < 4; ++k) {
-                    const int t = t0 + k;
-                    bf16x4v_t vt = __builtin_bit_cast(bf16x4v_t, vx[k]);
-                    if (ntok < kPage) {               // wave-uniform
-#pragma unroll
-                        for (int e = 0; e < 4; ++e)
-                            if (4 * kg + e >= ntok) vt[e] = 0;
-                    }
-                    if constexpr (STEP) {
-                        if (p == p_new && kg == slot_new / 4) vt[slot_new % 4] = (short)s_new[1][16 * t + n];
-                    }
-                    ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t], 0, 0, 0);
-                    ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t], 0, 0, 0);
-                }
-            }
-            __builtin_amdgcn_sched_barrier(0);            // the values' stage is read
-        }
-        if (phys_next >= 0) load_v_only(phys_next);
-        phys = phys_next;
-    };
-    int p = page_begin + wave;
-    int phys = p < page_end ? s_ids[p - page_begin] : -1;
-    if (phys >= 0) load_kv(phys);
-    if constexpr (PVM) {
-        for (; p < page_end; p += NW) page_pvm(p, phys);
-    } else {
-        for (; p < page_end; p += NW) page(p, phys);
-    }
-
-    // merge the waves: per-wave (max, sum) of each head, o of every dim (o
-    // goes where the stages were, once every wave is done with them)
-    if constexpr (PVM) {
-        pl_run += __shfl_xor(pl_run, 16, 64);
-        pl_run += __shfl_xor(pl_run, 32, 64);
-    } else {
-#pragma unroll
-        for (int i = 0; i < GI; ++i) lrun[i] = row_sum16(lrun[i]);
-    }
-    __syncthreads();
-    if constexpr (PVM) {
-        if (n < G) {
-            if (kg == 0) {
-                s_m[wave][n] = pm_run;
-                s_l[wave][n] = pl_run;
-            }
-#pragma unroll
-            for (int t = 0; t < DT; ++t)
-#pragma unroll
-                for (int e = 0; e < 4; ++e) s_o[wave][n][16 * t + 4 * kg + e] = ot[t][e];
-        }
-    } else {
-        if (kg < HR && n == 0) {
-#pragma unroll
-            for (int i = 0; i < GI; ++i) {
-                s_m[wave][kg * 4 + i] = mrun[i];
-                s_l[wave][kg * 4 + i] = lrun[i];
-            }
-        }
-#pragma unroll
-        for (int g = 0; g < G; ++g)
-#pragma unroll
-            for (int e = 0; e < DPL; ++e) s_o[wave][g][v_off + e] = o[g][e];
-    }
-    __syncthreads();
-
-    const bool single = nchunks == 1 && !pmatch;
-    float *part = a.partial + (((size_t)r * Hkv + h) * a.slots + slot0 + chunk) * G * (D + 2);
-    for (int i = tid; i < G * D; i += blockDim.x) {
-        const int g = i / D, dd = i % D;
-        float M = kNegInf;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) M = fmaxf(M, s_m[w][g]);
-        float Ls = 0.0f, Os = 0.0f;
+    // ---- the split: U pages in all, L per wave; the request at the run's start.
+    // Thread t takes request base + t; the prefix sums meet in LDS.  (Rolled up:
+    // the code before the first page is fetched cold by every CU.)
+    __shared__ int s_sum[NW], s_incl[NT], s_len[NT], s_np[NT];
+    auto scan_block = [&](int base, int acc) {        // inclusive sums of the block's requests; its end
+        const int r = min(base + tid, R - 1), sl = a.seq_lens[r], np = a.num_pages[r];
+        const int x = base + tid < R ? req_view<STEP, PREFIX>(a, r, sl, np).n : 0;
+        const int incl = wave_scan(x);
+        if (base > 0) __syncthreads();                // (the previous block has been read)
+        if (lane == 63) s_sum[wave] = incl;
+        __syncthreads();
+        int before = acc, all = acc;
 #pragma unroll
         for (int w = 0; w < NW; ++w) {
-            const float f = s_m[w][g] == kNegInf ? 0.0f : exp2f(s_m[w][g] - M);
-            Ls += s_l[w][g] * f;
-            Os += s_o[w][g][dd] * f;
+            const int t = s_sum[w];
+            if (w < wave) before += t;
+            all += t;
         }
-        if (single) {
-            out[(size_t)g * D + dd] = f32_to_bf16(Ls > 0.0f ? Os / Ls : 0.0f);
-        } else {
-            part[(size_t)g * (D + 2) + dd] = Os;
-            if (dd == 0) {
-                part[(size_t)g * (D + 2) + D] = M;
-                part[(size_t)g * (D + 2) + D + 1] = Ls;
+        s_incl[tid] = before + incl;
+        s_len[tid] = sl;
+        s_np[tid] = np;
+        __syncthreads();
+        return all;
+    };
+    int U = 0;
+    for (int base = 0; base < R; base += NT) U = uni(scan_block(base, U));
+    const int L = max(a.min_run, cdiv(U, a.W * NW));
+    if (wg == a.W - 1) {                              // (the workgroup with the fewest pages)
+        // for the merge pass, per request: tokens attended (-1: held), whether a
+        // token went in, and the partial slots it folds (first, count; count 0:
+        // this pass writes the output); outputs of requests without tokens
+        int acc = 0;
+        for (int base = 0; base < R; base += 64) {
+            const int r = base + lane;
+            const ReqView v = req_view<STEP, PREFIX>(a, min(r, R - 1));
+            const int np = r < R ? v.n : 0, incl = wave_scan(np), a0 = acc + incl - np;
+            acc += __builtin_amdgcn_readlane(incl, 63);
+            if (base / 64 % NW != wave || r >= R) continue;
+            if (h == 0) {
+                const int ws = a0 / L / NW, we = np > 0 ? (a0 + np - 1) / L / NW : ws;
+                a.lens[r] = v.held ? -1 : v.m_attn;
+                a.lens[R + r] = v.room ? 1 : 0;
+                a.lens[2 * R + r] = ws + r;
+                a.lens[3 * R + r] = np > 0 && (we > ws || v.base > 0) ? we - ws + 1 : 0;
+                if (!(PREFIX && v.base > 0)) a.lens[4 * R + r] = 0;   // (else: the wave that begins the request)
+            }
+            if (np == 0 && !v.held) {
+                T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
+                for (int i = 0; i < G * D; i += 4) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
             }
         }
     }
-}
+    if (wg * NW * L >= U) return;                     // (uniform over the workgroup)
 
-// Second pass for requests that span several chunks: one workgroup per
-// (KV head, request) merges the chunks' (max, sum, o) partials.  Running it
-// as its own launch lets the kernel boundary publish the partials; a
-// device-scope fence per workgroup would write back and invalidate the L2 of
-// every XCD thousands of times per step.
-constexpr int kFastMerge = 8;   // chunks a merge folds without staging
-template <typename T, int D, int G>
-__global__ __launch_bounds__(256) void merge_kernel(DecodeArgs a) {
-    using Tr = Traits<T>;
-    constexpr int MAXC = kMaxDecodeChunks + 1;       // partial slots (a shared prefix takes one more)
-    __shared__ float s_f[MAXC][G];                 // exp2(m_k - M) / L per chunk and head
-    __shared__ float s_ml[MAXC][G][2];
-    const int h = blockIdx.x, r = blockIdx.y;
-    const int tid = threadIdx.x;
-    const int kmax = a.max_chunks + (a.ngroups > 0 ? 1 : 0);   // slots any request can fill
-
-    // gp_decode_step, bfloat16: the summaries of query heads [h G, h G + G)
-    // are updated here (Sec. 4.1) rather than in the chunk pass, where the
-    // memory round trip it adds lengthened the workgroups that end the grid.
-    // The slot is requested first, the query and the old values after the
-    // partials (one more round trip at most), and the update is stored after
-    // the output.  A held request, or with a new token one without room, keeps
-    // its summaries, as in the float32 kernel.
-    constexpr bool FOLD = sizeof(T) == 2;
-    constexpr int FE = (G * D + 255) / 256;          // summary elements per thread
-    float f_q[FE], f_s[FE], f_l[FE];
-    float *fS = nullptr;
-    int f_slot = -1;
-    bool f_init = false;
-    if constexpr (FOLD) {
-        if (a.qstate) {
-            f_slot = a.slot_ids[r];
-            f_init = a.init[r] != 0;
+    const int f0 = min((wg * NW + wave) * L, U);
+    const int f1 = min(f0 + L, U);                    // this wave's run [f0, f1) of the flat list
+    int r = -1, a0 = 0, m_in = 0, P_in = 0;           // request at f0, its first page's place in the list, its length
+    for (int base = 0, acc = 0; base < R; base += NT) {
+        if (R > NT) {                                 // (one block is still in LDS)
+            __syncthreads();
+            acc = uni(scan_block(base, acc));
+        }
+        for (int j = 0; j < NT && r < 0 && f0 < f1; j += 64) {
+            const unsigned long long past = __ballot(base + j + lane < R && s_incl[j + lane] > f0);
+            if (past) {
+                const int l = j + uni(__builtin_ctzll(past));
+                r = base + l;
+                m_in = uni(s_len[l]);
+                P_in = uni(s_np[l]);
+                a0 = uni(s_incl[l]) - uni(req_view<STEP, PREFIX>(a, r, m_in, P_in).n);
+            }
         }
     }
-    auto load_fold = [&]() {
-        if constexpr (FOLD) {
-            if (a.qstate && f_slot >= 0 && f_slot < a.M) {
-                const size_t Hq = (size_t)a.Hkv * G;
-                const uint16_t *qp = reinterpret_cast<const uint16_t *>(a.q_pre) + ((size_t)r * Hq + (size_t)h * G) * D;
-                fS = a.qstate + (size_t)f_slot * 2 * Hq * D + (size_t)h * G * D;
-#pragma unroll
-                for (int e = 0; e < FE; ++e) {
-                    const int i = min(tid + 256 * e, G * D - 1);
-                    f_q[e] = bf16_to_f32(qp[i]);
-                    f_s[e] = fS[i];
-                    f_l[e] = fS[Hq * D + i];
+
+    char *const mine = s_wave[wave];
+    const size_t page_bytes = (size_t)Hkv * Pg::BYTES;
+    const char *const kpool = reinterpret_cast<const char *>(a.k) + (size_t)h * Pg::BYTES;
+    const char *const vpool = reinterpret_cast<const char *>(a.v) + (size_t)h * Pg::BYTES;
+    // this lane's offsets in a page slice and in its LDS copy.  (Made opaque on
+    // each page: hoisted out of the loop, their variants for every instruction
+    // would take two dozen registers and push the kernel past the 96 that leave
+    // room for other kernels' waves beside two of its workgroups.)
+    uint32_t ko = Pg::koff(lane), vo = Pg::voff(lane);
+    uint32_t kr = lds_addr(mine) + Pg::kread(n, kg), vr = lds_addr(mine) + Pg::BYTES + Pg::vread(n, kg);
+    auto request_keys = [&](int phys) {
+        const char *src = kpool + (size_t)phys * page_bytes;
+        __asm__ volatile("" : "+v"(ko));
+        load_page<LOADS>([&](int q) { return src + (size_t)((ko ^ Pg::kflip(q)) + (q - q % 4) * 1024u); }, mine);
+    };
+    auto request_values = [&](int phys) {
+        const char *src = vpool + (size_t)phys * page_bytes;
+        __asm__ volatile("" : "+v"(vo));
+        load_page<LOADS>([&](int q) { return src + (size_t)((vo ^ Pg::vflip(q)) + (q - q % 4) * 1024u); }, mine + Pg::BYTES);
+    };
+
+    // ---- one request's part of the run: pages [p, pend) of its covered pages
+    int p = 0, pend = 0, nseg = 0, base = 0, m_attn = 0;
+    bool whole = false;                               // the part begins with the request's first page
+    const int32_t *row = nullptr;
+    int idn = -1;                                     // page id at the cursor, requested ahead
+    auto request_id = [&]() { idn = scalar_load(row, min(max(base + p, 0), a.max_pages - 1)); };
+    // enters request r (uniform) at its covered page `from`; the step's new token
+    // goes into the cache here, before the page that takes it is requested
+    auto enter = [&](const ReqView &v, int from) {
+        base = uni(v.base);
+        nseg = uni(v.n);
+        m_attn = uni(v.m_attn);
+        p = from;
+        pend = min(nseg, f1 - a0);
+        whole = from == 0;
+        row = a.page_table + (size_t)r * a.max_pages;
+        if constexpr (PREFIX) {
+            if (base > 0 && whole) {
+                const int32_t *lead = nullptr;
+                for (int g = 0; g < a.ngroups; ++g)
+                    if (r >= a.g_first[g] && r < a.g_first[g] + a.g_num[g])
+                        lead = a.page_table + (size_t)a.g_first[g] * a.max_pages;
+                bool ok = true;
+                for (int j = lane; j < base; j += 64) ok = ok && row[j] == lead[j];
+                const bool match = __all(ok);
+                if (h == 0 && lane == 0) a.lens[4 * R + r] = match ? 1 : 0;
+                if (!match) p = -base;                // this wave takes the prefix pages too
+            }
+        }
+        if constexpr (STEP) {
+            const int pn = uni(v.m) / kPage, slot = uni(v.m) % kPage;
+            if (uni(v.room) && pn >= p && pn < pend) {
+                constexpr int NU = D * (int)sizeof(T) / 16;          // 16-byte units of one row
+                const int id = scalar_load(row, pn);
+                if (lane < 2 * NU && id >= 0 && id < a.pool_pages) {
+                    const bool isv = lane >= NU;
+                    const int u = isv ? lane - NU : lane;
+                    const u32x4_t x = reinterpret_cast<const u32x4_t *>(
+                        reinterpret_cast<const T *>(isv ? a.v_new : a.k_new) + ((size_t)r * Hkv + h) * D)[u];
+                    reinterpret_cast<u32x4_t *>(reinterpret_cast<T *>(isv ? a.v_w : a.k_w) +
+                                                (((size_t)id * Hkv + h) * kPage + slot) * D)[u] = x;
                 }
+                // (rare: once per request and head) the row is in memory before its page is requested
+                __builtin_amdgcn_s_waitcnt(kWaitVm0);
             }
         }
     };
-    auto fold = [&](int took) {
-        if constexpr (FOLD) {
-            if (fS && (a.k_new == nullptr || took)) {
-                const size_t Hq = (size_t)a.Hkv * G;
-                const double cs_ = 1.0 - a.beta_s, cl_ = 1.0 - a.beta_l;
+    // from page `from` of request r on, the next request that has pages for this
+    // wave (false: none before the run's end); known: m_in and P_in are r's
+    auto seek = [&](int from, bool known) {
+        while (r >= 0 && r < R && a0 < f1) {
+            if (!known) {
+                m_in = scalar_load(a.seq_lens, r);
+                P_in = scalar_load(a.num_pages, r);
+            }
+            known = false;
+            const ReqView v = req_view<STEP, PREFIX>(a, r, m_in, P_in);
+            const int n_ = uni(v.n);
+            if (!v.held && n_ > from) {
+                enter(v, from);
+                request_id();
+                return true;
+            }
+            a0 += n_;
+            from = 0;
+            ++r;
+        }
+        return false;
+    };
+    u32x4_t q[Pg::QREGS];                             // Q of the current request
+    auto load_q = [&](int rr) {
+        const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G + min(n, G - 1)) * D;
 #pragma unroll
-                for (int e = 0; e < FE; ++e) {
-                    const int i = tid + 256 * e;
-                    if (i < G * D) {
-                        fS[i] = f_init ? f_q[e] : ema_step(f_s[e], f_q[e], a.beta_s, cs_);
-                        fS[Hq * D + i] = f_init ? f_q[e] : ema_step(f_l[e], f_q[e], a.beta_l, cl_);
-                    }
+        for (int j = 0; j < Pg::QREGS; ++j) {
+            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + Pg::qdim(j, kg));
+            q[j] = n < G ? x : u32x4_t{};
+        }
+    };
+
+    f32x4_t ot[DT];
+    float mrun, lrun;                                 // head n: running max (log2 units), this lane's share of the sum
+    auto clear = [&]() {
+        mrun = kNegInf;
+        lrun = 0.0f;
+#pragma unroll
+        for (int t = 0; t < DT; ++t) ot[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    };
+    auto part_of = [&](int rr) { return a.partial + ((size_t)h * a.slots + wg + rr) * G * (D + 2); };
+    // the finished part of request rr: its output if the wave has all of it, else its partial
+    auto finish = [&](int rr, bool direct) {
+        const float l = cross_sum(lrun);
+        if (n < G) {
+            if (direct) {
+                T *o = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G + n) * D;
+#pragma unroll
+                for (int j = 0; j < Pg::GROUPS; ++j) {
+                    store_out(o + Pg::group_dim(j, kg), Pg::group(ot, j), l > 0.0f ? l : __builtin_inff());
                 }
+            } else {
+                float *pt = part_of(rr) + (size_t)n * (D + 2);
+#pragma unroll
+                for (int j = 0; j < Pg::GROUPS; ++j) {
+                    const f32x4_t x = Pg::group(ot, j);
+                    float *o = pt + Pg::group_dim(j, kg);
+                    reinterpret_cast<float2 *>(o)[0] = make_float2(x[0], x[1]);
+                    reinterpret_cast<float2 *>(o)[1] = make_float2(x[2], x[3]);
+                }
+                if (kg == 0) *reinterpret_cast<float2 *>(pt + D) = make_float2(mrun, l);
             }
         }
     };
-    if (kmax <= kFastMerge) {
-        // few slots: every thread requests its elements of every slot a
-        // request can fill together with the lengths (one round trip; the
-        // recorded count then decides which slots are folded)
-        constexpr int EPT = (G * D + 255) / 256;     // elements per thread
-        const float *base = a.partial + ((size_t)r * a.Hkv + h) * a.slots * G * (D + 2);
-        float mk[EPT][kFastMerge], lk[EPT][kFastMerge], ok[EPT][kFastMerge];
+
+    // what the wave leaves for the workgroup's merge: the request whose part
+    // reaches the end of its run without being a whole request, whether it holds
+    // the request's first or last page, and the request whose partial it wrote
+    // on the way (at most one: the one its run began in)
+    int open_r = -1, wrote_r = -1;
+    bool open_first = false, open_last = false;
+    // A page on its way: where it is and whose it is.
+    struct Ahead {
+        int phys, r, p, base, m_attn;
+        bool valid, last, first_of, ends;             // last page of the wave's part; part begins / ends the request
+    };
+    // the page at the cursor (r, p), then the cursor to the next page
+    bool more = false;
+    auto take = [&]() {
+        Ahead x;
+        x.valid = more;
+        x.phys = -1;
+        x.r = r;
+        x.p = p;
+        x.base = base;
+        x.m_attn = m_attn;
+        x.last = p + 1 >= pend;
+        x.first_of = whole;
+        x.ends = pend == nseg;
+        if (more) {
+            x.phys = idn >= 0 && idn < a.pool_pages ? idn : -1;
+            if (!x.last) {
+                ++p;
+                request_id();
+            } else {
+                a0 += nseg;
+                ++r;
+                more = seek(0, false);
+            }
+        }
+        return x;
+    };
+    if (f0 < f1) more = seek(f0 - a0, true);
+    if (more) {
+        load_q(r);
+        clear();
+        // cur is computed, nxt takes its place in LDS (the first round only requests)
+        Ahead cur = {-1, 0, 0, 0, 0, false, false, false, false};
+        while (true) {
+            const Ahead nxt = take();
+            const bool has = cur.phys >= 0, has1 = nxt.phys >= 0;
+            const int ntok = min(kPage, cur.m_attn - (cur.base + cur.p) * kPage);
+            f32x4_t sx = {0.0f, 0.0f, 0.0f, 0.0f};
+            if (has) {                                // wave-uniform
+                // the keys: requested after them are the page's values
+                __builtin_amdgcn_sched_barrier(0);
+                __builtin_amdgcn_s_waitcnt(wait_vm(LOADS));
+                __builtin_amdgcn_sched_barrier(0);
+                __asm__ volatile("" : "+v"(kr));
+                sx = Pg::scores(kr, q);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            if (has1) request_keys(nxt.phys);
+            if (has) {
+                // online softmax of head n over tokens 4 kg + e
+                float sc[4], ml = kNegInf;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = min(tid + 256 * e, G * D - 1);
-            const int g = i / D, dd = i % D;
-#pragma unroll
-            for (int k = 0; k < kFastMerge; ++k) {
-                mk[e][k] = kNegInf;
-                lk[e][k] = 0.0f;
-                ok[e][k] = 0.0f;
-                if (k < kmax) {
-                    const float *pp = base + ((size_t)k * G + g) * (D + 2);
-                    mk[e][k] = pp[D];
-                    lk[e][k] = pp[D + 1];
-                    ok[e][k] = pp[dd];
+                for (int e = 0; e < 4; ++e) {
+                    sc[e] = 4 * kg + e < ntok ? sx[e] * a.qscale : kNegInf;
+                    ml = fmaxf(ml, sc[e]);
                 }
-            }
-        }
-        load_fold();
-        const int m = a.lens[r], took = a.lens[a.R + r], nslots = a.lens[2 * a.R + r];
-        if (m < 0) return;
-        if (a.advance && h == 0 && tid == 0 && took) {
-            a.seq_lens_w[r] = m;
-            if (a.positions) a.positions[r] += 1;
-        }
-        if (nslots == 0) {
-            fold(took);
-            return;
-        }
-        T *out = reinterpret_cast<T *>(a.out) + ((size_t)r * a.Hkv * G + (size_t)h * G) * D;
+                const float mn = fmaxf(mrun, cross_max(ml));
+                // arguments are <= 0: the hardware exp2 needs no range fix-up
+                const float alpha = mn == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(mrun - mn);
+                float psum = 0.0f;
 #pragma unroll
-        for (int e = 0; e < EPT; ++e) {
-            const int i = tid + 256 * e;
-            float M = kNegInf;
-#pragma unroll
-            for (int k = 0; k < kFastMerge; ++k)
-                if (k < nslots) M = fmaxf(M, mk[e][k]);
-            float L = 0.0f, Os = 0.0f;
-#pragma unroll
-            for (int k = 0; k < kFastMerge; ++k) {
-                // slots past the count hold whatever an earlier call left
-                if (k < nslots) {
-                    const float f = mk[e][k] == kNegInf ? 0.0f : exp2f(mk[e][k] - M);
-                    L += lk[e][k] * f;
-                    Os += ok[e][k] * f;
+                for (int e = 0; e < 4; ++e) {
+                    sc[e] = mn == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(sc[e] - mn);
+                    psum += sc[e];
                 }
-            }
-            if (i < G * D) Tr::store(out + i, L > 0.0f ? Os / L : 0.0f);
-        }
-        fold(took);
-        return;
-    }
-    // tokens attended and partial slots, as the chunk pass recorded them
-    // (-1: held; 0 slots: the chunk pass wrote the output)
-    load_fold();
-    const int m = a.lens[r];
-    if (m < 0) return;
-    const int took = a.lens[a.R + r];
-    if (a.advance && h == 0 && threadIdx.x == 0 && took) {
-        // gp_decode_step: the request took the step's token
-        a.seq_lens_w[r] = m;
-        if (a.positions) a.positions[r] += 1;
-    }
-    const int nchunks = a.lens[2 * a.R + r];
-    if (nchunks == 0) {
-        fold(took);
-        return;
-    }
-    const int Hq = a.Hkv * G;
-    T *out = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-    const float *base = a.partial + ((size_t)r * a.Hkv + h) * a.slots * G * (D + 2);
-    if (nchunks <= kFastMerge) {
-        // few chunks: every thread loads all it needs at once (one round trip,
-        // the (max, sum) of a head are the same address for a whole wave) and
-        // folds them itself
-        for (int i = tid; i < G * D; i += blockDim.x) {
-            const int g = i / D, dd = i % D;
-            float mk[kFastMerge], lk[kFastMerge], ok[kFastMerge];
+                lrun = lrun * alpha + psum;
+                mrun = mn;
+                if (__any(alpha != 1.0f)) {           // skip while no head's max has moved
 #pragma unroll
-            for (int k = 0; k < kFastMerge; ++k) {
-                mk[k] = kNegInf;
-                lk[k] = 0.0f;
-                ok[k] = 0.0f;
-                if (k < nchunks) {
-                    const float *pp = base + ((size_t)k * G + g) * (D + 2);
-                    mk[k] = pp[D];
-                    lk[k] = pp[D + 1];
-                    ok[k] = pp[dd];
+                    for (int t = 0; t < DT; ++t)
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) ot[t][e] *= alpha;
                 }
+                // the values: requested after them are the next page's keys
+                __builtin_amdgcn_sched_barrier(0);
+                if (has1) __builtin_amdgcn_s_waitcnt(wait_vm(LOADS));
+                else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                __builtin_amdgcn_sched_barrier(0);
+                __asm__ volatile("" : "+v"(vr));
+                Pg::weigh(vr, sc, ntok, ot, kg);
+                __builtin_amdgcn_sched_barrier(0);
             }
-            float M = kNegInf;
-#pragma unroll
-            for (int k = 0; k < kFastMerge; ++k) M = fmaxf(M, mk[k]);
-            float L = 0.0f, Os = 0.0f;
-#pragma unroll
-            for (int k = 0; k < kFastMerge; ++k) {
-                const float f = mk[k] == kNegInf ? 0.0f : exp2f(mk[k] - M);
-                L += lk[k] * f;
-                Os += ok[k] * f;
+            if (has1) request_values(nxt.phys);
+            if (cur.valid && cur.last) {
+                const bool all = cur.first_of && cur.ends;        // the wave has the whole request
+                if (!nxt.valid) {
+                    open_first = cur.first_of;
+                    open_last = cur.ends;
+                    if (all && cur.base == 0) finish(cur.r, true);
+                    else open_r = cur.r;
+                    break;
+                }
+                finish(cur.r, all && cur.base == 0);
+                if (!cur.first_of) wrote_r = cur.r;
+                load_q(nxt.r);
+                clear();
             }
-            Tr::store(out + (size_t)g * D + dd, L > 0.0f ? Os / L : 0.0f);
+            cur = nxt;
         }
-        fold(took);
-        return;
     }
-    // all (max, sum) pairs at once, then one thread per head folds them
-    for (int t = tid; t < nchunks * G && t < MAXC * G; t += blockDim.x) {
-        const int k = t / G, g = t % G;
-        s_ml[k][g][0] = base[((size_t)k * G + g) * (D + 2) + D];
-        s_ml[k][g][1] = base[((size_t)k * G + g) * (D + 2) + D + 1];
+
+    // ---- the workgroup's merge of the open parts
+    if (open_r >= 0) {
+        const float l = cross_sum(lrun);
+        if (n < G) {
+            float *o = reinterpret_cast<float *>(mine) + n * D;
+#pragma unroll
+            for (int j = 0; j < Pg::GROUPS; ++j)
+                *reinterpret_cast<f32x4_t *>(o + Pg::group_dim(j, kg)) = Pg::group(ot, j);
+            if (kg == 0) {
+                s_ml[wave][n][0] = mrun;
+                s_ml[wave][n][1] = l;
+            }
+        }
+    }
+    if (lane == 0) {
+        s_open[wave][0] = open_r;
+        s_open[wave][1] = (open_first ? 1 : 0) | (open_last ? 2 : 0);
+        s_open[wave][2] = wrote_r;
     }
     __syncthreads();
-    const int nc = nchunks < MAXC ? nchunks : MAXC;
-    if (tid < G) {
-        float M = kNegInf;
-        for (int k = 0; k < nc; ++k) M = fmaxf(M, s_ml[k][tid][0]);
-        float L = 0.0f;
-        for (int k = 0; k < nc; ++k) {
-            const float f = s_ml[k][tid][0] == kNegInf ? 0.0f : exp2f(s_ml[k][tid][0] - M);
-            s_f[k][tid] = f;
-            L += s_ml[k][tid][1] * f;
+    for (int w0 = 0; w0 < NW;) {
+        const int rr = uni(s_open[w0][0]);
+        if (rr < 0) {
+            ++w0;
+            continue;
         }
-        const float inv = 1.0f / L;
-        for (int k = 0; k < nc; ++k) s_f[k][tid] *= inv;
+        int w1 = w0 + 1;                              // waves [w0, w1) left parts of request rr open
+        while (w1 < NW && uni(s_open[w1][0]) == rr) ++w1;
+        // the wave after them may have written the rest of rr as this workgroup's partial
+        const bool more_ = w1 < NW && uni(s_open[w1][2]) == rr;
+        const bool all = (uni(s_open[w0][1]) & 1) && (more_ || (uni(s_open[w1 - 1][1]) & 2));
+        bool direct = all;
+        if constexpr (PREFIX) direct = all && uni(req_view<STEP, PREFIX>(a, rr).base) == 0;
+        float *pt = part_of(rr);
+        T *out = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
+        constexpr int EPT = (G * D + NT - 1) / NT;
+        float M[EPT], Ls[EPT], Os[EPT];
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int i = min(tid + e * NT, G * D - 1), g = i / D, dd = i % D;
+            const float *q = pt + (size_t)g * (D + 2);
+            const float m1 = more_ ? q[D] : kNegInf;
+            M[e] = m1;
+            for (int w = w0; w < w1; ++w) M[e] = fmaxf(M[e], s_ml[w][g][0]);
+            Ls[e] = Os[e] = 0.0f;
+            for (int w = w0; w < w1; ++w) {
+                const float mw = s_ml[w][g][0];
+                const float fw = mw == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(mw - M[e]);
+                Ls[e] += s_ml[w][g][1] * fw;
+                Os[e] += reinterpret_cast<const float *>(s_wave[w])[i] * fw;
+            }
+            // (last, as if that wave had left its part open)
+            const float f1_ = m1 == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m1 - M[e]);
+            if (more_) {
+                Ls[e] += q[D + 1] * f1_;
+                Os[e] += q[dd] * f1_;
+            }
+        }
+        if (more_ && !direct) __syncthreads();         // every thread has read the partial that is replaced
+#pragma unroll
+        for (int e = 0; e < EPT; ++e) {
+            const int i = tid + e * NT, g = i / D, dd = i % D;
+            if (i >= G * D) continue;
+            if (direct) {
+                Traits<T>::store(out + i, Ls[e] > 0.0f ? Os[e] / Ls[e] : 0.0f);
+            } else {
+                pt[(size_t)g * (D + 2) + dd] = Os[e];
+                if (dd == 0) *reinterpret_cast<float2 *>(pt + (size_t)g * (D + 2) + D) = make_float2(M[e], Ls[e]);
+            }
+        }
+        w0 = w1;
     }
-    __syncthreads();
-    for (int i = tid; i < G * D; i += blockDim.x) {
-        const int g = i / D, dd = i % D;
-        float Os = 0.0f;
-#pragma unroll 8
-        for (int k = 0; k < nc; ++k) Os += base[((size_t)k * G + g) * (D + 2) + dd] * s_f[k][g];
-        Tr::store(out + (size_t)g * D + dd, Os);
-    }
-    fold(took);
 }
 
 // ---------------------------------------------------------------------------
@@ -1184,11 +839,17 @@ __global__ __launch_bounds__(256) void merge_kernel(DecodeArgs a) {
 // same test).
 // Bound: HBM on the tails; the prefix pages are read once per block of
 // requests instead of once per request.
-typedef short bf16x4s_t __attribute__((ext_vector_type(4)));
-
 // The pass stages kPrefixBatch pages (keys and values) per round and keeps
 // two rounds in LDS.
 constexpr int kPrefixBatch = 4;
+
+// Whether request r may read a prefix pass of pp pages: not held, more pages
+// and tokens than the prefix, within its table (the chunk pass makes the same
+// test); both passes also require the leader's page ids on every prefix page.
+__device__ inline bool prefix_reader(const DecodeArgs &a, int r, int pp) {
+    const int m = a.seq_lens[r], P = a.num_pages[r];
+    return m > pp * kPage && P > pp && P <= a.max_pages && m <= P * kPage;
+}
 
 template <int D, int G>
 __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a) {
@@ -1206,7 +867,7 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
     constexpr int IPW = NB * IPP / NW;    // load instructions per wave and round
     static_assert((NB * IPP) % NW == 0 && UPP % 64 == 0, "staging layout");
     __shared__ __attribute__((aligned(16))) uint4 s_stage[2][NB][2][UPP];   // [round % 2][page][keys, values]
-    __shared__ int s_ids[kMaxChunkPages];
+    __shared__ int s_ids[kMaxPrefixSlotPages];
     __shared__ int s_match[RPB];
 
     const int h = blockIdx.x, c = blockIdx.y, blk = blockIdx.z;
@@ -1217,9 +878,8 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
     while (gi + 1 < a.ngroups && blk >= a.g_blk0[gi + 1]) ++gi;
     const int first = a.g_first[gi], nreq = a.g_num[gi], ppages = a.g_pages[gi];
     const int r0 = first + (blk - a.g_blk0[gi]) * RPB;
-    // the prefix split evenly over its cdiv(ppages, chunk_pages) slots (cs <=
-    // chunk_pages; the last slot is never empty)
-    const int nps = cdiv(ppages, a.chunk_pages), cs = cdiv(ppages, nps);
+    // the prefix split evenly over its slots (cs <= kMaxPrefixSlotPages pages each)
+    const int cs = cdiv(ppages, a.g_slots[gi]);
     const int p_begin = c * cs, p_end = min(ppages, p_begin + cs);
     const int Hkv = a.Hkv, Hq = Hkv * G;
     const int32_t *lead = a.page_table + (size_t)first * a.max_pages;
@@ -1369,7 +1029,7 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
     lrun += __shfl_xor(lrun, 16, 64);
     lrun += __shfl_xor(lrun, 32, 64);
     if (rowq) {
-        float *part = a.partial + (((size_t)(r0 + jq) * Hkv + h) * a.slots + c) * G * (D + 2) +
+        float *part = a.prefix + (((size_t)(r0 + jq) * Hkv + h) * a.pslots + c) * G * (D + 2) +
                       (size_t)(n % G) * (D + 2);
 #pragma unroll
         for (int t = 0; t < DT; ++t) *reinterpret_cast<f32x4_t *>(part + 16 * t + 4 * kg) = o[t];
@@ -1380,39 +1040,178 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
     }
 }
 
+// ------------------------------------------------------------------- merge --
+// Second pass: one workgroup per (KV head, request) folds the (max, sum, o)
+// partials of a request that spans workgroups (or reads a prefix pass).
+// Running it as its own launch lets the kernel boundary publish the partials;
+// a device-scope fence per workgroup would write back and invalidate the L2 of
+// every XCD thousands of times per step.  A thread holds pairs of dims and
+// folds every NS-th slot, eight slots' loads in flight; with few (KV head,
+// request) pairs the workgroups are larger, so that more slots are in flight
+// (one request of a long context has dozens).
+//
+// gp_decode_step: the summaries of query heads [h G, h G + G) are updated here
+// (Sec. 4.1) rather than in the chunk pass, where the memory round trip it adds
+// lengthened the workgroups that end the grid.  The slot is requested first,
+// the query and the old values with the partials' bookkeeping, and the update
+// is stored after the output.  A held request, or with a new token one without
+// room, keeps its summaries.
+template <typename T, int D, int G, int NT>
+__global__ __launch_bounds__(NT) void merge_kernel(DecodeArgs a) {
+    using Tr = Traits<T>;
+    constexpr int GD2 = G * D / 2;                   // pairs of output dims
+    constexpr int EP = (GD2 + NT - 1) / NT;          // pairs per thread
+    constexpr int NS = GD2 < NT ? NT / GD2 : 1;      // threads per pair
+    constexpr int BATCH = EP > 1 ? 4 : 8;            // slots in flight per thread and pair
+    static_assert(GD2 % NT == 0 || NT % GD2 == 0, "thread layout");
+    __shared__ float4 s_red[NS > 1 ? NT : 1];
+    const int h = blockIdx.x, r = blockIdx.y;
+    const int tid = threadIdx.x;
+    const int R = a.R, Hq = a.Hkv * G;
+    constexpr int FE = (G * D + NT - 1) / NT;        // summary elements per thread
+    float f_q[FE], f_s[FE], f_l[FE];
+    float *fS = nullptr;
+    int f_slot = -1;
+    bool f_init = false;
+    if (a.qstate) {
+        f_slot = a.slot_ids[r];
+        f_init = a.init[r] != 0;
+    }
+    const int m = a.lens[r], took = a.lens[R + r], first = a.lens[2 * R + r], cnt = a.lens[3 * R + r];
+    const bool pre = a.ngroups > 0 && a.lens[4 * R + r] != 0;
+    if (m < 0) return;                               // held
+    if (a.qstate && f_slot >= 0 && f_slot < a.M) {
+        const T *qp = reinterpret_cast<const T *>(a.q_pre) + ((size_t)r * Hq + (size_t)h * G) * D;
+        fS = a.qstate + (size_t)f_slot * 2 * Hq * D + (size_t)h * G * D;
+#pragma unroll
+        for (int e = 0; e < FE; ++e) {
+            const int i = min(tid + NT * e, G * D - 1);
+            f_q[e] = Tr::load(qp + i);
+            f_s[e] = fS[i];
+            f_l[e] = fS[(size_t)Hq * D + i];
+        }
+    }
+    if (a.advance && h == 0 && tid == 0 && took) {   // the request took the step's token
+        a.seq_lens_w[r] = m;
+        if (a.positions) a.positions[r] += 1;
+    }
+    if (cnt > 0) {
+        int npre = 0;
+        if (pre)
+            for (int g = 0; g < a.ngroups; ++g)
+                if (r >= a.g_first[g] && r < a.g_first[g] + a.g_num[g]) npre = a.g_slots[g];
+        const int total = npre + cnt;
+        const float *pp = a.prefix + ((size_t)r * a.Hkv + h) * a.pslots * G * (D + 2);
+        const float *pt = a.partial + ((size_t)h * a.slots + first) * G * (D + 2);
+        const int sg = NS > 1 ? tid / GD2 : 0;
+        float M[EP], Ls[EP], Ox[EP], Oy[EP];
+#pragma unroll
+        for (int e = 0; e < EP; ++e) {
+            const int i = 2 * (NS > 1 ? tid % GD2 : tid + e * NT);
+            const int off = (i / D) * (D + 2);
+            M[e] = kNegInf;
+            Ls[e] = Ox[e] = Oy[e] = 0.0f;
+            for (int k0 = sg; k0 < total; k0 += NS * BATCH) {
+                float2 ml[BATCH], o[BATCH];
+#pragma unroll
+                for (int b = 0; b < BATCH; ++b) {
+                    const int k = min(k0 + b * NS, total - 1);
+                    const float *q = (k < npre ? pp + (size_t)k * G * (D + 2) : pt + (size_t)(k - npre) * G * (D + 2)) + off;
+                    ml[b] = *reinterpret_cast<const float2 *>(q + D);
+                    o[b] = *reinterpret_cast<const float2 *>(q + i % D);
+                }
+                float mn = M[e];
+#pragma unroll
+                for (int b = 0; b < BATCH; ++b)
+                    if (k0 + b * NS < total) mn = fmaxf(mn, ml[b].x);
+                const float f0 = M[e] == kNegInf ? 0.0f : exp2f(M[e] - mn);
+                Ls[e] *= f0;
+                Ox[e] *= f0;
+                Oy[e] *= f0;
+                M[e] = mn;
+#pragma unroll
+                for (int b = 0; b < BATCH; ++b) {
+                    if (k0 + b * NS < total && ml[b].x != kNegInf) {
+                        const float f = exp2f(ml[b].x - mn);
+                        Ls[e] += ml[b].y * f;
+                        Ox[e] += o[b].x * f;
+                        Oy[e] += o[b].y * f;
+                    }
+                }
+            }
+        }
+        if constexpr (NS > 1) {
+            s_red[tid] = make_float4(M[0], Ls[0], Ox[0], Oy[0]);
+            __syncthreads();
+            if (tid < GD2) {
+#pragma unroll
+                for (int k = 1; k < NS; ++k) M[0] = fmaxf(M[0], s_red[tid + k * GD2].x);
+                Ls[0] = Ox[0] = Oy[0] = 0.0f;
+#pragma unroll
+                for (int k = 0; k < NS; ++k) {
+                    const float4 x = s_red[tid + k * GD2];
+                    const float f = x.x == kNegInf ? 0.0f : exp2f(x.x - M[0]);
+                    Ls[0] += x.y * f;
+                    Ox[0] += x.z * f;
+                    Oy[0] += x.w * f;
+                }
+            }
+        }
+        T *out = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
+        if (NS == 1 || tid < GD2) {
+#pragma unroll
+            for (int e = 0; e < EP; ++e) {
+                const int i = 2 * (NS > 1 ? tid : tid + e * NT);
+                Tr::store(out + i, Ls[e] > 0.0f ? Ox[e] / Ls[e] : 0.0f);
+                Tr::store(out + i + 1, Ls[e] > 0.0f ? Oy[e] / Ls[e] : 0.0f);
+            }
+        }
+    }
+    if (fS && (a.k_new == nullptr || took)) {
+        const double cs_ = 1.0 - a.beta_s, cl_ = 1.0 - a.beta_l;
+#pragma unroll
+        for (int e = 0; e < FE; ++e) {
+            const int i = tid + NT * e;
+            if (i < G * D) {
+                fS[i] = f_init ? f_q[e] : ema_step(f_s[e], f_q[e], a.beta_s, cs_);
+                fS[(size_t)Hq * D + i] = f_init ? f_q[e] : ema_step(f_l[e], f_q[e], a.beta_l, cl_);
+            }
+        }
+    }
+}
+
 template <typename T, int D>
-hipError_t launch_g(int G, const DecodeArgs &a, dim3 grid, int stages, hipStream_t s) {
-    dim3 mgrid(a.Hkv, a.R);
+hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
+    const dim3 grid(a.Hkv, a.W), mgrid(a.Hkv, a.R);
     constexpr bool bf16 = sizeof(T) == 2;
+    constexpr int NT = 64 * Page<T, D>::WAVES;
     // the step variant with a new token and the tails of the shared-prefix
     // decode are their own instantiations, so plain decode attention carries
     // none of their code (a step call's summary update is in the merge pass:
     // without a new token its chunk pass is plain decode attention)
     const int mode = a.ngroups > 0 ? 2 : a.k_new != nullptr ? 1 : 0;
     // the merge pass also advances the lengths when a token went in, updates
-    // the summaries of a bfloat16 step call, and folds the prefix partials of a
-    // shared-prefix call
+    // the summaries of a step call, and folds the prefix partials of a
+    // shared-prefix call; with one workgroup per KV head no request spans two
     const bool chunks = stages & GP_DECODE_CHUNKS, prefix = (stages & GP_DECODE_PREFIX) && mode == 2,
                merge = (stages & GP_DECODE_MERGE) &&
-                       (a.max_chunks > 1 || (a.k_new && a.advance) || mode == 2 || (bf16 && a.qstate));
-    // prefix pass grid: (KV head, prefix chunk, request block)
-    int max_pc = 0;
-    for (int g = 0; g < a.ngroups; ++g) max_pc = max(max_pc, cdiv(a.g_pages[g], a.chunk_pages));
-    const dim3 pgrid(a.Hkv, max(max_pc, 1), max(a.g_blk0[a.ngroups], 1));
+                       (a.W > 1 || (a.k_new && a.advance) || mode == 2 || a.qstate);
+    const bool wide = (int64_t)a.Hkv * a.R < kWideMerge;
+    // prefix pass grid: (KV head, prefix slot, request block)
+    int max_ps = 1;
+    for (int g = 0; g < a.ngroups; ++g) max_ps = max(max_ps, a.g_slots[g]);
+    const dim3 pgrid(a.Hkv, max_ps, max(a.g_blk0[a.ngroups], 1));
     switch (G) {
-#define GP_CASE(GG)                                                  \
-    case GG:                                                         \
-        if (prefix && bf16)                                          \
-            prefix_kernel<D, GG><<<pgrid, 64 * kPrefixWaves, 0, s>>>(a); \
-        if (chunks && bf16 && mode == 2)                             \
-            decode_split_kernel<D, GG, 2><<<grid, 64 * kDecodeWaves, 0, s>>>(a); \
-        else if (chunks && bf16 && mode == 1)                        \
-            decode_split_kernel<D, GG, 1><<<grid, 64 * kDecodeWaves, 0, s>>>(a); \
-        else if (chunks && bf16)                                     \
-            decode_split_kernel<D, GG, 0><<<grid, 64 * kDecodeWaves, 0, s>>>(a); \
-        else if (chunks)                                             \
-            decode_kernel<float, D, GG><<<grid, 256, 0, s>>>(a);     \
-        if (merge) merge_kernel<T, D, GG><<<mgrid, 256, 0, s>>>(a);  \
+#define GP_CASE(GG)                                                                \
+    case GG:                                                                       \
+        if constexpr (bf16) {                                                      \
+            if (prefix) prefix_kernel<D, GG><<<pgrid, 64 * kPrefixWaves, 0, s>>>(a); \
+            if (chunks && mode == 2) decode_kernel<T, D, GG, 2><<<grid, NT, 0, s>>>(a); \
+        }                                                                          \
+        if (chunks && mode == 1) decode_kernel<T, D, GG, 1><<<grid, NT, 0, s>>>(a); \
+        if (chunks && mode == 0) decode_kernel<T, D, GG, 0><<<grid, NT, 0, s>>>(a); \
+        if (merge && wide) merge_kernel<T, D, GG, 1024><<<mgrid, 1024, 0, s>>>(a); \
+        if (merge && !wide) merge_kernel<T, D, GG, 256><<<mgrid, 256, 0, s>>>(a);  \
         break;
         GP_CASE(1) GP_CASE(2) GP_CASE(4) GP_CASE(8)
 #undef GP_CASE
@@ -1424,13 +1223,9 @@ hipError_t launch_g(int G, const DecodeArgs &a, dim3 grid, int stages, hipStream
 }  // namespace
 
 hipError_t launch_decode(gp_dtype_t dt, int D, int G, const DecodeArgs &a, int stages, hipStream_t s) {
-    // the KV heads of one chunk are neighbours in dispatch order: they read the
-    // head slices of the same pages at about the same time
-    dim3 grid(a.Hkv, a.max_chunks, a.R);
     if (dt == GP_BF16)
-        return D == 128 ? launch_g<uint16_t, 128>(G, a, grid, stages, s)
-                        : launch_g<uint16_t, 64>(G, a, grid, stages, s);
-    return D == 128 ? launch_g<float, 128>(G, a, grid, stages, s) : launch_g<float, 64>(G, a, grid, stages, s);
+        return D == 128 ? launch_g<uint16_t, 128>(G, a, stages, s) : launch_g<uint16_t, 64>(G, a, stages, s);
+    return D == 128 ? launch_g<float, 128>(G, a, stages, s) : launch_g<float, 64>(G, a, stages, s);
 }
 
 }  // namespace gp

@@ -12,20 +12,25 @@
 namespace gp {
 
 constexpr int kPage = 16;                 // tokens per page
-#ifndef GP_DECODE_CHUNK_PAGES
-#define GP_DECODE_CHUNK_PAGES 64
+// waves per decode workgroup: one LDS page (keys and values of one head, 4 to
+// 16 KiB) per wave, 64 KiB at most
+constexpr int decode_waves(int elem, int D) { return elem * D > 256 ? 4 : 8; }
+#ifndef GP_DECODE_WORKGROUPS
+#define GP_DECODE_WORKGROUPS 512
 #endif
-#ifndef GP_DECODE_PVM_MIN_G
-#define GP_DECODE_PVM_MIN_G 4
+constexpr int kDecodeWorkgroups = GP_DECODE_WORKGROUPS;    // decode workgroups of a call, all KV heads, about
+#ifndef GP_DECODE_MIN_RUN
+#define GP_DECODE_MIN_RUN 2
 #endif
-constexpr int kDecodePvmMinG = GP_DECODE_PVM_MIN_G;   // GQA ratios whose decode P.V runs on the matrix cores
-constexpr int kDecodeChunkPages = GP_DECODE_CHUNK_PAGES;   // pages per decode work item, about (split-K)
-constexpr int kMaxChunkPages = 64;                         // pages per decode chunk at most (LDS id table)
-#ifndef GP_DECODE_WAVES
-#define GP_DECODE_WAVES 8
+constexpr int kDecodeMinRun = GP_DECODE_MIN_RUN;           // pages a decode wave takes at least
+#ifndef GP_WIDE_MERGE
+#define GP_WIDE_MERGE 64
 #endif
-constexpr int kDecodeWaves = GP_DECODE_WAVES;              // waves per decode workgroup (bf16 path)
-constexpr int kMaxDecodeChunks = 128;                      // chunks one request may span
+constexpr int kWideMerge = GP_WIDE_MERGE; // (KV head, request) pairs below which the merge takes 1024 threads each
+constexpr int kPrefixSlotPages = 64;      // pages of one partial slot of a shared prefix, about
+constexpr int kMaxPrefixSlotPages = 128;  // and at most (LDS id table)
+constexpr int kMaxDecodePages = 8192;     // table width the decode calls accept
+constexpr size_t kScratchBytes = size_t(8) << 20;   // static scratch of gp_decode_attention_noalloc
 constexpr int kMaxBoundaryPages = 4096;                    // table width the boundary calls accept
 constexpr int kStatBlock = 64;            // candidate tokens per softmax-statistics block (one wave)
 constexpr int kProbChunk = 1024;          // tokens per weight/score work item
@@ -50,34 +55,54 @@ __device__ inline float ema_step(float prev, float x, double beta, double one_mi
 }
 
 struct DecodeWs {
-    size_t partial, lens, total;
-    int max_chunks, chunk_pages, slots;
+    size_t partial, lens, prefix, total;
+    size_t plain;                 // bytes a call without a shared prefix touches
+    int W, slots, pslots;
 };
 
-// Work split of decode attention: every request is cut into chunks of about
-// kDecodeChunkPages pages (sized so that max_pages splits evenly); when a
-// request spans several chunks a second kernel merges their partial results.
-__host__ __device__ inline int decode_chunk_pages(int max_pages) {
-    int chunks = cdiv(max_pages, kDecodeChunkPages);
-    if (chunks > kMaxDecodeChunks) chunks = kMaxDecodeChunks;
-    return cdiv(max_pages, chunks);
+// Bytes of a workspace with one (max, sum, o) partial per 64 pages of table
+// width and one more, and three words per request: what
+// gp_decode_attention_noalloc compares with its scratch.
+__host__ __device__ inline size_t decode_chunked_bytes(int R, int Hq, int D, int max_pages) {
+    const int chunks = cdiv(max_pages, cdiv(max_pages, cdiv(max_pages, 64)));
+    return align_up((size_t)R * (chunks + 1) * Hq * (D + 2) * sizeof(float)) + align_up((size_t)R * 3 * sizeof(int32_t));
 }
 
-__host__ __device__ inline DecodeWs decode_ws(int R, int Hq, int Hkv, int D, int max_pages) {
+// Work split of decode attention (see decode_kernel): W workgroups per KV head
+// take equal runs of the batch's pages; partial slot (workgroup + request).
+// W: kDecodeWorkgroups over all KV heads, the two that each CU holds, so that
+// every workgroup is there from the start and pays for its way to the first
+// page (lengths, page id, page: 3-4 us) once; fewer if the widest batch of this
+// shape has fewer runs of kDecodeMinRun pages.  With 512 / 1024 / 2048
+// workgroups: 40 short requests and a new token 44.0 / 46.9 / 53 us, Qwen3-8B
+// layer of 64 requests 96.6 / 97.4 / 99.2, 256 requests 482 / 486 / 490.  Runs of
+// two pages at least: one request of 6001 tokens 13.6 us against 16.2 with one.
+__host__ __device__ inline DecodeWs decode_ws(int R, int Hq, int Hkv, int D, int max_pages, int waves) {
     DecodeWs w;
-    const int G = Hq / Hkv;
-    w.chunk_pages = decode_chunk_pages(max_pages);
-    w.max_chunks = cdiv(max_pages, w.chunk_pages);
+    const size_t unit = (size_t)Hq * (D + 2) * sizeof(float);          // one slot of every KV head
+    w.W = cdiv(kDecodeWorkgroups, Hkv);
+    const int64_t most = (int64_t)R * max_pages;
+    if (most < (int64_t)w.W * waves * kDecodeMinRun) w.W = (int)((most + waves * kDecodeMinRun - 1) / (waves * kDecodeMinRun));
+    // a batch that the static scratch takes keeps fitting it
+    const size_t lens = align_up((size_t)R * 5 * sizeof(int32_t));
+    if (decode_chunked_bytes(R, Hq, D, max_pages) <= kScratchBytes) {
+        const int64_t fit = (int64_t)((kScratchBytes - lens - kAlign) / unit) - R;
+        if (w.W > fit) w.W = (int)fit;
+    }
+    if (w.W < 1) w.W = 1;
+    w.slots = w.W + R;
+    // partial slots of a shared prefix per request
+    const int chunks = cdiv(max_pages, cdiv(max_pages, cdiv(max_pages, kPrefixSlotPages)));
+    w.pslots = chunks > 1 ? chunks - 1 : 1;
     size_t off = 0;
-    // partial slots per (request, KV head): the chunks of the request, plus one
-    // more for a shared prefix (its chunks have the decode chunk size, so a
-    // request of a prefix group needs at most one slot more than its pages)
-    w.slots = w.max_chunks + 1;
-    w.partial = off;    // float: [R][Hkv][slots][G][D + 2] (o, max, sum)
-    off = align_up(off + (size_t)R * Hkv * w.slots * G * (D + 2) * sizeof(float));
-    w.lens = off;       // int32: [R] tokens attended (-1: held), [R] token appended (0/1),
-                        //        [R] partial slots the merge folds (0: none)
-    off = align_up(off + (size_t)R * 3 * sizeof(int32_t));
+    w.partial = off;    // float: [Hkv][slots][G][D + 2] (o, max, sum)
+    off = align_up(off + unit * w.slots);
+    w.lens = off;       // int32, each [R]: tokens attended (-1: held), token appended (0/1), first partial
+                        // slot, slots the merge folds (0: none), prefix pass read (0/1)
+    off += lens;
+    w.plain = off;
+    w.prefix = off;     // float: [R][Hkv][pslots][G][D + 2], partials of a shared prefix
+    off = align_up(off + unit * R * w.pslots);
     w.total = off;
     return w;
 }
@@ -175,15 +200,15 @@ struct DecodeArgs {
     const void *k_new, *v_new;    // [R][Hkv][D]; nullptr: no token
     int32_t *seq_lens_w, *positions;
     int advance;
-    float *partial;
-    int32_t *lens;                // [R] tokens attended (-1: held), [R] appended flags, [R] merge slots
+    float *partial, *prefix;      // workspace regions (DecodeWs)
+    int32_t *lens;
     // shared-prefix decode (gp_decode_attention_shared): requests
     // [g_first, g_first + g_num) share the first g_pages pages of g_first's
     // table; workgroup blocks [g_blk0[g], g_blk0[g + 1]) of the prefix pass
     int ngroups;
     int g_first[kMaxPrefixGroups], g_num[kMaxPrefixGroups], g_pages[kMaxPrefixGroups];
-    int g_blk0[kMaxPrefixGroups + 1];
-    int R, Hkv, max_pages, pool_pages, max_chunks, chunk_pages, slots;
+    int g_blk0[kMaxPrefixGroups + 1], g_slots[kMaxPrefixGroups];
+    int R, Hkv, max_pages, pool_pages, W, min_run, slots, pslots;
     float qscale;   // scale * log2(e)
 };
 

@@ -97,3 +97,133 @@ def test_append_layers(dtype, layers, hq, hkv, d, offset):
     assert torch.equal(qstate.cpu(), want_q.float())
     assert ps.seq_lens.cpu().tolist() == want_len
     assert positions.cpu().tolist() == [r + want_len[r] - lens[r] for r in range(R)]
+
+
+# ------------------------------------------------------------------ decode --
+#
+# Decode attention splits the batch's pages into equal runs, one per wave,
+# whatever requests they belong to: requests that end inside a run, span waves,
+# workgroups or whole blocks of the split's scan, empty and held ones between.
+
+def _reference(kc, vc, table, lens, q, scale):
+    """Attention of every request over its first lens[r] tokens, float64 on the CPU."""
+    R, Hq, d = q.shape
+    Hkv = kc.shape[1]
+    G = Hq // Hkv
+    out = torch.zeros(R, Hq, d, dtype=torch.float64)
+    k64, v64, q64 = kc.cpu().double(), vc.cpu().double(), q.cpu().double()
+    for r, m in enumerate(lens):
+        if m <= 0:
+            continue
+        ids = table[r, :-(-m // 16)].long()
+        K = k64[ids].transpose(0, 1).reshape(Hkv, -1, d)[:, :m]
+        V = v64[ids].transpose(0, 1).reshape(Hkv, -1, d)[:, :m]
+        z = scale * torch.matmul(q64[r].view(Hkv, G, d), K.transpose(1, 2).contiguous())
+        out[r] = torch.matmul(torch.softmax(z, -1), V).view(Hq, d)
+    return out
+
+
+def _check(got, want, dtype, what):
+    """Half a step of the output type, and float32 sums: 1e-5 of the row's largest value."""
+    got, tol = got.cpu().double(), 1e-5 * want.abs().amax(-1, keepdim=True)
+    if dtype == torch.bfloat16:
+        tol = tol + want.abs() * 2.0 ** -8
+    bad = ((got - want).abs() > tol + 1e-30) | ~torch.isfinite(got)
+    assert not bad.any(), f"{what}: rows {sorted(set(bad.nonzero()[:, 0].tolist()))[:8]}"
+
+
+def _decode_case(dtype, hq, hkv, d, lens, spare=0, seed=0):
+    gen = torch.Generator().manual_seed(seed)
+    npages = [-(-max(m, 0) // 16) + (r % 3 == 1) for r, m in enumerate(lens)]
+    R, width = len(lens), max(max(npages), 1) + spare
+    pool, table = _paged(R, width, npages, gen)
+    # pages that nobody holds, and slots past a length, are NaN: they must not be read
+    kc = torch.full((pool, hkv, 16, d), float("nan"), dtype=dtype)
+    vc = kc.clone()
+    for r, m in enumerate(lens):
+        for p in range(-(-max(m, 0) // 16)):
+            t = min(16, m - 16 * p)
+            kc[table[r, p], :, :t] = torch.randn(hkv, t, d, generator=gen).to(dtype)
+            vc[table[r, p], :, :t] = torch.randn(hkv, t, d, generator=gen).to(dtype)
+    q = torch.randn(R, hq, d, generator=gen).to(dtype)
+    kv = gp.KVLayer(kc.to(DEV), vc.to(DEV))
+    return kv, table, npages, pool, q.to(DEV)
+
+
+SPLITS = {
+    "one_token": [1],
+    "one_page_edges": [15, 16, 17, 0, 1, 33],
+    "one_request": [4099],
+    "a_run_each": [32] * 40,
+    "mixed": [0, 700, 3, 0, 0, 2500, 16, 48, 1, 1600, 0],
+    "past_a_scan_block": [(r * 37) % 50 for r in range(1100)],
+}
+
+
+@pytest.mark.parametrize("name", list(SPLITS))
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 8, 2, 128), (torch.bfloat16, 3, 3, 64),
+                                            (torch.float32, 8, 1, 128), (torch.float32, 4, 2, 64)])
+def test_decode_split(name, dtype, hq, hkv, d):
+    lens = SPLITS[name]
+    _say(f"decode split {name} {dtype} heads {hq}/{hkv} d {d}")
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=5)
+    ps = _state(table, npages, lens, pool)
+    ws = gp.workspace(gp.GP_OP_DECODE, len(lens), 0, hq, hkv, d, table.shape[1], dtype)
+    scale = d ** -0.5
+    out = torch.full_like(q, float("nan"))
+    gp.gp_decode_attention(kv, ps, q, scale, out, ws)
+    want = _reference(kv.k, kv.v, table, lens, q, scale)
+    _check(out, want, dtype, "decode")
+    # the same batch in two launches and without a workspace: the same bytes
+    slots = -(-table.shape[1] // 64) + 1                    # what the static scratch is compared with
+    fits = len(lens) * slots * hq * (d + 2) * 4 < 8_000_000
+    for how in ("stages", "noalloc") if fits else ("stages",):
+        again = torch.full_like(q, float("nan"))
+        if how == "stages":
+            gp.gp_decode_attention_stages(kv, ps, q, scale, again, gp.GP_DECODE_CHUNKS, ws)
+            gp.gp_decode_attention_stages(kv, ps, q, scale, again, gp.GP_DECODE_MERGE, ws)
+        else:
+            gp.gp_decode_attention_noalloc(kv, ps, q, scale, again)
+        torch.cuda.synchronize()
+        assert torch.equal(again.view(torch.uint8), out.view(torch.uint8)), how
+    # held requests keep their place: nobody else's output changes
+    held = [r for r in range(0, len(lens), 3) if lens[r] > 0]
+    for r in held:
+        ps.seq_lens[r] = -lens[r] - 1
+    again = torch.full_like(q, 7.0)
+    gp.gp_decode_attention(kv, ps, q, scale, again, ws)
+    torch.cuda.synchronize()
+    keep = torch.tensor([r not in held for r in range(len(lens))], device=DEV)
+    assert torch.equal(again[keep], out[keep]) and bool((again[~keep] == 7.0).all())
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(16, 2, 128), (4, 4, 64), (8, 2, 64)])
+@pytest.mark.parametrize("prefix", [1, 5, 70])
+def test_decode_shared_split(hq, hkv, d, prefix):
+    """Members with the whole prefix, with one page of it replaced (first,
+    middle, last), shorter than the prefix, exactly as long, one token longer,
+    held; and requests outside the group."""
+    _say(f"shared decode split heads {hq}/{hkv} d {d} prefix {prefix}")
+    dtype, P = torch.bfloat16, prefix
+    tails = [40, 1, 0, 17, 300, 33, 64, 2000, 16]
+    lens = [16 * P + t for t in tails] + [max(16 * P - 3, 1), 77]
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=3, seed=prefix)
+    R = len(lens)
+    k, v = kv.k.cpu(), kv.v.cpu()
+    for r in range(1, R - 1):                              # the group: all but the last request
+        keep = {3: 0, 4: P // 2, 5: P - 1}.get(r, -1)      # a page of its own
+        for p in range(min(P, -(-lens[r] // 16))):
+            if p != keep:
+                table[r, p] = table[0, p]
+    kv = gp.KVLayer(k.to(DEV), v.to(DEV))
+    lens[6] = -lens[6] - 1                                 # held
+    ps = _state(table, npages, lens, pool)
+    scale = d ** -0.5
+    ws = gp.workspace(gp.GP_OP_DECODE, R, 0, hq, hkv, d, table.shape[1], dtype)
+    out = torch.full_like(q, 7.0)
+    gp.gp_decode_attention_shared(kv, ps, q, scale, out, [(0, R - 1, P)], ws)
+    torch.cuda.synchronize()
+    want = _reference(kv.k, kv.v, table, lens, q, scale)
+    assert bool((out[6] == 7.0).all())
+    out[6] = 0.0
+    _check(out, want, dtype, "shared decode")
