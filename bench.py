@@ -13,8 +13,8 @@ replayed K / 5 times (``--graph-steps S`` sets the steps per graph; ``--eager``
 launches every call directly).  Decode attention reads
 a snapshot of the request metadata (written by the restore, in the same
 launch), so scoring, selection and the decision (which updates the live
-metadata) run on a second stream beside it; the summary update runs before
-the fork (``--layout``); the compaction, which moves cached rows, waits for
+metadata) run on a second stream beside it, after the summary update
+(``--layout``); the compaction, which moves cached rows, waits for
 both (``--serial`` runs everything on one stream, decode on the live
 metadata).
 
@@ -80,7 +80,7 @@ def parse():
     ap.add_argument("--eager", action="store_true", help="launch every call directly (no HIP graphs)")
     ap.add_argument("--graph-steps", type=int, default=5,
                     help="steps captured per HIP graph (a divisor of --steps is used)")
-    ap.add_argument("--layout", default="summaries-first",
+    ap.add_argument("--layout", default="boundary-first",
                     choices=["boundary-first", "decode-first", "summaries-first"],
                     help="capture order of the two branches of a step (see step())")
     ap.add_argument("--serial", action="store_true",

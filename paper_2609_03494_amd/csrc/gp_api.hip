@@ -3,6 +3,7 @@
 // then enqueues its kernels on the caller's stream and returns.
 #include <math.h>
 
+#include <algorithm>
 #include <mutex>
 
 #include "gp_internal.h"
@@ -233,6 +234,7 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
     a.max_pages = ps->max_pages;
     a.pool_pages = kv->pool_pages;
     a.W = w.W;
+    a.W1 = std::max(1, std::min(w.W, kDecodeResident / kv->num_kv_heads));
     a.min_run = kDecodeMinRun;
     a.slots = w.slots;
     a.pslots = w.pslots;

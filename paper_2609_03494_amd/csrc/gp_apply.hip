@@ -12,12 +12,13 @@
 //           before their owner reads them, and record which pages of the table
 //           row are shared (refcount > 1).
 //  decide   one workgroup.  Delta from the integer working-set counts per
-//           request in parallel; then one thread walks the requests in list
-//           order over LDS-resident data to hand out pages from the free stack
-//           (grow: one page; compress with a shared prefix: one page per shared
-//           page); then grows are applied, compressing requests get their new
-//           resident length, and shared pages are replaced by private ones, the
-//           old references dropped (pages reaching zero are listed).
+//           request in parallel; then pages are handed out from the free stack
+//           in list order (grow: one page; compress with a shared prefix: one
+//           page per shared page), by a prefix sum or, when the stack may run
+//           short, one thread's walk; then grows are applied, compressing
+//           requests get their new resident length, and shared pages are
+//           replaced by private ones (a wave per request), the old references
+//           dropped (pages reaching zero are listed).
 //  compact  per (K or V x KV head x layer, chunk of 256 slots, request): reads every row
 //           that moves (the border rows from the saved copy), then writes it to
 //           its new slot; in the shift layout rows move down by at most two
@@ -217,7 +218,7 @@ __device__ void select_tokens(const ApplyArgs &a, int i, int h, int l, int P, in
 // SHRINK: the Shrink policy's variant, which also selects the 32 tokens a
 // shrink would evict
 template <int D, int E, bool SHRINK>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))) void pre_kernel(ApplyArgs a, LayerTable lt) {
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(SHRINK ? 4 : 5))) void pre_kernel(ApplyArgs a, LayerTable lt) {
     __builtin_amdgcn_s_setprio(3);   // issue ahead of co-resident decode waves
     __shared__ int s_n;
     const int x = blockIdx.y, i = blockIdx.z;
@@ -350,18 +351,24 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
 // wants to shrink.
 enum { F_BOUNDARY = 1, F_GROW = 2, F_SHRINK = 4, F_SKIPPED = 8 };
 
-__global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
+// LDS per boundary request (dynamic: a few KB for the usual handful of events,
+// so that the kernel finds room beside decode attention's workgroups; sized for
+// kMaxBnd events it took 70 KB and had to wait for decode's drain).
+struct DecideReq {
+    unsigned long long D;   // sum of K^S - K^L (two's complement)
+    int P, flags;
+    int nsh, nsh_last;      // shared pages to replace; whether the last page is one of them
+    int dec, pop;
+};
+
+constexpr int kDecideThreads = 512;   // (two waves per SIMD: it starts beside two decode workgroups)
+__global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
     __builtin_amdgcn_s_setprio(3);   // issue ahead of co-resident decode waves
-    __shared__ int s_P[kMaxBnd];
-    __shared__ int s_flags[kMaxBnd];
-    __shared__ int s_nsh[kMaxBnd];     // shared pages to replace (after the decision)
-    __shared__ int s_nsh_last[kMaxBnd];  // whether the last page is one of them
-    __shared__ int s_dec[kMaxBnd];
-    __shared__ int s_pop[kMaxBnd];
-    __shared__ long long s_cnt[4];
-    __shared__ unsigned long long s_D[kMaxBnd];     // sum of K^S - K^L (two's complement)
+    extern __shared__ DecideReq s_rq[];
+    __shared__ unsigned long long s_cnt[4];
+    __shared__ int s_wsum[kDecideThreads / 64];
     __shared__ int s_fc0, s_popped;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int Rb = a.Rb;
 
     // The free count, this thread's first boundary request with its page
@@ -375,9 +382,10 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
     const int m_first = tid < Rb && a.R > 0 ? a.seq_lens[rc_first] : -1;
     const int nshc_first = tid < Rb * a.npc ? a.nshc[tid] : 0;
     for (int i = tid; i < Rb; i += blockDim.x) {
-        s_D[i] = 0;
-        s_nsh[i] = 0;
+        s_rq[i].D = 0;
+        s_rq[i].nsh = 0;
     }
+    if (tid < 4) s_cnt[tid] = 0;
     if (tid == 0) s_fc0 = fc < 0 ? 0 : (fc > a.pool_pages ? a.pool_pages : fc);
     __syncthreads();
     // The per-(layer, KV head) counts and the shared-page counts of every
@@ -388,11 +396,11 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
     for (int e = tid; e < Rb * LH; e += blockDim.x) {
         const int i = e / LH, l = e % LH / a.Hkv, h = e % a.Hkv;
         const int32_t *kc = a.k_counts + (((size_t)l * Rb + i) * a.Hkv + h) * 2;
-        atomicAdd(&s_D[i], (unsigned long long)((long long)kc[0] - (long long)kc[1]));
+        atomicAdd(&s_rq[i].D, (unsigned long long)((long long)kc[0] - (long long)kc[1]));
     }
     for (int e = tid; e < Rb * a.npc; e += blockDim.x) {
         const int v = e == tid ? nshc_first : a.nshc[e];
-        if (v) atomicAdd(&s_nsh[e / a.npc], v);
+        if (v) atomicAdd(&s_rq[e / a.npc].nsh, v);
     }
     __syncthreads();
 
@@ -410,8 +418,8 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
                 flags = F_BOUNDARY;
                 bool grow, shrink = false;
                 if (P >= 2) {
-                    wanted_action(a, i, P, (long long)s_D[i], grow, shrink, dl);
-                    nsh = s_nsh[i];
+                    wanted_action(a, i, P, (long long)s_rq[i].D, grow, shrink, dl);
+                    nsh = s_rq[i].nsh;
                     last_shared = a.shflag[(size_t)i * a.max_pages + P - 1];
                 } else {
                     grow = a.policy == GP_POLICY_FIXED ? P < a.fixed_pages : true;
@@ -422,65 +430,101 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
             }
         }
         a.delta[i] = dl;
-        s_P[i] = P;
-        s_flags[i] = flags;
-        s_nsh[i] = nsh;
-        s_nsh_last[i] = last_shared;
+        s_rq[i].P = P;
+        s_rq[i].flags = flags;
+        s_rq[i].nsh = nsh;
+        s_rq[i].nsh_last = last_shared;
     }
     __syncthreads();
 
-    if (tid == 0) {
-        const int fc0 = s_fc0;
-        int popped = 0;
-        long long cnt[4] = {0, 0, 0, 0};
-        for (int i = 0; i < Rb; ++i) {
-            const int P = s_P[i], fl = s_flags[i];
-            int dec = GP_NOT_BOUNDARY, pop = 0;
-            if (fl & F_BOUNDARY) {
-                const bool want = (fl & F_GROW) != 0, shrink = (fl & F_SHRINK) != 0;
-                const int avail = fc0 - popped;
-                const bool can_grow = avail > a.reserve && P < a.max_pages;
-                // a shrink keeps pages [0, P - 1) only: the last page needs no copy
-                const int nsh = shrink ? s_nsh[i] - s_nsh_last[i] : s_nsh[i];
-                if (want && can_grow) {
-                    dec = GP_GROW;
-                    pop = popped;
-                    popped += 1;
-                } else if (P <= 1 || nsh > avail || (fl & F_SKIPPED)) {
-                    // (a request the selection skipped as a certain grow has
-                    // no eviction lists: it is left as it is)
-                    dec = GP_PREEMPT;
-                } else {
-                    dec = shrink ? GP_SHRINK : (want ? GP_FALLBACK : GP_COMPRESS);
-                    pop = popped;
-                    popped += nsh;
-                    s_nsh[i] = nsh;
-                }
-                cnt[dec == GP_SHRINK ? GP_COMPRESS : dec] += 1;   // a shrink counts as a compression
-            }
-            s_dec[i] = dec;
-            s_pop[i] = pop;
+    // The action of request i with `avail` pages on the stack, and the pages it pops.
+    auto act = [&](int i, int avail, int &pop) -> int {
+        const DecideReq &q = s_rq[i];
+        pop = 0;
+        if (!(q.flags & F_BOUNDARY)) return GP_NOT_BOUNDARY;
+        const bool want = (q.flags & F_GROW) != 0, shrink = (q.flags & F_SHRINK) != 0;
+        // a shrink keeps pages [0, P - 1) only: the last page needs no copy
+        const int nsh = shrink ? q.nsh - q.nsh_last : q.nsh;
+        if (want && avail > a.reserve && q.P < a.max_pages) {
+            pop = 1;
+            return GP_GROW;
         }
-        s_popped = popped;
-        for (int k = 0; k < 4; ++k) s_cnt[k] = cnt[k];
+        // (a request the selection skipped as a certain grow has no eviction
+        // lists: it is left as it is)
+        if (q.P <= 1 || nsh > avail || (q.flags & F_SKIPPED)) return GP_PREEMPT;
+        pop = nsh;
+        return shrink ? GP_SHRINK : (want ? GP_FALLBACK : GP_COMPRESS);
+    };
+    auto settle = [&](int i, int dec, int pop, int popped) {
+        s_rq[i].dec = dec;
+        s_rq[i].pop = popped;
+        if (dec != GP_GROW && dec != GP_PREEMPT && dec != GP_NOT_BOUNDARY) s_rq[i].nsh = pop;
+        // (a shrink counts as a compression)
+        if (dec != GP_NOT_BOUNDARY) atomicAdd(&s_cnt[dec == GP_SHRINK ? GP_COMPRESS : dec], 1ull);
+    };
+    // In list order each request pops from what the earlier ones left.  If the
+    // stack covers all of them at once (what every request pops with no one
+    // before it, and reserve pages over), nobody goes short, and the places in
+    // the stack are a prefix sum; else thread 0 walks the list.
+    {
+        const int fc = s_fc0;
+        const int per = cdiv(Rb, (int)blockDim.x), i0 = min(tid * per, Rb), i1 = min(i0 + per, Rb);
+        int mine = 0;
+        for (int i = i0; i < i1; ++i) {
+            int pop;
+            act(i, fc, pop);
+            mine += pop;
+        }
+        int incl = mine;
+        for (int off = 1; off < 64; off <<= 1) {
+            const int y = __shfl_up(incl, off, 64);
+            if (lane >= off) incl += y;
+        }
+        if (lane == 63) s_wsum[wave] = incl;
+        __syncthreads();
+        int before = incl - mine, total = 0;
+#pragma unroll
+        for (int w = 0; w < kDecideThreads / 64; ++w) {
+            const int t = s_wsum[w];
+            if (w < wave) before += t;
+            total += t;
+        }
+        if ((long long)fc - total >= (long long)a.reserve) {
+            for (int i = i0; i < i1; ++i) {
+                int pop;
+                const int dec = act(i, fc, pop);
+                settle(i, dec, pop, before);
+                before += pop;
+            }
+            if (tid == 0) s_popped = total;
+        } else if (tid == 0) {
+            int popped = 0;
+            for (int i = 0; i < Rb; ++i) {
+                int pop;
+                const int dec = act(i, fc - popped, pop);
+                settle(i, dec, pop, popped);
+                popped += pop;
+            }
+            s_popped = popped;
+        }
     }
     __syncthreads();
 
     const int fc0 = s_fc0;
     for (int i = tid; i < Rb; i += blockDim.x) {
-        const int dec = s_dec[i], P = s_P[i];
+        const int dec = s_rq[i].dec, P = s_rq[i].P;
         const int r = a.bnd[i];
         const bool moves = compressing(dec) || dec == GP_SHRINK;
         a.decisions[i] = dec;
         int32_t *rq = a.req + (size_t)i * RQ_STRIDE;
         rq[RQ_R] = r;
         rq[RQ_P] = P;
-        rq[RQ_FLAGS] = s_flags[i];
-        rq[RQ_NSH] = moves ? s_nsh[i] : 0;
-        rq[RQ_POP] = s_pop[i];
+        rq[RQ_FLAGS] = s_rq[i].flags;
+        rq[RQ_NSH] = moves ? s_rq[i].nsh : 0;
+        rq[RQ_POP] = s_rq[i].pop;
         rq[RQ_DEC] = dec;
         if (dec == GP_GROW) {
-            const int pid = a.free_list[fc0 - 1 - s_pop[i]];
+            const int pid = a.free_list[fc0 - 1 - s_rq[i].pop];
             a.page_table[(size_t)r * a.max_pages + P] = pid;
             if (pid >= 0 && pid < a.pool_pages) a.refcount[pid] = 1;
             a.num_pages[r] = P + 1;
@@ -498,39 +542,34 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
         a.hdr[HDR_FC0] = fc0;
         a.hdr[HDR_FC1] = fc0 - s_popped;
         *a.free_count = fc0 - s_popped;
-        for (int k = 0; k < 4; ++k) a.counters[k] += s_cnt[k];
+        for (int k = 0; k < 4; ++k) a.counters[k] += (long long)s_cnt[k];
     }
 
-    // Requests whose table row changes: the old row is kept for the copy; a
-    // private page replaces each shared page that stays (ranked by logical
-    // page) and the old reference is dropped; a shrink also drops the last
-    // page.  Pages whose count reaches zero are listed.
-    __shared__ int s_scan[1024];
-    for (int i = 0; i < Rb; ++i) {
-        const int dec = s_dec[i];
+    // Requests whose table row changes, one wave each: the old row is kept for
+    // the copy; a private page replaces each shared page that stays (ranked by
+    // logical page) and the old reference is dropped; a shrink also drops the
+    // last page.  Pages whose count reaches zero are listed.  (The whole
+    // workgroup on one request after the other, with a barrier per scan step,
+    // took 3 us per request: 64 us for the kernel at 18 compressing requests
+    // with a shared prefix.)
+    for (int i = wave; i < Rb; i += (int)(blockDim.x >> 6)) {
+        const int dec = s_rq[i].dec;
         const bool shrink = dec == GP_SHRINK;
-        if (!(compressing(dec) && s_nsh[i] > 0) && !shrink) continue;      // uniform
-        const int r = a.bnd[i], P = s_P[i];
+        if (!(compressing(dec) && s_rq[i].nsh > 0) && !shrink) continue;      // wave-uniform
+        const int r = a.bnd[i], P = s_rq[i].P, pop = s_rq[i].pop;
         const int keep = shrink ? P - 1 : P;
         int32_t *row = a.page_table + (size_t)r * a.max_pages;
         int base = 0;
-        for (int j0 = 0; j0 < P; j0 += 1024) {
-            const int j = j0 + tid;
-            const int sh = j < keep ? a.shflag[(size_t)i * a.max_pages + j] : 0;
-            s_scan[tid] = sh;
-            __syncthreads();
-            for (int off = 1; off < 1024; off <<= 1) {
-                const int y = tid >= off ? s_scan[tid - off] : 0;
-                __syncthreads();
-                s_scan[tid] += y;
-                __syncthreads();
-            }
+        for (int j0 = 0; j0 < P; j0 += 64) {
+            const int j = j0 + lane;
+            const bool sh = j < keep && a.shflag[(size_t)i * a.max_pages + j] != 0;
+            const unsigned long long ms = __ballot(sh);
             if (j < P) {
                 const int old = row[j];
                 a.old_table[(size_t)i * a.max_pages + j] = old;
                 if (sh) {
-                    const int k = base + s_scan[tid] - 1;
-                    const int pid = a.free_list[fc0 - 1 - s_pop[i] - k];
+                    const int k = base + __popcll(ms & ((1ull << lane) - 1));
+                    const int pid = a.free_list[fc0 - 1 - pop - k];
                     row[j] = pid;
                     if (pid >= 0 && pid < a.pool_pages) a.refcount[pid] = 1;
                 }
@@ -542,8 +581,7 @@ __global__ __launch_bounds__(1024) void decide_kernel(ApplyArgs a) {
                     }
                 }
             }
-            base += s_scan[1023];
-            __syncthreads();
+            base += __popcll(ms);
         }
     }
 }
@@ -728,7 +766,7 @@ hipError_t launch_de(const ApplyArgs &a, const LayerTable &lt, int stages, hipSt
         else
             pre_kernel<D, E, false><<<gpre, kSelThreads, 0, s>>>(a, lt);
     }
-    if (stages & kStageDecide) decide_kernel<<<1, 1024, 0, s>>>(a);
+    if (stages & kStageDecide) decide_kernel<<<1, kDecideThreads, (size_t)a.Rb * sizeof(DecideReq), s>>>(a);
     if (stages & kStageCompact) compact_kernel<D, E><<<gcomp, 256, 0, s>>>(a, lt);
     return hipGetLastError();
 }

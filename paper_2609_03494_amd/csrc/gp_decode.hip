@@ -3,11 +3,10 @@
 //
 // Work split.  Per KV head the batch is one flat list of pages: the pages of
 // request 0, then of request 1, and so on (U pages, read off the lengths by
-// every wave itself).  The waves of a.W workgroups take equal runs of L =
-// max(kMinRun, ceil(U / waves)) consecutive pages of it, whatever requests they
-// belong to, so every workgroup of the grid has the same amount of work and
-// none is empty as long as there are pages; the next page's keys and values are
-// on their way across request boundaries too.  A wave that meets the end of a
+// every workgroup itself).  The waves take equal runs of L consecutive pages of
+// it, whatever requests they belong to, so all workgroups have the same amount
+// of work; the next page's keys and values are on their way across request
+// boundaries too.  A wave that meets the end of a
 // request writes that request's result (or its partial, if the request began
 // before the wave's run) and goes on with the next; at the end the workgroup
 // merges the runs its waves left open, and requests that span workgroups are
@@ -450,7 +449,7 @@ decode_kernel(
     };
     int U = 0;
     for (int base = 0; base < R; base += NT) U = uni(scan_block(base, U));
-    const int L = max(a.min_run, cdiv(U, a.W * NW));
+    const int L = max(max(a.min_run, cdiv(U, a.W * NW)), min(kDecodeShortRun, cdiv(U, a.W1 * NW)));
     if (wg == a.W - 1) {                              // (the workgroup with the fewest pages)
         // for the merge pass, per request: tokens attended (-1: held), whether a
         // token went in, and the partial slots it folds (first, count; count 0:

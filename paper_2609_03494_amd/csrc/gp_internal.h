@@ -16,13 +16,15 @@ constexpr int kPage = 16;                 // tokens per page
 // 16 KiB) per wave, 64 KiB at most
 constexpr int decode_waves(int elem, int D) { return elem * D > 256 ? 4 : 8; }
 #ifndef GP_DECODE_WORKGROUPS
-#define GP_DECODE_WORKGROUPS 512
+#define GP_DECODE_WORKGROUPS 768
 #endif
 constexpr int kDecodeWorkgroups = GP_DECODE_WORKGROUPS;    // decode workgroups of a call, all KV heads, about
 #ifndef GP_DECODE_MIN_RUN
 #define GP_DECODE_MIN_RUN 2
 #endif
 constexpr int kDecodeMinRun = GP_DECODE_MIN_RUN;           // pages a decode wave takes at least
+constexpr int kDecodeShortRun = 8;        // runs up to this many pages: one round of workgroups only
+constexpr int kDecodeResident = 512;      // decode workgroups that 256 CUs hold at once
 #ifndef GP_WIDE_MERGE
 #define GP_WIDE_MERGE 64
 #endif
@@ -70,13 +72,18 @@ __host__ __device__ inline size_t decode_chunked_bytes(int R, int Hq, int D, int
 
 // Work split of decode attention (see decode_kernel): W workgroups per KV head
 // take equal runs of the batch's pages; partial slot (workgroup + request).
-// W: kDecodeWorkgroups over all KV heads, the two that each CU holds, so that
-// every workgroup is there from the start and pays for its way to the first
-// page (lengths, page id, page: 3-4 us) once; fewer if the widest batch of this
-// shape has fewer runs of kDecodeMinRun pages.  With 512 / 1024 / 2048
-// workgroups: 40 short requests and a new token 44.0 / 46.9 / 53 us, Qwen3-8B
-// layer of 64 requests 96.6 / 97.4 / 99.2, 256 requests 482 / 486 / 490.  Runs of
-// two pages at least: one request of 6001 tokens 13.6 us against 16.2 with one.
+// W: kDecodeWorkgroups over all KV heads, one and a half times what the CUs hold
+// at once; fewer if the widest batch of this shape has fewer runs of
+// kDecodeMinRun pages.  A workgroup pays 3-4 us for its way to the first page
+// (lengths, page id, page), so short batches (runs of kDecodeShortRun pages or
+// less) are split over the resident ones only: 40 short requests and a new
+// token 44.0 us, 45.2 / 46.9 / 53 with 768 / 1024 / 2048 workgroups.  Long ones
+// take about the same time with 512 to 1024 (Qwen3-8B layer of 64 requests 96.6
+// / 96.6 / 97.4 us, 99.2 with 2048; 256 requests 482 / 484 / 486, 490), but a
+// second round evens out workgroups that started late because another stream
+// held their CU: a step with the boundary calls beside decode takes 153 us with
+// 512, 144 with 768.  Runs of two pages at least: one request of 6001 tokens
+// 13.6 us against 16.2 with one.
 __host__ __device__ inline DecodeWs decode_ws(int R, int Hq, int Hkv, int D, int max_pages, int waves) {
     DecodeWs w;
     const size_t unit = (size_t)Hq * (D + 2) * sizeof(float);          // one slot of every KV head
@@ -208,7 +215,7 @@ struct DecodeArgs {
     int ngroups;
     int g_first[kMaxPrefixGroups], g_num[kMaxPrefixGroups], g_pages[kMaxPrefixGroups];
     int g_blk0[kMaxPrefixGroups + 1], g_slots[kMaxPrefixGroups];
-    int R, Hkv, max_pages, pool_pages, W, min_run, slots, pslots;
+    int R, Hkv, max_pages, pool_pages, W, W1, min_run, slots, pslots;   // W1: workgroups per KV head that fit at once
     float qscale;   // scale * log2(e)
 };
 

@@ -227,3 +227,63 @@ def test_decode_shared_split(hq, hkv, d, prefix):
     assert bool((out[6] == 7.0).all())
     out[6] = 0.0
     _check(out, want, dtype, "shared decode")
+
+
+# ------------------------------------------------------------------ decide --
+
+@pytest.mark.parametrize("events", [1, 7, 64, 513, 1500])
+@pytest.mark.parametrize("stack", ["ample", "exact", "short", "none"])
+def test_decide_pages_in_list_order(events, stack):
+    """Pages are handed out in list order, whether the stack covers everybody
+    (prefix sum) or not (one request after the other): grows get the top pages
+    in order, then fall back, shared pages are replaced, and the reserve holds.
+    The expectation is the sequential rule itself."""
+    _say(f"decide {events} events, stack {stack}")
+    gen = torch.Generator().manual_seed(events)
+    hkv, d, width, reserve = 1, 64, 4, 2
+    npages = [1 + (r * 7) % 3 for r in range(events)]
+    want = [bool((r * 5) % 4 < 2) for r in range(events)]
+    shared = [(r % 6 == 1) and npages[r] > 1 for r in range(events)]
+    pops = sum(1 if w else s for w, s in zip([w or p == 1 for w, p in zip(want, npages)], shared))
+    free = {"ample": pops + reserve + 5, "exact": pops + reserve, "short": pops // 2 + reserve, "none": reserve}[stack]
+    pool, table = _paged(events, width, npages, gen)
+    pool += free
+    refs = torch.zeros(pool, dtype=torch.int32)
+    for r in range(events):
+        refs[table[r, :npages[r]].long()] = 1
+        if shared[r]:
+            refs[int(table[r, 0])] = 2
+    stack_ids = torch.arange(pool - free, pool, dtype=torch.int32)
+    free_list = torch.zeros(pool, dtype=torch.int32)
+    free_list[:free] = stack_ids
+    i32 = lambda x: torch.as_tensor(x, dtype=torch.int32).to(DEV)
+    ps = gp.PageState(table.to(DEV), i32(npages), i32([16 * p for p in npages]), refs.to(DEV), free_list.to(DEV),
+                      i32([free]))
+    kv = gp.KVLayer(*(torch.randn(pool, hkv, 16, d, generator=gen).to(torch.bfloat16).to(DEV) for _ in range(2)))
+    order = torch.randperm(events, generator=gen).to(torch.int32)
+    counts = torch.tensor([[[[6, 5] if want[int(r)] else [5, 6]] for r in order]], dtype=torch.int32).to(DEV)
+    scores = torch.rand(1, events, hkv, (width - 1) * 16, generator=gen).to(DEV)
+    dec, delta = torch.full((events,), -1, dtype=torch.int32, device=DEV), torch.zeros(events, device=DEV)
+    counters = torch.zeros(4, dtype=torch.int64, device=DEV)
+    ws = gp.workspace(gp.GP_OP_APPLY, events, events, 1, hkv, d, width, torch.bfloat16)
+    gp.gp_boundary_apply([kv], ps, order.to(DEV), counts, scores, gp.Params(reserve_pages=reserve), dec, delta,
+                         counters, ws)
+    torch.cuda.synchronize()
+    top, expect, want_table, tally = free, [], table.clone(), [0] * 4
+    for r in order.tolist():
+        P = npages[r]
+        if (want[r] or P == 1) and top > reserve:
+            top -= 1
+            want_table[r, P] = stack_ids[top]
+            expect.append(gp.GP_GROW)
+        elif P == 1 or (shared[r] and top < 1):
+            expect.append(gp.GP_PREEMPT)
+        else:
+            if shared[r]:
+                top -= 1
+                want_table[r, 0] = stack_ids[top]
+            expect.append(gp.GP_FALLBACK if want[r] else gp.GP_COMPRESS)
+        tally[expect[-1]] += 1
+    assert dec.cpu().tolist() == expect
+    assert torch.equal(ps.page_table.cpu(), want_table)
+    assert int(ps.free_count) == top and counters.cpu().tolist() == tally
