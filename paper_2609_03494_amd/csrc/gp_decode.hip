@@ -400,13 +400,15 @@ __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
 // the loads reads 6.7-6.8 TB/s whether or not a wave pauses for 1000 cycles
 // between a page's arrival and its refill; eight waves with two pages each read
 // 6.9 TB/s without the pause and 6.2-6.4 with it.
-template <typename T, int D, int G, int MODE>
-__global__ __launch_bounds__((64 * Page<T, D>::WAVES)) __attribute__((amdgpu_waves_per_eu(Page<T, D>::WAVES >= 8 ? 4 : 2))) void
-decode_kernel(
-    DecodeArgs a) {
+// OWN > 0: short tables, workgroup r of OWN waves takes request r (see decode_own).
+template <typename T, int D, int G, int MODE, int OWN>
+__global__ __launch_bounds__((64 * (OWN ? OWN : Page<T, D>::WAVES)))
+    __attribute__((amdgpu_waves_per_eu(Page<T, D>::BYTES <= 2048 && OWN && G <= 4 ? 8 : Page<T, D>::WAVES >= 8 ? 4 : 2))) void
+decode_kernel(DecodeArgs a) {
+    static_assert(!OWN || MODE != 2, "a shared-prefix call is always merged");
     constexpr bool STEP = MODE == 1, PREFIX = MODE == 2;
     using Pg = Page<T, D>;
-    constexpr int NW = Page<T, D>::WAVES;
+    constexpr int NW = OWN ? OWN : Page<T, D>::WAVES;
     constexpr int NT = 64 * NW;
     constexpr int LOADS = Pg::LOADS, DT = Pg::DT;
     // per wave its pages (keys, values); when they are read, the wave's o goes
@@ -415,7 +417,7 @@ decode_kernel(
     static_assert(G * D * 4 <= STAGE, "merge buffer");
     __shared__ __attribute__((aligned(1024))) char s_wave[NW][STAGE];
     __shared__ float s_ml[NW][G][2];                  // (max, sum) of each wave's open part
-    __shared__ int s_open[NW][3];                     // its request, first (1) and last (2) page flags; request written
+    __shared__ int s_open[NW][3];                     // its request; flags first page 1, last page 2, tail 4; request written
 
     const int h = blockIdx.x, wg = blockIdx.y;
     const int tid = threadIdx.x, lane = tid & 63;
@@ -423,76 +425,99 @@ decode_kernel(
     const int n = lane & 15, kg = lane >> 4;
     const int Hkv = a.Hkv, Hq = Hkv * G, R = a.R;
 
-    // ---- the split: U pages in all, L per wave; the request at the run's start.
-    // Thread t takes request base + t; the prefix sums meet in LDS.  (Rolled up:
-    // the code before the first page is fetched cold by every CU.)
-    __shared__ int s_sum[NW], s_incl[NT], s_len[NT], s_np[NT];
-    auto scan_block = [&](int base, int acc) {        // inclusive sums of the block's requests; its end
-        const int r = min(base + tid, R - 1), sl = a.seq_lens[r], np = a.num_pages[r];
-        const int x = base + tid < R ? req_view<STEP, PREFIX>(a, r, sl, np).n : 0;
-        const int incl = wave_scan(x);
-        if (base > 0) __syncthreads();                // (the previous block has been read)
-        if (lane == 63) s_sum[wave] = incl;
-        __syncthreads();
-        int before = acc, all = acc;
-#pragma unroll
-        for (int w = 0; w < NW; ++w) {
-            const int t = s_sum[w];
-            if (w < wave) before += t;
-            all += t;
+    // this wave's run [f0, f1) of the flat list; the request at f0, its first page's
+    // place in the list, and its length
+    int f0, f1, r = -1, a0 = 0, m_in = 0, P_in = 0;
+    if constexpr (OWN > 0) {
+        r = wg;
+        m_in = scalar_load(a.seq_lens, r);
+        P_in = scalar_load(a.num_pages, r);
+        const ReqView v = req_view<STEP, PREFIX>(a, r, m_in, P_in);
+        const int run = cdiv(v.n, NW);
+        f0 = min(wave * run, v.n);
+        f1 = v.held ? f0 : min(f0 + run, v.n);
+        if (h == 0 && tid == 0) {                     // for the merge pass (see below): nothing to fold
+            a.lens[r] = v.held ? -1 : v.m_attn;
+            a.lens[R + r] = v.room ? 1 : 0;
+            a.lens[2 * R + r] = a.lens[3 * R + r] = a.lens[4 * R + r] = 0;
         }
-        s_incl[tid] = before + incl;
-        s_len[tid] = sl;
-        s_np[tid] = np;
-        __syncthreads();
-        return all;
-    };
-    int U = 0;
-    for (int base = 0; base < R; base += NT) U = uni(scan_block(base, U));
-    const int L = max(max(a.min_run, cdiv(U, a.W * NW)), min(kDecodeShortRun, cdiv(U, a.W1 * NW)));
-    if (wg == a.W - 1) {                              // (the workgroup with the fewest pages)
-        // for the merge pass, per request: tokens attended (-1: held), whether a
-        // token went in, and the partial slots it folds (first, count; count 0:
-        // this pass writes the output); outputs of requests without tokens
-        int acc = 0;
-        for (int base = 0; base < R; base += 64) {
-            const int r = base + lane;
-            const ReqView v = req_view<STEP, PREFIX>(a, min(r, R - 1));
-            const int np = r < R ? v.n : 0, incl = wave_scan(np), a0 = acc + incl - np;
-            acc += __builtin_amdgcn_readlane(incl, 63);
-            if (base / 64 % NW != wave || r >= R) continue;
-            if (h == 0) {
-                const int ws = a0 / L / NW, we = np > 0 ? (a0 + np - 1) / L / NW : ws;
-                a.lens[r] = v.held ? -1 : v.m_attn;
-                a.lens[R + r] = v.room ? 1 : 0;
-                a.lens[2 * R + r] = ws + r;
-                a.lens[3 * R + r] = np > 0 && (we > ws || v.base > 0) ? we - ws + 1 : 0;
-                if (!(PREFIX && v.base > 0)) a.lens[4 * R + r] = 0;   // (else: the wave that begins the request)
-            }
-            if (np == 0 && !v.held) {
-                T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-                for (int i = 0; i < G * D; i += 4) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
-            }
+        if (v.n == 0 && !v.held) {                    // no tokens
+            T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
+            for (int i = 4 * tid; i < G * D; i += 4 * NT) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
         }
-    }
-    if (wg * NW * L >= U) return;                     // (uniform over the workgroup)
-
-    const int f0 = min((wg * NW + wave) * L, U);
-    const int f1 = min(f0 + L, U);                    // this wave's run [f0, f1) of the flat list
-    int r = -1, a0 = 0, m_in = 0, P_in = 0;           // request at f0, its first page's place in the list, its length
-    for (int base = 0, acc = 0; base < R; base += NT) {
-        if (R > NT) {                                 // (one block is still in LDS)
+    } else {
+        // ---- the split: U pages in all, L per wave; the request at the run's start.
+        // Thread t takes request base + t; the prefix sums meet in LDS.  (Rolled up:
+        // the code before the first page is fetched cold by every CU.)
+        __shared__ int s_sum[NW], s_incl[NT], s_len[NT], s_np[NT];
+        auto scan_block = [&](int base, int acc) {        // inclusive sums of the block's requests; its end
+            const int r = min(base + tid, R - 1), sl = a.seq_lens[r], np = a.num_pages[r];
+            const int x = base + tid < R ? req_view<STEP, PREFIX>(a, r, sl, np).n : 0;
+            const int incl = wave_scan(x);
+            if (base > 0) __syncthreads();                // (the previous block has been read)
+            if (lane == 63) s_sum[wave] = incl;
             __syncthreads();
-            acc = uni(scan_block(base, acc));
+            int before = acc, all = acc;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                const int t = s_sum[w];
+                if (w < wave) before += t;
+                all += t;
+            }
+            s_incl[tid] = before + incl;
+            s_len[tid] = sl;
+            s_np[tid] = np;
+            __syncthreads();
+            return all;
+        };
+        int U = 0;
+        for (int base = 0; base < R; base += NT) U = uni(scan_block(base, U));
+        const int L = max(max(a.min_run, cdiv(U, a.W * NW)), min(kDecodeShortRun, cdiv(U, a.W1 * NW)));
+        if (wg == a.W - 1) {                              // (the workgroup with the fewest pages)
+            // for the merge pass, per request: tokens attended (-1: held), whether a
+            // token went in, and the partial slots it folds (first, count; count 0:
+            // this pass writes the output); outputs of requests without tokens
+            int acc = 0;
+            for (int base = 0; base < R; base += 64) {
+                const int r = base + lane;
+                const ReqView v = req_view<STEP, PREFIX>(a, min(r, R - 1));
+                const int np = r < R ? v.n : 0, incl = wave_scan(np), a0 = acc + incl - np;
+                acc += __builtin_amdgcn_readlane(incl, 63);
+                if (base / 64 % NW != wave || r >= R) continue;
+                if (h == 0) {
+                    // (the lengths are read a second time here: should another stream be
+                    // writing them, the slots named still lie in the workspace)
+                    const int ws = min(a0 / L / NW, a.W - 1), we = np > 0 ? min((a0 + np - 1) / L / NW, a.W - 1) : ws;
+                    a.lens[r] = v.held ? -1 : v.m_attn;
+                    a.lens[R + r] = v.room ? 1 : 0;
+                    a.lens[2 * R + r] = ws + r;
+                    a.lens[3 * R + r] = np > 0 && (we > ws || v.base > 0) ? we - ws + 1 : 0;
+                    if (!(PREFIX && v.base > 0)) a.lens[4 * R + r] = 0;   // (else: the wave that begins the request)
+                }
+                if (np == 0 && !v.held) {
+                    T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
+                    for (int i = 0; i < G * D; i += 4) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
+                }
+            }
         }
-        for (int j = 0; j < NT && r < 0 && f0 < f1; j += 64) {
-            const unsigned long long past = __ballot(base + j + lane < R && s_incl[j + lane] > f0);
-            if (past) {
-                const int l = j + uni(__builtin_ctzll(past));
-                r = base + l;
-                m_in = uni(s_len[l]);
-                P_in = uni(s_np[l]);
-                a0 = uni(s_incl[l]) - uni(req_view<STEP, PREFIX>(a, r, m_in, P_in).n);
+        if (wg * NW * L >= U) return;                     // (uniform over the workgroup)
+
+        f0 = min((wg * NW + wave) * L, U);
+        f1 = min(f0 + L, U);
+        for (int base = 0, acc = 0; base < R; base += NT) {
+            if (R > NT) {                                 // (one block is still in LDS)
+                __syncthreads();
+                acc = uni(scan_block(base, acc));
+            }
+            for (int j = 0; j < NT && r < 0 && f0 < f1; j += 64) {
+                const unsigned long long past = __ballot(base + j + lane < R && s_incl[j + lane] > f0);
+                if (past) {
+                    const int l = j + uni(__builtin_ctzll(past));
+                    r = base + l;
+                    m_in = uni(s_len[l]);
+                    P_in = uni(s_np[l]);
+                    a0 = uni(s_incl[l]) - uni(req_view<STEP, PREFIX>(a, r, m_in, P_in).n);
+                }
             }
         }
     }
@@ -588,11 +613,14 @@ decode_kernel(
         return false;
     };
     u32x4_t q[Pg::QREGS];                             // Q of the current request
+    // (uniform bases and 32-bit lane offsets, here and in finish: 64-bit lane
+    // addresses kept across the loop would cost registers)
+    const uint32_t q_at = (uint32_t)(min(n, G - 1) * D + Pg::qdim(0, kg));
     auto load_q = [&](int rr) {
-        const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G + min(n, G - 1)) * D;
+        const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G) * D;
 #pragma unroll
         for (int j = 0; j < Pg::QREGS; ++j) {
-            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + Pg::qdim(j, kg));
+            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + (q_at + (uint32_t)(Pg::qdim(j, 0))));
             q[j] = n < G ? x : u32x4_t{};
         }
     };
@@ -609,23 +637,26 @@ decode_kernel(
     // the finished part of request rr: its output if the wave has all of it, else its partial
     auto finish = [&](int rr, bool direct) {
         const float l = cross_sum(lrun);
+        uint32_t nn = n, dd = Pg::group_dim(0, kg);
+        __asm__ volatile("" : "+v"(nn), "+v"(dd));
         if (n < G) {
             if (direct) {
-                T *o = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G + n) * D;
+                T *o = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
+                const uint32_t at = nn * D + dd;
 #pragma unroll
-                for (int j = 0; j < Pg::GROUPS; ++j) {
-                    store_out(o + Pg::group_dim(j, kg), Pg::group(ot, j), l > 0.0f ? l : __builtin_inff());
-                }
+                for (int j = 0; j < Pg::GROUPS; ++j)
+                    store_out(o + (at + (uint32_t)Pg::group_dim(j, 0)), Pg::group(ot, j), l > 0.0f ? l : __builtin_inff());
             } else {
-                float *pt = part_of(rr) + (size_t)n * (D + 2);
+                float *pt = part_of(rr);
+                const uint32_t at = nn * (D + 2) + dd;
 #pragma unroll
                 for (int j = 0; j < Pg::GROUPS; ++j) {
                     const f32x4_t x = Pg::group(ot, j);
-                    float *o = pt + Pg::group_dim(j, kg);
+                    float *o = pt + (at + (uint32_t)Pg::group_dim(j, 0));
                     reinterpret_cast<float2 *>(o)[0] = make_float2(x[0], x[1]);
                     reinterpret_cast<float2 *>(o)[1] = make_float2(x[2], x[3]);
                 }
-                if (kg == 0) *reinterpret_cast<float2 *>(pt + D) = make_float2(mrun, l);
+                if (kg == 0) *reinterpret_cast<float2 *>(pt + (nn * (D + 2) + D)) = make_float2(mrun, l);
             }
         }
     };
@@ -635,7 +666,7 @@ decode_kernel(
     // the request's first or last page, and the request whose partial it wrote
     // on the way (at most one: the one its run began in)
     int open_r = -1, wrote_r = -1;
-    bool open_first = false, open_last = false;
+    bool open_first = false, open_last = false, open_tail = false;
     // A page on its way: where it is and whose it is.
     struct Ahead {
         int phys, r, p, base, m_attn;
@@ -728,6 +759,7 @@ decode_kernel(
                 if (!nxt.valid) {
                     open_first = cur.first_of;
                     open_last = cur.ends;
+                    open_tail = cur.base > 0;         // (a prefix pass has the pages before)
                     if (all && cur.base == 0) finish(cur.r, true);
                     else open_r = cur.r;
                     break;
@@ -757,7 +789,7 @@ decode_kernel(
     }
     if (lane == 0) {
         s_open[wave][0] = open_r;
-        s_open[wave][1] = (open_first ? 1 : 0) | (open_last ? 2 : 0);
+        s_open[wave][1] = (open_first ? 1 : 0) | (open_last ? 2 : 0) | (open_tail ? 4 : 0);
         s_open[wave][2] = wrote_r;
     }
     __syncthreads();
@@ -772,8 +804,7 @@ decode_kernel(
         // the wave after them may have written the rest of rr as this workgroup's partial
         const bool more_ = w1 < NW && uni(s_open[w1][2]) == rr;
         const bool all = (uni(s_open[w0][1]) & 1) && (more_ || (uni(s_open[w1 - 1][1]) & 2));
-        bool direct = all;
-        if constexpr (PREFIX) direct = all && uni(req_view<STEP, PREFIX>(a, rr).base) == 0;
+        const bool direct = all && !(uni(s_open[w0][1]) & 4);
         float *pt = part_of(rr);
         T *out = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
         constexpr int EPT = (G * D + NT - 1) / NT;
@@ -1183,7 +1214,8 @@ template <typename T, int D>
 hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
     const dim3 grid(a.Hkv, a.W), mgrid(a.Hkv, a.R);
     constexpr bool bf16 = sizeof(T) == 2;
-    constexpr int NT = 64 * Page<T, D>::WAVES;
+    constexpr int NW = Page<T, D>::WAVES, NT = 64 * NW;
+    constexpr int NN = Page<T, D>::BYTES <= 2048 ? 4 : NW;        // (see decode_own_narrow)
     // the step variant with a new token and the tails of the shared-prefix
     // decode are their own instantiations, so plain decode attention carries
     // none of their code (a step call's summary update is in the merge pass:
@@ -1191,10 +1223,12 @@ hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
     const int mode = a.ngroups > 0 ? 2 : a.k_new != nullptr ? 1 : 0;
     // the merge pass also advances the lengths when a token went in, updates
     // the summaries of a step call, and folds the prefix partials of a
-    // shared-prefix call; with one workgroup per KV head no request spans two
+    // shared-prefix call; with a workgroup per request there is nothing to fold
+    const bool own = mode != 2 && decode_own(a.max_pages, a.R, a.Hkv);
+    const bool narrow = own && decode_own_narrow(a.R, a.Hkv);
     const bool chunks = stages & GP_DECODE_CHUNKS, prefix = (stages & GP_DECODE_PREFIX) && mode == 2,
                merge = (stages & GP_DECODE_MERGE) &&
-                       (a.W > 1 || (a.k_new && a.advance) || mode == 2 || a.qstate);
+                       (!own || (a.k_new && a.advance) || a.qstate);
     const bool wide = (int64_t)a.Hkv * a.R < kWideMerge;
     // prefix pass grid: (KV head, prefix slot, request block)
     int max_ps = 1;
@@ -1205,10 +1239,18 @@ hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
     case GG:                                                                       \
         if constexpr (bf16) {                                                      \
             if (prefix) prefix_kernel<D, GG><<<pgrid, 64 * kPrefixWaves, 0, s>>>(a); \
-            if (chunks && mode == 2) decode_kernel<T, D, GG, 2><<<grid, NT, 0, s>>>(a); \
+            if (chunks && mode == 2) decode_kernel<T, D, GG, 2, 0><<<grid, NT, 0, s>>>(a); \
         }                                                                          \
-        if (chunks && mode == 1) decode_kernel<T, D, GG, 1><<<grid, NT, 0, s>>>(a); \
-        if (chunks && mode == 0) decode_kernel<T, D, GG, 0><<<grid, NT, 0, s>>>(a); \
+        if (chunks && mode == 1 && own) {                                         \
+            if (NN < NW && narrow) decode_kernel<T, D, GG, 1, NN><<<mgrid, 64 * NN, 0, s>>>(a); \
+            else decode_kernel<T, D, GG, 1, NW><<<mgrid, NT, 0, s>>>(a);            \
+        }                                                                          \
+        if (chunks && mode == 1 && !own) decode_kernel<T, D, GG, 1, 0><<<grid, NT, 0, s>>>(a); \
+        if (chunks && mode == 0 && own) {                                         \
+            if (NN < NW && narrow) decode_kernel<T, D, GG, 0, NN><<<mgrid, 64 * NN, 0, s>>>(a); \
+            else decode_kernel<T, D, GG, 0, NW><<<mgrid, NT, 0, s>>>(a);            \
+        }                                                                          \
+        if (chunks && mode == 0 && !own) decode_kernel<T, D, GG, 0, 0><<<grid, NT, 0, s>>>(a); \
         if (merge && wide) merge_kernel<T, D, GG, 1024><<<mgrid, 1024, 0, s>>>(a); \
         if (merge && !wide) merge_kernel<T, D, GG, 256><<<mgrid, 256, 0, s>>>(a);  \
         break;

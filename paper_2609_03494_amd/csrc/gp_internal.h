@@ -56,6 +56,22 @@ __device__ inline float ema_step(float prev, float x, double beta, double one_mi
     return (float)(a + b);
 }
 
+// Short tables: one workgroup per (KV head, request), so that no request spans
+// two and the merge launch falls away.  Up to 64 pages (1024 tokens) that saves
+// more than equal runs do (64 requests of up to 500 tokens, 32/8 heads, d 128:
+// 20.8 us against 26.3; 8/8 heads, d 64: 11.5 against 15.8), up to 128 where there
+// are two workgroups per CU (256 requests of up to 1000 tokens, 66 pages, 32/8
+// heads: 130 against 142; 64 requests of up to 1900: 63.1 against 64.6; but 4 of
+// them 21 against 13.9).
+__host__ __device__ inline bool decode_own(int max_pages, int R, int Hkv) {
+    return max_pages <= 64 || (max_pages <= 128 && (int64_t)R * Hkv >= 512);
+}
+// ... of four waves instead of eight where a wave holds 64 registers (pages of 2 KB)
+// and as many workgroups are there: more of them fit a CU, fewer waves have no page
+// (8/8 heads, d 64, up to 200 tokens: 256 requests 15.8 us against 20.3, 128 10.3
+// against 11.2; 16 requests of up to 500 tokens the other way round, 9.8 against 8.1).
+__host__ __device__ inline bool decode_own_narrow(int R, int Hkv) { return (int64_t)R * Hkv >= 512; }
+
 struct DecodeWs {
     size_t partial, lens, prefix, total;
     size_t plain;                 // bytes a call without a shared prefix touches

@@ -161,12 +161,13 @@ SPLITS = {
 
 
 @pytest.mark.parametrize("name", list(SPLITS))
+@pytest.mark.parametrize("spare", [5, 70, 130])    # a workgroup per request up to 64 columns, or 128 if there are many
 @pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 8, 2, 128), (torch.bfloat16, 3, 3, 64),
                                             (torch.float32, 8, 1, 128), (torch.float32, 4, 2, 64)])
-def test_decode_split(name, dtype, hq, hkv, d):
+def test_decode_split(name, spare, dtype, hq, hkv, d):
     lens = SPLITS[name]
-    _say(f"decode split {name} {dtype} heads {hq}/{hkv} d {d}")
-    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=5)
+    _say(f"decode split {name} {dtype} heads {hq}/{hkv} d {d} spare table columns {spare}")
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
     ps = _state(table, npages, lens, pool)
     ws = gp.workspace(gp.GP_OP_DECODE, len(lens), 0, hq, hkv, d, table.shape[1], dtype)
     scale = d ** -0.5
