@@ -11,7 +11,8 @@
 // requests x 36 layers of 32/8 heads, d 128, where the traffic is 189 MB;
 // 49 us now, 3.8 TB/s of reads and writes.)  A
 // call of one layer has nothing to spread: its workgroups advance the lengths
-// themselves, in one launch.  Held requests (seq_len < 0) and requests whose
+// themselves, in one launch; so do those of a call small enough for one workgroup
+// per request (append_flat_kernel).  Held requests (seq_len < 0) and requests whose
 // pages are full (at a capacity boundary, waiting for a decision) take no token
 // and keep their summaries.  The summary arithmetic is ema_step, the same as
 // the summaries kernel's, so the two agree bit for bit.
@@ -129,6 +130,69 @@ __global__ __launch_bounds__(256) void append_kernel(AppendArgs a) {
     }
 }
 
+// Few layers and short rows: one launch of one workgroup per request, all of whose
+// 16-byte units (K and V of every layer, groups of four summary elements) are in
+// flight at once, so the workgroup advances the length itself.  Up to kFlatUnits
+// of them, one round: the second launch costs a host that launches call by call
+// 4 us (12 layers of 16/4 heads, d 64, 16 requests: 25.4 us a call against 29.9),
+// and the GPU 1 us (2 layers of 4/2 heads, d 64: 5.4 against 6.1 in a graph).
+// With more units the CUs that hold no request are missed: 5 layers of 32/8
+// heads, d 128, in two rounds 10.7 us in a graph against 7.2.
+constexpr int kFlatThreads = 1024, kFlatUnits = kUnroll * kFlatThreads;
+template <typename T, int D>
+__global__ __launch_bounds__(kFlatThreads) void append_flat_kernel(AppendArgs a) {
+    const int r = blockIdx.x, tid = threadIdx.x;
+    const int slot = a.slot_ids[r];
+    const bool has_slot = slot >= 0 && slot < a.M;
+    const bool init = a.init != nullptr && a.init[r] != 0;
+    int m;
+    const int pid = append_page(a, r, m);
+    if (pid < 0) return;
+    constexpr int EPU = 16 / sizeof(T), UPR = D / EPU;         // elements per unit, units per row
+    const int HkvD = a.Hkv * D, HqD = a.Hq * D;
+    const double cs = 1.0 - a.beta_s, cl = 1.0 - a.beta_l;
+    const int half = a.Hkv * UPR, KV = 2 * half, U = KV + (has_slot ? HqD / 4 : 0), N = a.n_layers * U;
+    if (tid < N) {                                   // (waves without a unit have nothing to load)
+        float4 x[kUnroll], s[kUnroll], w[kUnroll];
+        T *kv[kUnroll];
+        float *S[kUnroll];
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
+            const int i = min(tid + kFlatThreads * k, N - 1), l = i / U, u = i - l * U;
+            kv[k] = nullptr;
+            if (u < KV) {
+                const bool isv = u >= half;
+                const int j = isv ? u - half : u, h = j / UPR;
+                x[k] = reinterpret_cast<const float4 *>(reinterpret_cast<const T *>(isv ? a.v_new : a.k_new) +
+                                                        ((size_t)l * a.R + r) * HkvD)[j];
+                kv[k] = reinterpret_cast<T *>(isv ? a.v[l] : a.k[l]) +
+                        (((size_t)pid * a.Hkv + h) * kPage + m % kPage) * D + (j % UPR) * EPU;
+            } else {
+                const int j = 4 * (u - KV);
+                S[k] = a.qstate + ((size_t)l * a.M + slot) * 2 * HqD + j;
+                x[k] = load4(reinterpret_cast<const T *>(a.q_pre) + ((size_t)l * a.R + r) * HqD + j);
+                s[k] = *reinterpret_cast<const float4 *>(S[k]);
+                w[k] = *reinterpret_cast<const float4 *>(S[k] + HqD);
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < kUnroll; ++k) {
+            if (tid + kFlatThreads * k >= N) break;
+            if (kv[k]) {
+                *reinterpret_cast<float4 *>(kv[k]) = x[k];
+            } else {
+                *reinterpret_cast<float4 *>(S[k]) = init ? x[k] : ema4(s[k], x[k], a.beta_s, cs);
+                *reinterpret_cast<float4 *>(S[k] + HqD) = init ? x[k] : ema4(w[k], x[k], a.beta_l, cl);
+            }
+        }
+    }
+    __syncthreads();
+    if (tid == 0) {
+        a.seq_lens[r] = m + 1;
+        a.positions[r] += 1;
+    }
+}
+
 __global__ __launch_bounds__(64) void advance_kernel(AppendArgs a) {
     const int r = blockIdx.x * 64 + threadIdx.x;
     int m;
@@ -145,6 +209,11 @@ void launch_td(const AppendArgs &a, hipStream_t s) {
     for (int l = 0; l < a.n_layers; ++l)
         bits |= reinterpret_cast<uintptr_t>(a.k[l]) | reinterpret_cast<uintptr_t>(a.v[l]);
     const dim3 grid(a.R, a.n_layers);
+    const int units = 2 * a.Hkv * (D * (int)sizeof(T) / 16) + a.Hq * (D / 4);         // of a request, per layer
+    if (bits % 16 == 0 && a.n_layers > 1 && (int64_t)units * a.n_layers <= kFlatUnits) {
+        append_flat_kernel<T, D><<<a.R, kFlatThreads, 0, s>>>(a);
+        return;
+    }
     if (bits % 16 == 0)
         append_kernel<T, D, true><<<grid, 256, 0, s>>>(a);
     else

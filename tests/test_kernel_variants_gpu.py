@@ -47,7 +47,8 @@ def _state(table, num_pages, seq_lens, pool):
 
 @pytest.mark.parametrize("dtype", [torch.bfloat16, torch.float32])
 @pytest.mark.parametrize("layers,hq,hkv,d,offset", [(1, 8, 2, 64, 0), (3, 4, 4, 64, 1), (5, 24, 3, 128, 0),
-                                                    (2, 40, 5, 128, 8), (2, 32, 8, 128, 2)])
+                                                    (2, 40, 5, 128, 8), (2, 32, 8, 128, 2),
+                                                    (3, 32, 8, 128, 0), (4, 24, 3, 128, 0), (7, 32, 8, 128, 0)])
 def test_append_layers(dtype, layers, hq, hkv, d, offset):
     """Rows copied, summaries stepped and lengths advanced once per request,
     over one or several layers, for aligned and unaligned buffers; full, held
