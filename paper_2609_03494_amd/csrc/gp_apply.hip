@@ -218,7 +218,7 @@ __device__ void select_tokens(const ApplyArgs &a, int i, int h, int l, int P, in
 // SHRINK: the Shrink policy's variant, which also selects the 32 tokens a
 // shrink would evict
 template <int D, int E, bool SHRINK>
-__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(SHRINK ? 4 : 5))) void pre_kernel(ApplyArgs a, LayerTable lt) {
+__global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))) void pre_kernel(ApplyArgs a, LayerTable lt) {
     __builtin_amdgcn_s_setprio(3);   // issue ahead of co-resident decode waves
     __shared__ int s_n;
     const int x = blockIdx.y, i = blockIdx.z;
