@@ -88,6 +88,13 @@ __device__ inline void lds_read16(uint32_t a0, uint32_t a1, uint32_t a2, uint32_
         "s_waitcnt lgkmcnt(0)"
         : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
 }
+__device__ inline void lds_read8(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2_t &x0, u32x2_t &x1,
+                                 u32x2_t &x2, u32x2_t &x3) {
+    __asm__ volatile(
+        "ds_read_b64 %0, %4\n\tds_read_b64 %1, %5\n\tds_read_b64 %2, %6\n\tds_read_b64 %3, %7\n\t"
+        "s_waitcnt lgkmcnt(0)"
+        : "=&v"(x0), "=&v"(x1), "=&v"(x2), "=&v"(x3) : "v"(a0), "v"(a1), "v"(a2), "v"(a3) : "memory");
+}
 // four transposed 16-bit reads (ds_read_b64_tr_b16)
 __device__ inline void lds_read_tr(uint32_t a0, uint32_t a1, uint32_t a2, uint32_t a3, u32x2_t &x0, u32x2_t &x1,
                                    u32x2_t &x2, u32x2_t &x3) {
@@ -191,8 +198,48 @@ __device__ inline ReqView req_view(const DecodeArgs &a, int r) {
 // 16), which is the layout P^T needs as the B operand of O^T += V^T.P^T; every
 // lane then owns output dims of one head, so the softmax rescale needs no lane
 // exchange, and the cost does not depend on G.
-template <typename T, int D>
+//
+// QUAD (few query heads per KV head): P.V on v_mfma_f32_4x4x1f32, sixteen
+// outer products of four dims and four heads each, in float32 throughout.  The
+// columns of S^T repeat the heads (column n is head n % 4), so that every quad
+// of lanes has P of its row's tokens as the B operand in place; lane (n, kg)
+// brings dims 4 n .. + 3 of token 4 kg + e, and the four rows of lanes are
+// added up at the end of a request (gather).
+//
+// What a lane holds of a request: the head `head(n)`, its first GROUPS groups
+// of four consecutive dims, group j from `group_dim(j, n, kg)`.
+template <typename T, int D, bool QUAD>
 struct Page;
+
+// O^T of the QUAD products: acc[4 g + c][i] of lane (n, kg) is dim 64 g + 4 (n
+// / 4 * 4 + i) + c of head n % 4, summed over the tokens of row kg.  The sums
+// over the rows, with the four dims 4 c' .. + 3 of each left in one row:
+// v_permlane32_swap and v_permlane16_swap put the halves (rows) of two values
+// side by side, so that each addition sums one value in one half and the other
+// in the other.
+__device__ inline float pair32(float x, float y) {    // rows 0, 1: x, rows 2, 3: y, each of both halves
+    auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ inline float pair16(float x, float y) {    // rows 0, 2: x, rows 1, 3: y, each of both rows of a half
+    auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+template <int D>
+struct QuadOut {
+    static constexpr int ACC = D / 16, GROUPS = D / 64;
+    __device__ static inline int head(int n) { return n & 3; }
+    __device__ static inline int group_dim(int j, int n, int kg) { return 64 * j + 4 * (n / 4 * 4 + kg); }
+    __device__ static inline void gather(const f32x4_t (&acc)[ACC], f32x4_t (&o)[GROUPS]) {
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j)
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const f32x4_t &x = acc[4 * j + c];
+                o[j][c] = pair16(pair32(x[0], x[2]), pair32(x[1], x[3]));
+            }
+    }
+};
 
 // bfloat16: S^T on v_mfma_f32_16x16x32_bf16; P split into two bfloat16 terms
 // (hi + lo carry its float32 value to about 2^-17) and O^T on
@@ -201,15 +248,14 @@ struct Page;
 // bytes) of row R sits at R UPR + (u ^ R % UPR), so that the 16 rows of a
 // score-layout read fall on distinct banks; values at u ^ 2 (R % (UPR / 2)),
 // so that the transposed reads of 4 rows x 2 units do.
-template <int D>
-struct Page<uint16_t, D> {
+template <int D, bool QUAD>
+struct PageBf16 {
     static constexpr int UPR = D / 8;                 // 16-byte units per row
     static constexpr int BYTES = kPage * D * 2;       // keys or values of one page and head
     static constexpr int LOADS = BYTES / 1024;        // load instructions (64 lanes x 16 bytes) per page
     static constexpr int WAVES = decode_waves(2, D);  // per workgroup: 64 KiB of pages at most
     static constexpr int RPI = 64 / UPR;              // rows per load instruction
     static constexpr int KK = D / 32;                 // product steps over the head dims
-    static constexpr int DT = D / 16;                 // O^T tiles of 16 dims
 
     // byte offset of this lane's unit in load instruction q of keys or values,
     // less 1024 q (the instruction's immediate): row R = q RPI + lane / UPR, unit
@@ -219,21 +265,19 @@ struct Page<uint16_t, D> {
         return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (lane / UPR))) * 16;
     }
     static constexpr uint32_t kflip(int q) { return q * RPI % UPR * 16; }
+    // values: as the transposed reads want them (see above); QUAD: rows R and R +
+    // 4, which one read takes together, on different halves of the banks
     __device__ static inline uint32_t voff(int lane) {
-        return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (2 * (lane / UPR % (UPR / 2))))) * 16;
+        const int R = lane / UPR, u = lane % UPR;
+        if constexpr (QUAD) return (uint32_t)(D == 64 ? (R ^ (R / 4 & 1)) * UPR + u : R * UPR + u) * 16;
+        return (uint32_t)(R * UPR + (u ^ (2 * (R % (UPR / 2))))) * 16;
     }
-    static constexpr uint32_t vflip(int q) { return 2 * (q * RPI % (UPR / 2)) * 16; }
-    // LDS offsets of this lane's reads, to be xored with 64 kk (key operand kk) or
-    // 32 t (transposed values of tile t)
+    static constexpr uint32_t vflip(int q) {
+        return QUAD ? (D == 64 ? 0 : (q & 1) * 128) : 2 * (q * RPI % (UPR / 2)) * 16;
+    }
+    // LDS offset of this lane's key reads, to be xored with 64 kk (operand kk)
     __device__ static inline uint32_t kread(int n, int kg) { return (n * UPR + (kg ^ (n % UPR))) * 16; }
-    __device__ static inline uint32_t vread(int n, int kg) {
-        // V^T tile t as the A operand by transposed reads: lane j of group kg
-        // names row R = 4 kg + j / 4, dims 16 t + 4 (j % 4); lane n receives
-        // tokens 4 kg .. + 3 at dim 16 t + n
-        const int R = 4 * kg + n / 4, qd = n % 4;
-        return (R * UPR + ((qd / 2) ^ (2 * (R % (UPR / 2))))) * 16 + (qd & 1) * 8;
-    }
-    // Q of head n as the B operand: unit kk of lane (n, kg) is head dims 32 kk + 8 kg .. + 7
+    // Q of the lane's head as the B operand: unit kk of lane (n, kg) is head dims 32 kk + 8 kg .. + 7
     static constexpr int QREGS = KK;
     __device__ static inline int qdim(int j, int kg) { return 32 * j + 8 * kg; }
     __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
@@ -247,6 +291,20 @@ struct Page<uint16_t, D> {
                                                          __builtin_bit_cast(bf16x8_t, q[kk]), st, 0, 0, 0);
         }
         return st;
+    }
+};
+
+template <int D>
+struct Page<uint16_t, D, false> : PageBf16<D, false> {
+    using B = PageBf16<D, false>;
+    static constexpr int UPR = B::UPR, DT = D / 16, ACC = DT;     // O^T tiles of 16 dims
+    // LDS offset of this lane's transposed reads, to be xored with 32 t (tile t)
+    __device__ static inline uint32_t vread(int n, int kg) {
+        // V^T tile t as the A operand by transposed reads: lane j of group kg
+        // names row R = 4 kg + j / 4, dims 16 t + 4 (j % 4); lane n receives
+        // tokens 4 kg .. + 3 at dim 16 t + n
+        const int R = 4 * kg + n / 4, qd = n % 4;
+        return (R * UPR + ((qd / 2) ^ (2 * (R % (UPR / 2))))) * 16 + (qd & 1) * 8;
     }
     // O^T += V^T.P^T; ntok: tokens of the page (slots past the last may hold
     // anything: 0 x inf would reach o, so they read as zero)
@@ -275,10 +333,52 @@ struct Page<uint16_t, D> {
             }
         }
     }
-    // group j of four consecutive dims that the lane owns: its first dim and values
     static constexpr int GROUPS = DT;
-    __device__ static inline int group_dim(int j, int kg) { return 16 * j + 4 * kg; }
-    __device__ static inline f32x4_t group(const f32x4_t (&ot)[DT], int j) { return ot[j]; }
+    __device__ static inline int head(int n) { return n; }
+    __device__ static inline int group_dim(int j, int n, int kg) { return 16 * j + 4 * kg; }
+    __device__ static inline void gather(const f32x4_t (&ot)[ACC], f32x4_t (&o)[GROUPS]) {
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j) o[j] = ot[j];
+    }
+};
+
+// The weights stay float32 and the values are widened (exactly), so a product
+// is as exact as a float32 multiply-add, and an infinite value weighs as one
+// (a second bfloat16 term of P may be negative).  16 (d = 64) or 32 products
+// of 8 cycles per page: 9 % of the cycles that a page's transfer gives a SIMD.
+template <int D>
+struct Page<uint16_t, D, true> : PageBf16<D, true>, QuadOut<D> {
+    using B = PageBf16<D, true>;
+    static constexpr int UPR = B::UPR, ACC = QuadOut<D>::ACC, NU = D / 64;
+    // LDS offset of this lane's reads: dims 4 n .. + 3 of token 4 kg + e of 64-dim
+    // group g at + e UPR 16, xored by e's and g's parts
+    __device__ static inline uint32_t vread(int n, int kg) {
+        if constexpr (D == 64) return (4 * kg * UPR) * 16 + 8 * n;
+        return (4 * kg * UPR) * 16 + (8 * n ^ (kg & 1) * 128);
+    }
+    __device__ static inline uint32_t vtoken(uint32_t va, int e, int kg) {
+        return D == 64 ? va + (e ^ (kg & 1)) * UPR * 16 : va + e * UPR * 16;
+    }
+    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&acc)[ACC], int kg) {
+        u32x2_t vx[4 * NU];
+#pragma unroll
+        for (int j = 0; j < NU; ++j)
+            lds_read8(vtoken(va, 0, kg) ^ j * 128, vtoken(va, 1, kg) ^ j * 128, vtoken(va, 2, kg) ^ j * 128,
+                      vtoken(va, 3, kg) ^ j * 128, vx[4 * j], vx[4 * j + 1], vx[4 * j + 2], vx[4 * j + 3]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+#pragma unroll
+            for (int j = 0; j < NU; ++j) {
+                u32x2_t v = vx[4 * j + e];
+                if (ntok < kPage && 4 * kg + e >= ntok) v = u32x2_t{0u, 0u};
+                f32x4_t *o = acc + 4 * j;
+                o[0] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_lo(v[0]), p[e], o[0], 0, 0, 0);
+                o[1] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_hi(v[0]), p[e], o[1], 0, 0, 0);
+                o[2] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_lo(v[1]), p[e], o[2], 0, 0, 0);
+                o[3] = __builtin_amdgcn_mfma_f32_4x4x1f32(bf16_hi(v[1]), p[e], o[3], 0, 0, 0);
+            }
+        }
+    }
 };
 
 // float32: both products on v_mfma_f32_16x16x4f32 (float32 products and sums).
@@ -288,14 +388,14 @@ struct Page<uint16_t, D> {
 // dim 64 j + 4 n + c.  Keys are swizzled (u ^ R % 16); a value read is one
 // 256-byte run per row.
 template <int D>
-struct Page<float, D> {
+struct Page<float, D, false> {
     static constexpr int UPR = D / 4;
     static constexpr int BYTES = kPage * D * 4;
     static constexpr int LOADS = BYTES / 1024;
     static constexpr int WAVES = decode_waves(4, D);
     static constexpr int RPI = 64 / UPR;
     static constexpr int NJ = D / 16;                 // key units per lane
-    static constexpr int DT = D / 16;
+    static constexpr int DT = D / 16, ACC = DT;
 
     __device__ static inline uint32_t koff(int lane) {
         return (uint32_t)(lane / UPR * UPR + ((lane % UPR) ^ (lane / UPR))) * 16;
@@ -352,12 +452,25 @@ struct Page<float, D> {
         for (int t = 0; t < DT; ++t) ot[t] += pv[t];
     }
     static constexpr int GROUPS = DT;
-    __device__ static inline int group_dim(int j, int kg) { return 64 * (j / 4) + 16 * kg + 4 * (j % 4); }
-    __device__ static inline f32x4_t group(const f32x4_t (&ot)[DT], int j) {
-        const int t = 4 * (j / 4), e = j % 4;
-        return f32x4_t{ot[t][e], ot[t + 1][e], ot[t + 2][e], ot[t + 3][e]};
+    __device__ static inline int head(int n) { return n; }
+    __device__ static inline int group_dim(int j, int n, int kg) { return 64 * (j / 4) + 16 * kg + 4 * (j % 4); }
+    __device__ static inline void gather(const f32x4_t (&ot)[ACC], f32x4_t (&o)[GROUPS]) {
+#pragma unroll
+        for (int j = 0; j < GROUPS; ++j) {
+            const int t = 4 * (j / 4), e = j % 4;
+            o[j] = f32x4_t{ot[t][e], ot[t + 1][e], ot[t + 2][e], ot[t + 3][e]};
+        }
     }
 };
+
+template <typename T, int D>
+constexpr int waves_of() { return decode_waves(sizeof(T), D); }
+template <typename T, int D>
+constexpr int page_bytes_of() { return kPage * D * (int)sizeof(T); }
+// The query heads per KV head of which P.V runs in QUAD products.  bfloat16, more
+// heads: the two-term P of four or eight heads costs the matrix cores less.
+template <typename T>
+constexpr bool quad_heads(int G) { return sizeof(T) == 2 && G <= 2; }
 
 // One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
 // stage + 1024 q (the immediate offset moves source and destination).
@@ -402,15 +515,15 @@ __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
 // 6.9 TB/s without the pause and 6.2-6.4 with it.
 // OWN > 0: short tables, workgroup r of OWN waves takes request r (see decode_own).
 template <typename T, int D, int G, int MODE, int OWN>
-__global__ __launch_bounds__((64 * (OWN ? OWN : Page<T, D>::WAVES)))
-    __attribute__((amdgpu_waves_per_eu(Page<T, D>::BYTES <= 2048 && OWN && G <= 4 ? 8 : Page<T, D>::WAVES >= 8 ? 4 : 2))) void
+__global__ __launch_bounds__((64 * (OWN ? OWN : waves_of<T, D>())))
+    __attribute__((amdgpu_waves_per_eu(page_bytes_of<T, D>() <= 2048 && OWN && G <= 4 ? 8 : waves_of<T, D>() >= 8 ? 4 : 2))) void
 decode_kernel(DecodeArgs a) {
     static_assert(!OWN || MODE != 2, "a shared-prefix call is always merged");
     constexpr bool STEP = MODE == 1, PREFIX = MODE == 2;
-    using Pg = Page<T, D>;
-    constexpr int NW = OWN ? OWN : Page<T, D>::WAVES;
+    using Pg = Page<T, D, quad_heads<T>(G)>;
+    constexpr int NW = OWN ? OWN : waves_of<T, D>();
     constexpr int NT = 64 * NW;
-    constexpr int LOADS = Pg::LOADS, DT = Pg::DT;
+    constexpr int LOADS = Pg::LOADS, ACC = Pg::ACC;
     // per wave its pages (keys, values); when they are read, the wave's o goes
     // where the first keys were
     constexpr int STAGE = 2 * Pg::BYTES;
@@ -423,6 +536,7 @@ decode_kernel(DecodeArgs a) {
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = uni(tid >> 6);
     const int n = lane & 15, kg = lane >> 4;
+    const int hn = Pg::head(n);                       // the lane's query head of the group
     const int Hkv = a.Hkv, Hq = Hkv * G, R = a.R;
 
     // this wave's run [f0, f1) of the flat list; the request at f0, its first page's
@@ -615,48 +729,49 @@ decode_kernel(DecodeArgs a) {
     u32x4_t q[Pg::QREGS];                             // Q of the current request
     // (uniform bases and 32-bit lane offsets, here and in finish: 64-bit lane
     // addresses kept across the loop would cost registers)
-    const uint32_t q_at = (uint32_t)(min(n, G - 1) * D + Pg::qdim(0, kg));
+    const uint32_t q_at = (uint32_t)(min(hn, G - 1) * D + Pg::qdim(0, kg));
     auto load_q = [&](int rr) {
         const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G) * D;
 #pragma unroll
         for (int j = 0; j < Pg::QREGS; ++j) {
             const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + (q_at + (uint32_t)(Pg::qdim(j, 0))));
-            q[j] = n < G ? x : u32x4_t{};
+            q[j] = hn < G ? x : u32x4_t{};
         }
     };
 
-    f32x4_t ot[DT];
-    float mrun, lrun;                                 // head n: running max (log2 units), this lane's share of the sum
+    f32x4_t ot[ACC];
+    float mrun, lrun;                                 // the lane's head: running max (log2 units), this lane's share of the sum
     auto clear = [&]() {
         mrun = kNegInf;
         lrun = 0.0f;
 #pragma unroll
-        for (int t = 0; t < DT; ++t) ot[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        for (int t = 0; t < ACC; ++t) ot[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
     };
     auto part_of = [&](int rr) { return a.partial + ((size_t)h * a.slots + wg + rr) * G * (D + 2); };
     // the finished part of request rr: its output if the wave has all of it, else its partial
     auto finish = [&](int rr, bool direct) {
         const float l = cross_sum(lrun);
-        uint32_t nn = n, dd = Pg::group_dim(0, kg);
+        f32x4_t og[Pg::GROUPS];
+        Pg::gather(ot, og);
+        uint32_t nn = hn, dd = Pg::group_dim(0, n, kg);
         __asm__ volatile("" : "+v"(nn), "+v"(dd));
-        if (n < G) {
+        if (hn < G) {
             if (direct) {
                 T *o = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
                 const uint32_t at = nn * D + dd;
 #pragma unroll
                 for (int j = 0; j < Pg::GROUPS; ++j)
-                    store_out(o + (at + (uint32_t)Pg::group_dim(j, 0)), Pg::group(ot, j), l > 0.0f ? l : __builtin_inff());
+                    store_out(o + (at + (uint32_t)Pg::group_dim(j, 0, 0)), og[j], l > 0.0f ? l : __builtin_inff());
             } else {
                 float *pt = part_of(rr);
                 const uint32_t at = nn * (D + 2) + dd;
 #pragma unroll
                 for (int j = 0; j < Pg::GROUPS; ++j) {
-                    const f32x4_t x = Pg::group(ot, j);
-                    float *o = pt + (at + (uint32_t)Pg::group_dim(j, 0));
-                    reinterpret_cast<float2 *>(o)[0] = make_float2(x[0], x[1]);
-                    reinterpret_cast<float2 *>(o)[1] = make_float2(x[2], x[3]);
+                    float *o = pt + (at + (uint32_t)Pg::group_dim(j, 0, 0));
+                    reinterpret_cast<float2 *>(o)[0] = make_float2(og[j][0], og[j][1]);
+                    reinterpret_cast<float2 *>(o)[1] = make_float2(og[j][2], og[j][3]);
                 }
-                if (kg == 0) *reinterpret_cast<float2 *>(pt + (nn * (D + 2) + D)) = make_float2(mrun, l);
+                if (n == hn && kg == 0) *reinterpret_cast<float2 *>(pt + (nn * (D + 2) + D)) = make_float2(mrun, l);
             }
         }
     };
@@ -720,7 +835,7 @@ decode_kernel(DecodeArgs a) {
             }
             if (has1) request_keys(nxt.phys);
             if (has) {
-                // online softmax of head n over tokens 4 kg + e
+                // online softmax of the lane's head over tokens 4 kg + e
                 float sc[4], ml = kNegInf;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
@@ -740,7 +855,7 @@ decode_kernel(DecodeArgs a) {
                 mrun = mn;
                 if (__any(alpha != 1.0f)) {           // skip while no head's max has moved
 #pragma unroll
-                    for (int t = 0; t < DT; ++t)
+                    for (int t = 0; t < ACC; ++t)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) ot[t][e] *= alpha;
                 }
@@ -776,14 +891,15 @@ decode_kernel(DecodeArgs a) {
     // ---- the workgroup's merge of the open parts
     if (open_r >= 0) {
         const float l = cross_sum(lrun);
-        if (n < G) {
-            float *o = reinterpret_cast<float *>(mine) + n * D;
+        f32x4_t og[Pg::GROUPS];
+        Pg::gather(ot, og);
+        if (hn < G) {
+            float *o = reinterpret_cast<float *>(mine) + hn * D;
 #pragma unroll
-            for (int j = 0; j < Pg::GROUPS; ++j)
-                *reinterpret_cast<f32x4_t *>(o + Pg::group_dim(j, kg)) = Pg::group(ot, j);
-            if (kg == 0) {
-                s_ml[wave][n][0] = mrun;
-                s_ml[wave][n][1] = l;
+            for (int j = 0; j < Pg::GROUPS; ++j) *reinterpret_cast<f32x4_t *>(o + Pg::group_dim(j, n, kg)) = og[j];
+            if (n == hn && kg == 0) {
+                s_ml[wave][hn][0] = mrun;
+                s_ml[wave][hn][1] = l;
             }
         }
     }
@@ -1214,8 +1330,8 @@ template <typename T, int D>
 hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
     const dim3 grid(a.Hkv, a.W), mgrid(a.Hkv, a.R);
     constexpr bool bf16 = sizeof(T) == 2;
-    constexpr int NW = Page<T, D>::WAVES, NT = 64 * NW;
-    constexpr int NN = Page<T, D>::BYTES <= 2048 ? 4 : NW;        // (see decode_own_narrow)
+    constexpr int NW = waves_of<T, D>(), NT = 64 * NW;
+    constexpr int NN = page_bytes_of<T, D>() <= 2048 ? 4 : NW;        // (see decode_own_narrow)
     // the step variant with a new token and the tails of the shared-prefix
     // decode are their own instantiations, so plain decode attention carries
     // none of their code (a step call's summary update is in the merge pass:

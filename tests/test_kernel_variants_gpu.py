@@ -199,6 +199,67 @@ def test_decode_split(name, spare, dtype, hq, hkv, d):
     assert torch.equal(again[keep], out[keep]) and bool((again[~keep] == 7.0).all())
 
 
+def _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, scale):
+    ps = _state(table, npages, lens, pool)
+    ws = gp.workspace(gp.GP_OP_DECODE, len(lens), 0, hq, hkv, d, table.shape[1], dtype)
+    out = torch.full_like(q, 7.0)
+    gp.gp_decode_attention(kv, ps, q, scale, out, ws)
+    torch.cuda.synchronize()
+    return out
+
+
+@pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 64), (8, 4, 64), (2, 2, 128), (4, 2, 128)])
+def test_decode_weights_in_float32(hq, hkv, d, spare):
+    """One and two query heads per KV head: P.V keeps the weights' float32 bits.
+    Three tokens, weights w0 = 1, wA and wB nearly equal, values 0, 1, -1: the
+    output (wA - wB) / (1 + wA + wB) is of the order of 1e-4, where a weight
+    rounded to 17 bits shows.  Scores are exact in float32 (few-bit factors), so
+    what is left is an exp2 unit of each weight (2^-23 together) and the output's
+    rounding."""
+    _say(f"float32 weights heads {hq}/{hkv} d {d} spare {spare}")
+    gen = torch.Generator().manual_seed(d + hq)
+    R, dtype, G = 48, torch.bfloat16, hq // hkv
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, [3] * R, spare=spare)
+    k, v = kv.k.cpu(), kv.v.cpu()
+    q = torch.randint(-4, 5, (R, hq, d), generator=gen).to(dtype) / 8
+    q[..., 0] = torch.randint(1, 9, (R, hq), generator=gen).to(dtype) / 16
+    for r in range(R):
+        pid = int(table[r, 0])
+        base = torch.randint(-4, 5, (hkv, d), generator=gen).float() / 8
+        base[:, 0] = 1.0
+        k[pid, :, 0] = 0
+        k[pid, :, 1] = (base - 2 * torch.sign((base * q[r, ::G].float()).sum(-1, keepdim=True)) * base).to(dtype)
+        k[pid, :, 2] = k[pid, :, 1]
+        k[pid, :, 2, 0] = k[pid, :, 1, 0] * (1 + 2.0 ** -7)
+        v[pid, :, 0], v[pid, :, 1], v[pid, :, 2] = 0, 1, -1
+    kv, q = gp.KVLayer(k.to(DEV), v.to(DEV)), q.to(DEV)
+    scale = 0.125
+    got = _attend(kv, table, npages, pool, [3] * R, q, hq, hkv, d, dtype, scale).cpu().double()
+    want = _reference(kv.k, kv.v, table, [3] * R, q, scale)
+    bad = (got - want).abs() > want.abs() * 2.0 ** -8 + 2.0 ** -22
+    assert not bad.any(), f"{int(bad.any(-1).sum())} of {R * hq} rows, worst {float((got - want).abs().max()):.2e}"
+
+
+@pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 64), (4, 2, 128)])
+def test_decode_infinite_values(hq, hkv, d, spare):
+    """An infinite value in a resident slot gives that infinity (one and two
+    query heads per KV head, whose weights are one float32 number each)."""
+    _say(f"infinite values heads {hq}/{hkv} d {d} spare {spare}")
+    lens, dtype = [40, 700, 3, 1000, 16], torch.bfloat16
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
+    want = _reference(kv.k, kv.v, table, lens, q, d ** -0.5)
+    for r, m in enumerate(lens):
+        t = (7 * r + 2) % m
+        kv.v[int(table[r, t // 16]), :, t % 16, 5] = float("inf")
+        kv.v[int(table[r, t // 16]), :, t % 16, 9] = -float("inf")
+    got = _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, d ** -0.5)
+    assert bool((got[..., 5] == float("inf")).all()) and bool((got[..., 9] == -float("inf")).all())
+    got[..., [5, 9]] = want[..., [5, 9]].to(DEV, dtype)
+    _check(got, want, dtype, "decode beside infinite values")
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(16, 2, 128), (4, 4, 64), (8, 2, 64)])
 @pytest.mark.parametrize("prefix", [1, 5, 70])
 def test_decode_shared_split(hq, hkv, d, prefix):
