@@ -1,6 +1,7 @@
 // Host side of the C ABI: argument validation, workspace carving and launch.
 // Every entry point checks what the host can see (pointers, shapes, sizes),
 // then enqueues its kernels on the caller's stream and returns.
+#include <float.h>
 #include <math.h>
 
 #include <algorithm>
@@ -239,6 +240,12 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
     a.slots = w.slots;
     a.pslots = w.pslots;
     a.qscale = scale * 1.4426950408889634f;
+    if (kv->dtype == GP_F32) {
+        const double q = (double)scale * 1.4426950408889634;
+        a.qscale = (float)q;
+        if (a.qscale > q) a.qscale = nextafterf(a.qscale, 0.0f);
+        a.qscale_lo = std::max((float)(q - a.qscale), FLT_MIN);
+    }
     return from_hip(launch_decode(kv->dtype, kv->head_dim, num_q_heads / kv->num_kv_heads, a, stages, stream));
 }
 

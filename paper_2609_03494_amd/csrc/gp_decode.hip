@@ -124,6 +124,12 @@ __device__ inline float cross_sum(float x) {
     return __uint_as_float(q[0]) + __uint_as_float(q[1]);
 }
 
+// x of the lane N places before, around the row of 16 lanes
+template <int N>
+__device__ inline float row_ror(float x) {
+    return __uint_as_float(__builtin_amdgcn_update_dpp(0, __float_as_uint(x), 0x120 + N, 0xf, 0xf, false));
+}
+
 // element i (wave-uniform) of an array that nothing writes during the kernel,
 // by a scalar load: it is counted apart from the pages in flight, so waiting for
 // it does not drain them
@@ -279,7 +285,7 @@ struct PageBf16 {
     __device__ static inline uint32_t kread(int n, int kg) { return (n * UPR + (kg ^ (n % UPR))) * 16; }
     // Q of the lane's head as the B operand: unit kk of lane (n, kg) is head dims 32 kk + 8 kg .. + 7
     static constexpr int QREGS = KK;
-    __device__ static inline int qdim(int j, int kg) { return 32 * j + 8 * kg; }
+    __device__ static inline int qdim(int j, int n, int kg) { return 32 * j + 8 * kg; }
     __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
         u32x4_t kx[KK];
         if constexpr (KK == 4) lds_read16(ka, ka ^ 64, ka ^ 128, ka ^ 192, kx[0], kx[1], kx[2], kx[3]);
@@ -381,12 +387,15 @@ struct Page<uint16_t, D, true> : PageBf16<D, true>, QuadOut<D> {
     }
 };
 
-// float32: both products on v_mfma_f32_16x16x4f32 (float32 products and sums).
-// The contraction takes the head dims of a 16-byte key unit one by one, unit
-// 4 j + kg in lane group kg; P.V takes tokens 4 kg + e in step e, so P is in
-// place, and the value units of a row as they lie: row n of O^T tile 4 j + c is
-// dim 64 j + 4 n + c.  Keys are swizzled (u ^ R % 16); a value read is one
-// 256-byte run per row.
+// float32, eight query heads per KV head: both products on
+// v_mfma_f32_16x16x4f32 (float32 products and sums).  The contraction takes the
+// head dims of a 16-byte key unit one by one, unit 4 j + kg in lane group kg; P.V
+// takes tokens 4 kg + e in step e, so P is in place, and the value units of a row
+// as they lie: row n of O^T tile 4 j + c is dim 64 j + 4 n + c.  Keys are
+// swizzled (u ^ R % 16); a value read is one 256-byte run per row.  Every product
+// sums four terms on its own and the sums are added as a tree: chained, a score
+// of d = 128 lost a quarter of a digit more (error against 64 bits 1.4 times as
+// large at one page).
 template <int D>
 struct Page<float, D, false> {
     static constexpr int UPR = D / 4;
@@ -407,29 +416,29 @@ struct Page<float, D, false> {
     __device__ static inline uint32_t kread(int n, int kg) { return (n * UPR + (kg ^ n)) * 16; }
     __device__ static inline uint32_t vread(int n, int kg) { return (4 * kg * UPR + n) * 16; }
     static constexpr int QREGS = NJ;
-    __device__ static inline int qdim(int j, int kg) { return 16 * j + 4 * kg; }
+    __device__ static inline int qdim(int j, int n, int kg) { return 16 * j + 4 * kg; }
+    __device__ static inline f32x4_t mfma4(uint32_t x, uint32_t y) {
+        return __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(x), __uint_as_float(y), f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0, 0, 0);
+    }
     __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
-        f32x4_t st[4];                                // (four short sums per score, added at the end)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) st[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4_t sum = {0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
         for (int j0 = 0; j0 < NJ; j0 += 4) {
             u32x4_t kx[4];
             lds_read16(ka ^ 64 * j0, ka ^ 64 * (j0 + 1), ka ^ 64 * (j0 + 2), ka ^ 64 * (j0 + 3), kx[0], kx[1], kx[2], kx[3]);
+            f32x4_t st[16];                           // sums of four dims, added as a tree
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
+            for (int i = 0; i < 16; ++i) st[i] = mfma4(kx[i / 4][i % 4], q[j0 + i / 4][i % 4]);
 #pragma unroll
-                for (int e = 0; e < 4; ++e)
-                    st[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(__uint_as_float(kx[k][e]), __uint_as_float(q[j0 + k][e]),
-                                                                 st[e], 0, 0, 0);
-            }
+            for (int n = 8; n > 0; n /= 2)
+#pragma unroll
+                for (int c = 0; c < n; ++c) st[c] += st[c + n];
+            sum = j0 == 0 ? st[0] : sum + st[0];
         }
-        return (st[0] + st[1]) + (st[2] + st[3]);
+        return sum;
     }
     __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&ot)[DT], int kg) {
-        f32x4_t pv[DT];                               // (the page's own sum, then added to the run's)
-#pragma unroll
-        for (int t = 0; t < DT; ++t) pv[t] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+        f32x4_t pv[DT];                               // the page's own sum, then added to the run's
 #pragma unroll
         for (int e0 = 0; e0 < 4; e0 += 8 / (D / 32)) {    // four reads at a time
             constexpr int NE = 8 / (D / 32), NU = D / 64; // tokens and units per token of one batch
@@ -437,13 +446,18 @@ struct Page<float, D, false> {
             auto at = [&](int k) { return va + ((e0 + k / NU) * UPR + 16 * (k % NU)) * 16; };
             lds_read16(at(0), at(1), at(2), at(3), vx[0], vx[1], vx[2], vx[3]);
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int e = e0 + k / NU, j = k % NU;
-                const bool in = 4 * kg + e < ntok;
+            for (int j = 0; j < NU; ++j) {
 #pragma unroll
                 for (int c = 0; c < 4; ++c) {
-                    const float v = in ? __uint_as_float(vx[k][c]) : 0.0f;
-                    pv[4 * j + c] = __builtin_amdgcn_mfma_f32_16x16x4f32(v, p[e], pv[4 * j + c], 0, 0, 0);
+                    f32x4_t x[NE];
+#pragma unroll
+                    for (int i = 0; i < NE; ++i)
+                        x[i] = mfma4(4 * kg + e0 + i < ntok ? vx[i * NU + j][c] : 0u, __float_as_uint(p[e0 + i]));
+#pragma unroll
+                    for (int n = NE / 2; n > 0; n /= 2)
+#pragma unroll
+                        for (int i = 0; i < n; ++i) x[i] += x[i + n];
+                    pv[4 * j + c] = e0 == 0 ? x[0] : pv[4 * j + c] + x[0];
                 }
             }
             static_assert(NE * NU == 4, "four reads per batch");
@@ -463,14 +477,88 @@ struct Page<float, D, false> {
     }
 };
 
+// float32, up to four query heads: both products on v_mfma_f32_4x4x1f32, which
+// a page costs a quarter of the cycles of the sixteen columns above (512 at d =
+// 128).  Scores: block (n / 4, kg) of lanes multiplies tokens 4 kg .. + 3 with
+// the four heads over the 16-byte key units n / 4 + 4 j, and the four blocks of
+// a row are added with row rotations, so that the scores of row kg's tokens end
+// in every quad of the row.  Keys are swizzled by u ^ 4 (R % 4): the sixteen
+// units that a row of lanes reads at once lie on distinct banks.
+template <int D>
+struct Page<float, D, true> : QuadOut<D> {
+    static constexpr int UPR = D / 4;
+    static constexpr int BYTES = kPage * D * 4;
+    static constexpr int LOADS = BYTES / 1024;
+    static constexpr int RPI = 64 / UPR;
+    static constexpr int NJ = D / 16, NU = D / 64;
+    static constexpr int ACC = QuadOut<D>::ACC;
+
+    __device__ static inline uint32_t koff(int lane) {
+        const int R = lane / UPR;                     // (% 4, of the first instruction's rows)
+        return (uint32_t)(R * UPR + ((lane % UPR) ^ 4 * R)) * 16;
+    }
+    static constexpr uint32_t kflip(int q) { return q * RPI % 4 * 64; }
+    __device__ static inline uint32_t voff(int lane) { return lane * 16; }
+    static constexpr uint32_t vflip(int) { return 0; }
+    // key operand j: xor 64 j; values of token 4 kg + e, unit n + 16 j: plus (e UPR + 16 j) 16
+    __device__ static inline uint32_t kread(int n, int kg) {
+        return ((4 * kg + n % 4) * UPR + n / 4 + 4 * (n % 4)) * 16;
+    }
+    __device__ static inline uint32_t vread(int n, int kg) { return (4 * kg * UPR + n) * 16; }
+    static constexpr int QREGS = NJ;
+    __device__ static inline int qdim(int j, int n, int kg) { return 16 * j + 4 * (n / 4); }
+    __device__ static inline f32x4_t scores(uint32_t ka, const u32x4_t (&q)[QREGS]) {
+        f32x4_t x = {0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+        for (int j0 = 0; j0 < NJ; j0 += 4) {
+            u32x4_t kx[4];
+            lds_read16(ka ^ 64 * j0, ka ^ 64 * (j0 + 1), ka ^ 64 * (j0 + 2), ka ^ 64 * (j0 + 3), kx[0], kx[1], kx[2], kx[3]);
+            f32x4_t st[4];                            // by the place in the unit (short sums, added as a tree)
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+                    st[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(__uint_as_float(kx[k][e]), __uint_as_float(q[j0 + k][e]),
+                                                               k == 0 ? f32x4_t{0.0f, 0.0f, 0.0f, 0.0f} : st[e], 0, 0, 0);
+            st[0] = (st[0] + st[1]) + (st[2] + st[3]);
+            x = j0 == 0 ? st[0] : x + st[0];
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            x[e] += row_ror<8>(x[e]);
+            x[e] += row_ror<4>(x[e]);
+        }
+        return x;
+    }
+    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&acc)[ACC], int kg) {
+        constexpr int NE = 4 / NU;                    // tokens per four reads
+#pragma unroll
+        for (int e0 = 0; e0 < 4; e0 += NE) {
+            u32x4_t vx[4];
+            auto at = [&](int k) { return va + ((e0 + k / NU) * UPR + 16 * (k % NU)) * 16; };
+            lds_read16(at(0), at(1), at(2), at(3), vx[0], vx[1], vx[2], vx[3]);
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int e = e0 + k / NU, j = k % NU;
+                const bool in = 4 * kg + e < ntok;
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    acc[4 * j + c] = __builtin_amdgcn_mfma_f32_4x4x1f32(in ? __uint_as_float(vx[k][c]) : 0.0f, p[e],
+                                                                        acc[4 * j + c], 0, 0, 0);
+            }
+        }
+    }
+};
+
 template <typename T, int D>
 constexpr int waves_of() { return decode_waves(sizeof(T), D); }
 template <typename T, int D>
 constexpr int page_bytes_of() { return kPage * D * (int)sizeof(T); }
 // The query heads per KV head of which P.V runs in QUAD products.  bfloat16, more
-// heads: the two-term P of four or eight heads costs the matrix cores less.
+// heads: the two-term P of four or eight heads costs the matrix cores less.  float32:
+// as far as one product's columns go.
 template <typename T>
-constexpr bool quad_heads(int G) { return sizeof(T) == 2 && G <= 2; }
+constexpr bool quad_heads(int G) { return sizeof(T) == 2 ? G <= 2 : G <= 4; }
 
 // One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
 // stage + 1024 q (the immediate offset moves source and destination).
@@ -729,12 +817,12 @@ decode_kernel(DecodeArgs a) {
     u32x4_t q[Pg::QREGS];                             // Q of the current request
     // (uniform bases and 32-bit lane offsets, here and in finish: 64-bit lane
     // addresses kept across the loop would cost registers)
-    const uint32_t q_at = (uint32_t)(min(hn, G - 1) * D + Pg::qdim(0, kg));
+    const uint32_t q_at = (uint32_t)(min(hn, G - 1) * D + Pg::qdim(0, n, kg));
     auto load_q = [&](int rr) {
         const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G) * D;
 #pragma unroll
         for (int j = 0; j < Pg::QREGS; ++j) {
-            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + (q_at + (uint32_t)(Pg::qdim(j, 0))));
+            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + (q_at + (uint32_t)(Pg::qdim(j, 0, 0))));
             q[j] = hn < G ? x : u32x4_t{};
         }
     };
@@ -843,12 +931,17 @@ decode_kernel(DecodeArgs a) {
                     ml = fmaxf(ml, sc[e]);
                 }
                 const float mn = fmaxf(mrun, cross_max(ml));
-                // arguments are <= 0: the hardware exp2 needs no range fix-up
+                // arguments are <= 0 (or a rounding above): the hardware exp2 needs no range fix-up
                 const float alpha = mn == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(mrun - mn);
                 float psum = 0.0f;
 #pragma unroll
                 for (int e = 0; e < 4; ++e) {
-                    sc[e] = mn == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(sc[e] - mn);
+                    // float32: the distance to the maximum rounded once, not the score, the
+                    // scale and the distance each (a third of the output's error at d = 64)
+                    float x = sc[e] - mn;
+                    if constexpr (sizeof(T) == 4)
+                        x = 4 * kg + e < ntok ? fmaf(sx[e], a.qscale_lo, fmaf(sx[e], a.qscale, -mn)) : kNegInf;
+                    sc[e] = mn == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(x);
                     psum += sc[e];
                 }
                 lrun = lrun * alpha + psum;

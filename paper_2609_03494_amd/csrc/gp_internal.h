@@ -232,7 +232,8 @@ struct DecodeArgs {
     int g_first[kMaxPrefixGroups], g_num[kMaxPrefixGroups], g_pages[kMaxPrefixGroups];
     int g_blk0[kMaxPrefixGroups + 1], g_slots[kMaxPrefixGroups];
     int R, Hkv, max_pages, pool_pages, W, W1, min_run, slots, pslots;   // W1: workgroups per KV head that fit at once
-    float qscale;   // scale * log2(e)
+    float qscale;      // scale * log2(e); float32 caches: rounded down, and the rest of it
+    float qscale_lo;   // (> 0, so that an infinite score times it keeps its sign)
 };
 
 struct SummaryArgs {

@@ -164,7 +164,8 @@ SPLITS = {
 @pytest.mark.parametrize("name", list(SPLITS))
 @pytest.mark.parametrize("spare", [5, 70, 130])    # a workgroup per request up to 64 columns, or 128 if there are many
 @pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 8, 2, 128), (torch.bfloat16, 3, 3, 64),
-                                            (torch.float32, 8, 1, 128), (torch.float32, 4, 2, 64)])
+                                            (torch.float32, 8, 1, 128), (torch.float32, 4, 2, 64),
+                                            (torch.float32, 4, 1, 128), (torch.float32, 8, 1, 64)])
 def test_decode_split(name, spare, dtype, hq, hkv, d):
     lens = SPLITS[name]
     _say(f"decode split {name} {dtype} heads {hq}/{hkv} d {d} spare table columns {spare}")
@@ -239,6 +240,32 @@ def test_decode_weights_in_float32(hq, hkv, d, spare):
     want = _reference(kv.k, kv.v, table, [3] * R, q, scale)
     bad = (got - want).abs() > want.abs() * 2.0 ** -8 + 2.0 ** -22
     assert not bad.any(), f"{int(bad.any(-1).sum())} of {R * hq} rows, worst {float((got - want).abs().max()):.2e}"
+
+
+@pytest.mark.parametrize("hq,hkv,d", [(12, 12, 64), (32, 8, 128), (16, 2, 128)])
+def test_decode_f32_error(hq, hkv, d):
+    """Large scores (keys of four times the norm) in float32: the output is off
+    by no more than twice what one rounding of every score (in log2 units) and
+    weight to float32 costs -- the score's own sum and its scaling lose about as
+    much again."""
+    _say(f"float32 error heads {hq}/{hkv} d {d}")
+    lens, dtype, scale = [500 + 640 * r for r in range(8)], torch.float32, d ** -0.5
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, seed=5)
+    kv.k.mul_(4)
+    got = _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, scale).cpu().double()
+    want = _reference(kv.k, kv.v, table, lens, q, scale)
+    once = torch.zeros_like(want)
+    k, v, G = kv.k.cpu().double(), kv.v.cpu().double(), hq // hkv
+    s32 = float(np.float32(scale)) * 1.4426950408889634
+    for r, m in enumerate(lens):
+        ids = table[r, :-(-m // 16)].long()
+        K, V = (t[ids].transpose(0, 1).reshape(hkv, -1, d)[:, :m] for t in (k, v))
+        z = (s32 * torch.matmul(q[r].cpu().double().view(hkv, G, d), K.transpose(1, 2).contiguous())).float()
+        w = torch.exp2(z - z.amax(-1, keepdim=True)).double()
+        once[r] = (torch.matmul(w, V) / w.sum(-1, keepdim=True)).view(hq, d)
+    err, bar = float((got - want).norm() / want.norm()), float((once - want).norm() / want.norm())
+    print(f"  error {err:.3e} = {err / bar:.2f} roundings", flush=True)
+    assert err <= 2 * bar, f"error {err:.2e}, one rounding {bar:.2e}"
 
 
 @pytest.mark.parametrize("spare", [2, 130])
