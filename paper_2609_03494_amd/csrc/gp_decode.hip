@@ -931,27 +931,36 @@ decode_kernel(DecodeArgs a) {
                     ml = fmaxf(ml, sc[e]);
                 }
                 const float mn = fmaxf(mrun, cross_max(ml));
-                // arguments are <= 0 (or a rounding above): the hardware exp2 needs no range fix-up
-                const float alpha = mn == kNegInf ? 1.0f : __builtin_amdgcn_exp2f(mrun - mn);
-                float psum = 0.0f;
-#pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    // float32: the distance to the maximum rounded once, not the score, the
-                    // scale and the distance each (a third of the output's error at d = 64)
-                    float x = sc[e] - mn;
-                    if constexpr (sizeof(T) == 4)
-                        x = 4 * kg + e < ntok ? fmaf(sx[e], a.qscale_lo, fmaf(sx[e], a.qscale, -mn)) : kNegInf;
-                    sc[e] = mn == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(x);
-                    psum += sc[e];
-                }
-                lrun = lrun * alpha + psum;
-                mrun = mn;
-                if (__any(alpha != 1.0f)) {           // skip while no head's max has moved
+                const float top = mn == kNegInf ? 0.0f : mn;
+                if (__any(mn != mrun)) {              // skip while no head's max has moved
+                    const float alpha = exp2f(mrun - top);
+                    lrun *= alpha;
 #pragma unroll
                     for (int t = 0; t < ACC; ++t)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) ot[t][e] *= alpha;
+                    mrun = mn;
                 }
+                // weights; the instruction by itself flushes those below 2^-126
+                float lowest = 0.0f;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    // float32: the distance to the maximum rounded once, not the score, the
+                    // scale and the distance each (a third of the output's error at d = 64)
+                    if constexpr (sizeof(T) == 4)
+                        sc[e] = 4 * kg + e < ntok ? fmaf(sx[e], a.qscale_lo, fmaf(sx[e], a.qscale, -top)) : kNegInf;
+                    else
+                        sc[e] -= top;
+                    lowest = fminf(lowest, sc[e]);
+                }
+                if (ntok < kPage || __any(lowest < -126.0f)) {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[e] = exp2f(sc[e]);
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) sc[e] = __builtin_amdgcn_exp2f(sc[e]);
+                }
+                lrun += (sc[0] + sc[1]) + (sc[2] + sc[3]);
                 // the values: requested after them are the next page's keys
                 __builtin_amdgcn_sched_barrier(0);
                 if (has1) __builtin_amdgcn_s_waitcnt(wait_vm(LOADS));
@@ -1028,12 +1037,12 @@ decode_kernel(DecodeArgs a) {
             Ls[e] = Os[e] = 0.0f;
             for (int w = w0; w < w1; ++w) {
                 const float mw = s_ml[w][g][0];
-                const float fw = mw == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(mw - M[e]);
+                const float fw = mw == kNegInf ? 0.0f : exp2f(mw - M[e]);
                 Ls[e] += s_ml[w][g][1] * fw;
                 Os[e] += reinterpret_cast<const float *>(s_wave[w])[i] * fw;
             }
             // (last, as if that wave had left its part open)
-            const float f1_ = m1 == kNegInf ? 0.0f : __builtin_amdgcn_exp2f(m1 - M[e]);
+            const float f1_ = m1 == kNegInf ? 0.0f : exp2f(m1 - M[e]);
             if (more_) {
                 Ls[e] += q[D + 1] * f1_;
                 Os[e] += q[dd] * f1_;

@@ -264,8 +264,30 @@ def test_decode_f32_error(hq, hkv, d):
         w = torch.exp2(z - z.amax(-1, keepdim=True)).double()
         once[r] = (torch.matmul(w, V) / w.sum(-1, keepdim=True)).view(hq, d)
     err, bar = float((got - want).norm() / want.norm()), float((once - want).norm() / want.norm())
-    print(f"  error {err:.3e} = {err / bar:.2f} roundings", flush=True)
     assert err <= 2 * bar, f"error {err:.2e}, one rounding {bar:.2e}"
+
+
+@pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 3, 3, 64), (torch.bfloat16, 8, 2, 128), (torch.float32, 2, 2, 64),
+                                            (torch.float32, 4, 1, 128), (torch.float32, 8, 1, 64)])
+def test_decode_small_weights(dtype, hq, hkv, d, spare):
+    """A weight of 2^-130 beside one of 1 whose value is zero: the result is that
+    weight times its value (a subnormal weight has 2^-150 of absolute error, here
+    2^-20 of the result), with both tokens in one page and in two of them."""
+    _say(f"small weights {dtype} heads {hq}/{hkv} d {d} spare {spare}")
+    lens = [2, 17]
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
+    kv.k.zero_(), kv.v.zero_(), q.zero_()
+    q[..., 0] = 1.0
+    scale = 1.0 / 1.4426950408889634
+    for r, m in enumerate(lens):
+        kv.k[int(table[r, 0]), :, :, 0] = -600.0                # 2^-600: zero beside the others
+        kv.k[int(table[r, 0]), :, 0, 0] = 0.0
+        kv.k[int(table[r, (m - 1) // 16]), :, (m - 1) % 16, 0] = -130.0
+        kv.v[int(table[r, (m - 1) // 16]), :, (m - 1) % 16] = 2.0 ** 100
+    got = _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, scale).cpu().double()
+    # the float32 scale moves 2^-130 by 130 of its roundings at most
+    assert bool(((got / 2.0 ** -30 - 1).abs() < 2.0 ** -16).all()), got.flatten()[:4]
 
 
 @pytest.mark.parametrize("spare", [2, 130])
