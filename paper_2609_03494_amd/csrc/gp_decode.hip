@@ -578,11 +578,10 @@ __device__ inline void load_page(At at, char *stage) {
 
 // four consecutive outputs o / l (l > 0)
 __device__ inline void store_out(uint16_t *p, const f32x4_t &o, float l) {
-    const float inv = 1.0f / l;                       // (far below the bfloat16 rounding that follows)
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     bf16x4_t x;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = (__bf16)(o[e] * inv);
+    for (int e = 0; e < 4; ++e) x[e] = (__bf16)(o[e] / l);
     *reinterpret_cast<bf16x4_t *>(p) = x;
 }
 __device__ inline void store_out(float *p, const f32x4_t &o, float l) {

@@ -291,6 +291,28 @@ def test_decode_small_weights(dtype, hq, hkv, d, spare):
 
 
 @pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("hq,hkv,d", [(3, 3, 64), (8, 2, 128)])
+def test_decode_division(hq, hkv, d, spare):
+    """The output is the sum divided by the weights' sum, rounded once: seven
+    equal weights and values whose sum is seven times the midpoint of two
+    bfloat16 numbers give the even one (the product with a rounded reciprocal
+    misses the midpoint)."""
+    _say(f"division heads {hq}/{hkv} d {d} spare {spare}")
+    dtype, lens = torch.bfloat16, [7]
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
+    mid = (257 + 2 * torch.arange(d) % 256).float() / 256                 # nine significant bits
+    want = mid.to(dtype)
+    pid = int(table[0, 0])
+    kv.k.zero_()
+    kv.v.zero_()
+    high = (7 * mid).to(dtype)
+    kv.v[pid, :, 0], kv.v[pid, :, 3] = high.to(DEV), (7 * mid - high.float()).to(dtype).to(DEV)
+    assert torch.equal(kv.v[pid, 0].cpu().float().sum(0), 7 * mid)
+    got = _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, d ** -0.5).cpu()
+    assert torch.equal(got, want.expand_as(got)), (got != want).sum()
+
+
+@pytest.mark.parametrize("spare", [2, 130])
 @pytest.mark.parametrize("hq,hkv,d", [(3, 3, 64), (4, 2, 128)])
 def test_decode_infinite_values(hq, hkv, d, spare):
     """An infinite value in a resident slot gives that infinity (one and two
