@@ -203,7 +203,8 @@ gp_status_t gp_update_summaries(const void *q_pre, gp_dtype_t dtype, int32_t num
  * out[r][g] = sum_{i < m_r} softmax_i(scale * q_post[r][g] . k_i) v_i, with
  * k_i, v_i read from KV head g / (num_q_heads / num_kv_heads) through the page
  * table.  fp32 accumulation; output in the KV dtype.  A request with m_r == 0
- * gets a zero output; a held request (seq_lens[r] < 0) gets none (its rows of
+ * gets a zero output, and so does a query head whose weights have no positive
+ * sum (a score is NaN, or all are -inf); a held request (seq_lens[r] < 0) gets none (its rows of
  * out are not written, and gp_decode_step leaves its summaries alone).  Page slots at or beyond m_r are never used, whatever
  * they hold.  The work is split over the pages of the whole batch, so the
  * float32 sums of a request run in an order that depends on the lengths of the

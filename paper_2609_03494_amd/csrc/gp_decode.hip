@@ -576,16 +576,19 @@ __device__ inline void load_page(At at, char *stage) {
     }
 }
 
-// four consecutive outputs o / l (l > 0)
+// One output: a sum of weights that is not positive (no tokens, scores of -inf or
+// NaN) gives zero, in whichever pass the output is written.
+__device__ inline float divided(float o, float l) { return l > 0.0f ? o / l : 0.0f; }
+// four consecutive outputs
 __device__ inline void store_out(uint16_t *p, const f32x4_t &o, float l) {
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
     bf16x4_t x;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) x[e] = (__bf16)(o[e] / l);
+    for (int e = 0; e < 4; ++e) x[e] = (__bf16)divided(o[e], l);
     *reinterpret_cast<bf16x4_t *>(p) = x;
 }
 __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
-    *reinterpret_cast<f32x4_t *>(p) = f32x4_t{o[0] / l, o[1] / l, o[2] / l, o[3] / l};
+    *reinterpret_cast<f32x4_t *>(p) = f32x4_t{divided(o[0], l), divided(o[1], l), divided(o[2], l), divided(o[3], l)};
 }
 
 // MODE 0: decode attention; 1: gp_decode_step with the step's new token (the
@@ -644,7 +647,7 @@ decode_kernel(DecodeArgs a) {
         }
         if (v.n == 0 && !v.held) {                    // no tokens
             T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-            for (int i = 4 * tid; i < G * D; i += 4 * NT) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
+            for (int i = 4 * tid; i < G * D; i += 4 * NT) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0.0f);
         }
     } else {
         // ---- the split: U pages in all, L per wave; the request at the run's start.
@@ -697,7 +700,7 @@ decode_kernel(DecodeArgs a) {
                 }
                 if (np == 0 && !v.held) {
                     T *o = reinterpret_cast<T *>(a.out) + ((size_t)r * Hq + (size_t)h * G) * D;
-                    for (int i = 0; i < G * D; i += 4) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 1.0f);
+                    for (int i = 0; i < G * D; i += 4) store_out(o + i, f32x4_t{0.0f, 0.0f, 0.0f, 0.0f}, 0.0f);
                 }
             }
         }
@@ -848,7 +851,7 @@ decode_kernel(DecodeArgs a) {
                 const uint32_t at = nn * D + dd;
 #pragma unroll
                 for (int j = 0; j < Pg::GROUPS; ++j)
-                    store_out(o + (at + (uint32_t)Pg::group_dim(j, 0, 0)), og[j], l > 0.0f ? l : __builtin_inff());
+                    store_out(o + (at + (uint32_t)Pg::group_dim(j, 0, 0)), og[j], l);
             } else {
                 float *pt = part_of(rr);
                 const uint32_t at = nn * (D + 2) + dd;
@@ -1053,7 +1056,7 @@ decode_kernel(DecodeArgs a) {
             const int i = tid + e * NT, g = i / D, dd = i % D;
             if (i >= G * D) continue;
             if (direct) {
-                Traits<T>::store(out + i, Ls[e] > 0.0f ? Os[e] / Ls[e] : 0.0f);
+                Traits<T>::store(out + i, divided(Os[e], Ls[e]));
             } else {
                 pt[(size_t)g * (D + 2) + dd] = Os[e];
                 if (dd == 0) *reinterpret_cast<float2 *>(pt + (size_t)g * (D + 2) + D) = make_float2(M[e], Ls[e]);
@@ -1409,8 +1412,8 @@ __global__ __launch_bounds__(NT) void merge_kernel(DecodeArgs a) {
 #pragma unroll
             for (int e = 0; e < EP; ++e) {
                 const int i = 2 * (NS > 1 ? tid : tid + e * NT);
-                Tr::store(out + i, Ls[e] > 0.0f ? Ox[e] / Ls[e] : 0.0f);
-                Tr::store(out + i + 1, Ls[e] > 0.0f ? Oy[e] / Ls[e] : 0.0f);
+                Tr::store(out + i, divided(Ox[e], Ls[e]));
+                Tr::store(out + i + 1, divided(Oy[e], Ls[e]));
             }
         }
     }

@@ -313,6 +313,26 @@ def test_decode_division(hq, hkv, d, spare):
 
 
 @pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 3, 3, 64), (torch.bfloat16, 8, 2, 128), (torch.float32, 4, 2, 64),
+                                            (torch.float32, 8, 1, 128)])
+def test_decode_nan_scores(dtype, hq, hkv, d, spare):
+    """A NaN key gives a zero output, however the batch's split cuts its request
+    (one wave, several waves of a workgroup, several workgroups); the others'
+    outputs are theirs."""
+    _say(f"NaN scores {dtype} heads {hq}/{hkv} d {d} spare {spare}")
+    lens = [5, 16, 17, 300, 40, 1000, 900, 2000 if spare > 64 else 1, 33]
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
+    scale = d ** -0.5
+    want = _reference(kv.k, kv.v, table, lens, q, scale)
+    for r in (0, 2, 3, 5, 7):
+        t = lens[r] * 2 // 3
+        kv.k[int(table[r, t // 16]), :, t % 16, 3] = float("nan")
+        want[r] = 0.0
+    got = _attend(kv, table, npages, pool, lens, q, hq, hkv, d, dtype, scale)
+    _check(got, want, dtype, "decode beside NaN")
+
+
+@pytest.mark.parametrize("spare", [2, 130])
 @pytest.mark.parametrize("hq,hkv,d", [(3, 3, 64), (4, 2, 128)])
 def test_decode_infinite_values(hq, hkv, d, spare):
     """An infinite value in a resident slot gives that infinity (one and two
