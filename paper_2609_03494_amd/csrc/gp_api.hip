@@ -208,6 +208,7 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
     }
     a.k = kv->k;
     a.v = kv->v;
+    a.aligned = (reinterpret_cast<uintptr_t>(kv->k) | reinterpret_cast<uintptr_t>(kv->v)) % 16 == 0;
     a.page_table = ps->page_table;
     a.num_pages = ps->num_pages;
     a.seq_lens = ps->seq_lens;

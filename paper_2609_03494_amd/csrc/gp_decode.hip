@@ -54,6 +54,18 @@ typedef unsigned int u32x2_t __attribute__((ext_vector_type(2)));
 typedef __attribute__((ext_vector_type(8))) __bf16 bf16x8_t;
 typedef __attribute__((ext_vector_type(4))) float f32x4_t;
 typedef short bf16x4s_t __attribute__((ext_vector_type(4)));
+// 16 and 8 bytes as a caller's buffers may lie: at any multiple of the element
+typedef u32x4_t u32x4_e2_t __attribute__((aligned(2)));
+typedef u32x4_t u32x4_e4_t __attribute__((aligned(4)));
+typedef f32x4_t f32x4_e4_t __attribute__((aligned(4)));
+typedef float f32x2_t __attribute__((ext_vector_type(2)));
+typedef f32x2_t f32x2_e4_t __attribute__((aligned(4)));
+__device__ inline u32x4_t load16(const uint16_t *p) { return *reinterpret_cast<const u32x4_e2_t *>(p); }
+__device__ inline u32x4_t load16(const float *p) { return *reinterpret_cast<const u32x4_e4_t *>(p); }
+__device__ inline void store16(uint16_t *p, const u32x4_t &x) { *reinterpret_cast<u32x4_e2_t *>(p) = x; }
+__device__ inline void store16(float *p, const u32x4_t &x) { *reinterpret_cast<u32x4_e4_t *>(p) = x; }
+__device__ inline f32x2_t load8(const float *p) { return *reinterpret_cast<const f32x2_e4_t *>(p); }
+__device__ inline void store8(float *p, float x, float y) { *reinterpret_cast<f32x2_e4_t *>(p) = f32x2_t{x, y}; }
 
 // s_waitcnt immediates: vmcnt(0) (vmcnt in bits 3:0 and 15:14, the others at
 // their maximum); and the cache-policy operand of a direct-to-LDS load that
@@ -562,8 +574,19 @@ constexpr bool quad_heads(int G) { return sizeof(T) == 2 ? G <= 2 : G <= 4; }
 
 // One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
 // stage + 1024 q (the immediate offset moves source and destination).
-template <int LOADS, typename At>
-__device__ inline void load_page(At at, char *stage) {
+// Direct-to-LDS loads of 16 bytes want addresses that are multiples of 16; float32
+// pools that lie at another multiple of 4 go through registers.
+template <int LOADS, bool ANY, typename At>
+__device__ inline void load_page(At at, char *stage, bool aligned, int lane) {
+    if constexpr (ANY) {
+        if (!aligned) {                               // (uniform over the grid)
+#pragma unroll
+            for (int q = 0; q < LOADS; ++q)
+                *reinterpret_cast<u32x4_t *>(stage + q * 1024 + lane * 16) =
+                    load16(reinterpret_cast<const float *>(at(q) + q % 4 * 1024));
+            return;
+        }
+    }
 #pragma unroll
     for (int q = 0; q < LOADS; q += 4) {
         lds_void_t *const to = (lds_void_t *)(stage + q * 1024);
@@ -582,13 +605,14 @@ __device__ inline float divided(float o, float l) { return l > 0.0f ? o / l : 0.
 // four consecutive outputs
 __device__ inline void store_out(uint16_t *p, const f32x4_t &o, float l) {
     typedef __bf16 bf16x4_t __attribute__((ext_vector_type(4)));
+    typedef bf16x4_t bf16x4_e2_t __attribute__((aligned(2)));
     bf16x4_t x;
 #pragma unroll
     for (int e = 0; e < 4; ++e) x[e] = (__bf16)divided(o[e], l);
-    *reinterpret_cast<bf16x4_t *>(p) = x;
+    *reinterpret_cast<bf16x4_e2_t *>(p) = x;
 }
 __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
-    *reinterpret_cast<f32x4_t *>(p) = f32x4_t{divided(o[0], l), divided(o[1], l), divided(o[2], l), divided(o[3], l)};
+    *reinterpret_cast<f32x4_e4_t *>(p) = f32x4_t{divided(o[0], l), divided(o[1], l), divided(o[2], l), divided(o[3], l)};
 }
 
 // MODE 0: decode attention; 1: gp_decode_step with the step's new token (the
@@ -739,12 +763,14 @@ decode_kernel(DecodeArgs a) {
     auto request_keys = [&](int phys) {
         const char *src = kpool + (size_t)phys * page_bytes;
         __asm__ volatile("" : "+v"(ko));
-        load_page<LOADS>([&](int q) { return src + (size_t)((ko ^ Pg::kflip(q)) + (q - q % 4) * 1024u); }, mine);
+        load_page<LOADS, sizeof(T) == 4>([&](int q) { return src + (size_t)((ko ^ Pg::kflip(q)) + (q - q % 4) * 1024u); }, mine,
+                                        a.aligned, lane);
     };
     auto request_values = [&](int phys) {
         const char *src = vpool + (size_t)phys * page_bytes;
         __asm__ volatile("" : "+v"(vo));
-        load_page<LOADS>([&](int q) { return src + (size_t)((vo ^ Pg::vflip(q)) + (q - q % 4) * 1024u); }, mine + Pg::BYTES);
+        load_page<LOADS, sizeof(T) == 4>([&](int q) { return src + (size_t)((vo ^ Pg::vflip(q)) + (q - q % 4) * 1024u); },
+                                        mine + Pg::BYTES, a.aligned, lane);
     };
 
     // ---- one request's part of the run: pages [p, pend) of its covered pages
@@ -784,10 +810,11 @@ decode_kernel(DecodeArgs a) {
                 if (lane < 2 * NU && id >= 0 && id < a.pool_pages) {
                     const bool isv = lane >= NU;
                     const int u = isv ? lane - NU : lane;
-                    const u32x4_t x = reinterpret_cast<const u32x4_t *>(
-                        reinterpret_cast<const T *>(isv ? a.v_new : a.k_new) + ((size_t)r * Hkv + h) * D)[u];
-                    reinterpret_cast<u32x4_t *>(reinterpret_cast<T *>(isv ? a.v_w : a.k_w) +
-                                                (((size_t)id * Hkv + h) * kPage + slot) * D)[u] = x;
+                    constexpr int EPU = 16 / (int)sizeof(T);
+                    const u32x4_t x = load16(reinterpret_cast<const T *>(isv ? a.v_new : a.k_new) +
+                                             ((size_t)r * Hkv + h) * D + u * EPU);
+                    store16(reinterpret_cast<T *>(isv ? a.v_w : a.k_w) +
+                                (((size_t)id * Hkv + h) * kPage + slot) * D + u * EPU, x);
                 }
                 // (rare: once per request and head) the row is in memory before its page is requested
                 __builtin_amdgcn_s_waitcnt(kWaitVm0);
@@ -824,7 +851,7 @@ decode_kernel(DecodeArgs a) {
         const T *src = reinterpret_cast<const T *>(a.q) + ((size_t)rr * Hq + (size_t)h * G) * D;
 #pragma unroll
         for (int j = 0; j < Pg::QREGS; ++j) {
-            const u32x4_t x = *reinterpret_cast<const u32x4_t *>(src + (q_at + (uint32_t)(Pg::qdim(j, 0, 0))));
+            const u32x4_t x = load16(src + (q_at + (uint32_t)(Pg::qdim(j, 0, 0))));
             q[j] = hn < G ? x : u32x4_t{};
         }
     };
@@ -858,10 +885,10 @@ decode_kernel(DecodeArgs a) {
 #pragma unroll
                 for (int j = 0; j < Pg::GROUPS; ++j) {
                     float *o = pt + (at + (uint32_t)Pg::group_dim(j, 0, 0));
-                    reinterpret_cast<float2 *>(o)[0] = make_float2(og[j][0], og[j][1]);
-                    reinterpret_cast<float2 *>(o)[1] = make_float2(og[j][2], og[j][3]);
+                    store8(o, og[j][0], og[j][1]);
+                    store8(o + 2, og[j][2], og[j][3]);
                 }
-                if (n == hn && kg == 0) *reinterpret_cast<float2 *>(pt + (nn * (D + 2) + D)) = make_float2(mrun, l);
+                if (n == hn && kg == 0) store8(pt + (nn * (D + 2) + D), mrun, l);
             }
         }
     };
@@ -1059,7 +1086,7 @@ decode_kernel(DecodeArgs a) {
                 Traits<T>::store(out + i, divided(Os[e], Ls[e]));
             } else {
                 pt[(size_t)g * (D + 2) + dd] = Os[e];
-                if (dd == 0) *reinterpret_cast<float2 *>(pt + (size_t)g * (D + 2) + D) = make_float2(M[e], Ls[e]);
+                if (dd == 0) store8(pt + (size_t)g * (D + 2) + D, M[e], Ls[e]);
             }
         }
         w0 = w1;
@@ -1166,7 +1193,7 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
                              ((size_t)(rowq ? r0 + jq : first) * Hq + (size_t)h * G + n % G) * D;
 #pragma unroll
         for (int kk = 0; kk < KK; ++kk) {
-            const bf16x8_t x = *reinterpret_cast<const bf16x8_t *>(qp + kk * 32 + kg * 8);
+            const bf16x8_t x = __builtin_bit_cast(bf16x8_t, load16(qp + kk * 32 + kg * 8));
             qb[kk] = rowq ? x : bf16x8_t{};
         }
     }
@@ -1282,7 +1309,7 @@ __global__ __launch_bounds__(64 * kPrefixWaves) void prefix_kernel(DecodeArgs a)
         float *part = a.prefix + (((size_t)(r0 + jq) * Hkv + h) * a.pslots + c) * G * (D + 2) +
                       (size_t)(n % G) * (D + 2);
 #pragma unroll
-        for (int t = 0; t < DT; ++t) *reinterpret_cast<f32x4_t *>(part + 16 * t + 4 * kg) = o[t];
+        for (int t = 0; t < DT; ++t) *reinterpret_cast<f32x4_e4_t *>(part + 16 * t + 4 * kg) = o[t];
         if (kg == 0) {
             part[D] = mrun;
             part[D + 1] = lrun;
@@ -1362,18 +1389,18 @@ __global__ __launch_bounds__(NT) void merge_kernel(DecodeArgs a) {
             M[e] = kNegInf;
             Ls[e] = Ox[e] = Oy[e] = 0.0f;
             for (int k0 = sg; k0 < total; k0 += NS * BATCH) {
-                float2 ml[BATCH], o[BATCH];
+                f32x2_t ml[BATCH], o[BATCH];
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b) {
                     const int k = min(k0 + b * NS, total - 1);
                     const float *q = (k < npre ? pp + (size_t)k * G * (D + 2) : pt + (size_t)(k - npre) * G * (D + 2)) + off;
-                    ml[b] = *reinterpret_cast<const float2 *>(q + D);
-                    o[b] = *reinterpret_cast<const float2 *>(q + i % D);
+                    ml[b] = load8(q + D);
+                    o[b] = load8(q + i % D);
                 }
                 float mn = M[e];
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b)
-                    if (k0 + b * NS < total) mn = fmaxf(mn, ml[b].x);
+                    if (k0 + b * NS < total) mn = fmaxf(mn, ml[b][0]);
                 const float f0 = M[e] == kNegInf ? 0.0f : exp2f(M[e] - mn);
                 Ls[e] *= f0;
                 Ox[e] *= f0;
@@ -1381,11 +1408,11 @@ __global__ __launch_bounds__(NT) void merge_kernel(DecodeArgs a) {
                 M[e] = mn;
 #pragma unroll
                 for (int b = 0; b < BATCH; ++b) {
-                    if (k0 + b * NS < total && ml[b].x != kNegInf) {
-                        const float f = exp2f(ml[b].x - mn);
-                        Ls[e] += ml[b].y * f;
-                        Ox[e] += o[b].x * f;
-                        Oy[e] += o[b].y * f;
+                    if (k0 + b * NS < total && ml[b][0] != kNegInf) {
+                        const float f = exp2f(ml[b][0] - mn);
+                        Ls[e] += ml[b][1] * f;
+                        Ox[e] += o[b][0] * f;
+                        Oy[e] += o[b][1] * f;
                     }
                 }
             }

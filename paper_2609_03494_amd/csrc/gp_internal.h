@@ -206,6 +206,7 @@ constexpr int kPrefixWaves = 4;           // waves per workgroup of the shared-p
 
 struct DecodeArgs {
     const void *k, *v;
+    bool aligned;                 // k and v are multiples of 16 (float32: others take a slower path)
     const int32_t *page_table, *num_pages, *seq_lens;
     const void *q;
     void *out;

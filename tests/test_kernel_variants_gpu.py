@@ -351,6 +351,41 @@ def test_decode_infinite_values(hq, hkv, d, spare):
     _check(got, want, dtype, "decode beside infinite values")
 
 
+@pytest.mark.parametrize("spare", [2, 130])
+@pytest.mark.parametrize("offset", [1, 2])
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.float32, 4, 2, 64), (torch.float32, 4, 1, 128), (torch.float32, 8, 1, 64),
+                                            (torch.bfloat16, 8, 2, 128), (torch.bfloat16, 3, 3, 64)])
+def test_decode_unaligned(dtype, hq, hkv, d, offset, spare):
+    """Buffers one or two elements into their allocations (bfloat16 pools excepted)
+    give the bytes of aligned ones: decode attention, and a step with a token."""
+    _say(f"unaligned {dtype} heads {hq}/{hkv} d {d} offset {offset} spare {spare}")
+    lens = [1, 40, 0, 700, 16, 77, 1500 if spare > 64 else 33]
+    R, scale = len(lens), d ** -0.5
+    kv, table, npages, pool, q = _decode_case(dtype, hq, hkv, d, lens, spare=spare)
+    gen = torch.Generator().manual_seed(3)
+    rand = lambda *s: torch.randn(*s, generator=gen).to(dtype).to(DEV)
+    q_pre, k_new, v_new = rand(R, hq, d), rand(R, hkv, d), rand(R, hkv, d)
+    qs = torch.randn(R, 2, hq, d, generator=gen).to(DEV)
+    slots, init = torch.arange(R, dtype=torch.int32, device=DEV), torch.zeros(R, dtype=torch.uint8, device=DEV)
+    n = gp.gp_workspace_bytes(gp.GP_OP_DECODE, R, 0, hq, hkv, d, table.shape[1], dtype)
+    results = []
+    for off in (0, offset):
+        at = lambda t: _offset(t, off)
+        pool_at = at if dtype == torch.float32 else torch.clone
+        layer = gp.KVLayer(pool_at(kv.k), pool_at(kv.v))
+        ps = _state(table, npages, lens, pool)
+        ws = torch.zeros(n + 16, dtype=torch.uint8, device=DEV)[4 * off:4 * off + n]
+        out, out2, qstate = at(torch.full_like(q, 7.0)), at(torch.full_like(q, 7.0)), at(qs)
+        gp.gp_decode_attention(layer, ps, at(q), scale, out, ws)
+        gp.gp_decode_step(layer, ps, at(q), at(q_pre), scale, out2, slots, init, qstate, 0.9, 0.999, ws, at(k_new),
+                          at(v_new), torch.zeros(R, dtype=torch.int32, device=DEV))
+        torch.cuda.synchronize()
+        results.append([out, out2, qstate, layer.k, layer.v, ps.seq_lens])
+    for a, b in zip(*results):
+        assert torch.equal(a.contiguous().view(torch.uint8), b.contiguous().view(torch.uint8))
+    _check(results[1][0], _reference(kv.k, kv.v, table, lens, q, scale), dtype, "decode")
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(16, 2, 128), (4, 4, 64), (8, 2, 64)])
 @pytest.mark.parametrize("prefix", [1, 5, 70])
 def test_decode_shared_split(hq, hkv, d, prefix):
