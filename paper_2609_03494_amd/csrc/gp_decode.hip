@@ -656,6 +656,7 @@ decode_kernel(DecodeArgs a) {
     // this wave's run [f0, f1) of the flat list; the request at f0, its first page's
     // place in the list, and its length
     int f0, f1, r = -1, a0 = 0, m_in = 0, P_in = 0;
+    int parts = 0;                                    // OWN: waves that have a part of the request
     if constexpr (OWN > 0) {
         r = wg;
         m_in = scalar_load(a.seq_lens, r);
@@ -664,6 +665,7 @@ decode_kernel(DecodeArgs a) {
         const int run = cdiv(v.n, NW);
         f0 = min(wave * run, v.n);
         f1 = v.held ? f0 : min(f0 + run, v.n);
+        parts = v.held || v.n == 0 ? 0 : cdiv(v.n, run);
         if (h == 0 && tid == 0) {                     // for the merge pass (see below): nothing to fold
             a.lens[r] = v.held ? -1 : v.m_attn;
             a.lens[R + r] = v.room ? 1 : 0;
@@ -1034,24 +1036,11 @@ decode_kernel(DecodeArgs a) {
             }
         }
     }
-    if (lane == 0) {
-        s_open[wave][0] = open_r;
-        s_open[wave][1] = (open_first ? 1 : 0) | (open_last ? 2 : 0) | (open_tail ? 4 : 0);
-        s_open[wave][2] = wrote_r;
-    }
-    __syncthreads();
-    for (int w0 = 0; w0 < NW;) {
-        const int rr = uni(s_open[w0][0]);
-        if (rr < 0) {
-            ++w0;
-            continue;
-        }
-        int w1 = w0 + 1;                              // waves [w0, w1) left parts of request rr open
-        while (w1 < NW && uni(s_open[w1][0]) == rr) ++w1;
-        // the wave after them may have written the rest of rr as this workgroup's partial
-        const bool more_ = w1 < NW && uni(s_open[w1][2]) == rr;
-        const bool all = (uni(s_open[w0][1]) & 1) && (more_ || (uni(s_open[w1 - 1][1]) & 2));
-        const bool direct = all && !(uni(s_open[w0][1]) & 4);
+    // the parts of waves [w0, w1) of request rr (m1, pt: and the partial that the
+    // wave after them wrote, folded last, as if it had left its part open).  All
+    // waves' values are requested at once, whichever count: a loop over the waves
+    // paid an LDS latency for each (1.5 us of a call).
+    auto fold = [&](int w0, int w1, int rr, bool more_, bool direct) {
         float *pt = part_of(rr);
         T *out = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
         constexpr int EPT = (G * D + NT - 1) / NT;
@@ -1061,16 +1050,27 @@ decode_kernel(DecodeArgs a) {
             const int i = min(tid + e * NT, G * D - 1), g = i / D, dd = i % D;
             const float *q = pt + (size_t)g * (D + 2);
             const float m1 = more_ ? q[D] : kNegInf;
-            M[e] = m1;
-            for (int w = w0; w < w1; ++w) M[e] = fmaxf(M[e], s_ml[w][g][0]);
-            Ls[e] = Os[e] = 0.0f;
-            for (int w = w0; w < w1; ++w) {
-                const float mw = s_ml[w][g][0];
-                const float fw = mw == kNegInf ? 0.0f : exp2f(mw - M[e]);
-                Ls[e] += s_ml[w][g][1] * fw;
-                Os[e] += reinterpret_cast<const float *>(s_wave[w])[i] * fw;
+            float mw[NW], lw[NW], ow[NW];
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                mw[w] = s_ml[w][g][0];
+                lw[w] = s_ml[w][g][1];
+                ow[w] = reinterpret_cast<const float *>(s_wave[w])[i];
             }
-            // (last, as if that wave had left its part open)
+            M[e] = m1;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (w < w0 || w >= w1) mw[w] = kNegInf;
+                M[e] = fmaxf(M[e], mw[w]);
+            }
+            Ls[e] = Os[e] = 0.0f;
+#pragma unroll
+            for (int w = 0; w < NW; ++w) {
+                if (w < w0 || w >= w1) continue;      // (uniform)
+                const float fw = mw[w] == kNegInf ? 0.0f : exp2f(mw[w] - M[e]);
+                Ls[e] += lw[w] * fw;
+                Os[e] += ow[w] * fw;
+            }
             const float f1_ = m1 == kNegInf ? 0.0f : exp2f(m1 - M[e]);
             if (more_) {
                 Ls[e] += q[D + 1] * f1_;
@@ -1089,7 +1089,33 @@ decode_kernel(DecodeArgs a) {
                 if (dd == 0) store8(pt + (size_t)g * (D + 2) + D, M[e], Ls[e]);
             }
         }
-        w0 = w1;
+    };
+    if constexpr (OWN > 0) {
+        __syncthreads();
+        if (parts > 1) fold(0, parts, wg, false, true);    // (one part: its wave wrote the output)
+    } else {
+        if (lane == 0) {
+            s_open[wave][0] = open_r;
+            s_open[wave][1] = (open_first ? 1 : 0) | (open_last ? 2 : 0) | (open_tail ? 4 : 0);
+            s_open[wave][2] = wrote_r;
+        }
+        __syncthreads();
+        const int reqs = s_open[lane % NW][0], ends = s_open[lane % NW][1], wrote = s_open[lane % NW][2];
+        for (int w0 = 0; w0 < NW;) {
+            const int rr = __builtin_amdgcn_readlane(reqs, w0);
+            if (rr < 0) {
+                ++w0;
+                continue;
+            }
+            int w1 = w0 + 1;                          // waves [w0, w1) left parts of request rr open
+            while (w1 < NW && __builtin_amdgcn_readlane(reqs, w1) == rr) ++w1;
+            // the wave after them may have written the rest of rr as this workgroup's partial
+            const bool more_ = w1 < NW && __builtin_amdgcn_readlane(wrote, w1) == rr;
+            const int begin = __builtin_amdgcn_readlane(ends, w0), end = __builtin_amdgcn_readlane(ends, w1 - 1);
+            const bool all = (begin & 1) && (more_ || (end & 2));
+            fold(w0, w1, rr, more_, all && !(begin & 4));
+            w0 = w1;
+        }
     }
 }
 
