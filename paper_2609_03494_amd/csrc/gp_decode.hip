@@ -615,6 +615,17 @@ __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
     *reinterpret_cast<f32x4_e4_t *>(p) = f32x4_t{divided(o[0], l), divided(o[1], l), divided(o[2], l), divided(o[3], l)};
 }
 
+// Waves per SIMD that the registers are to leave room for.  Workgroups of one
+// request at 2 KB pages: 6 and 5 (80 and 96 registers); held to 64 registers they
+// spilled up to 9 of them, 5-20 % of a step with a token, and nothing was gained by
+// the room (256 requests of 64-200 tokens, 8/4 heads: 9.0 us a call at 5, 6 or 7).
+template <typename T, int D, int OWN>
+constexpr int decode_occupancy() {
+    if (waves_of<T, D>() < 8) return 2;
+    if (OWN == 0 || page_bytes_of<T, D>() > 2048) return 4;
+    return OWN < waves_of<T, D>() ? 6 : 5;
+}
+
 // MODE 0: decode attention; 1: gp_decode_step with the step's new token (the
 // summary update is in the merge pass); 2: the private tails of
 // gp_decode_attention_shared.
@@ -630,7 +641,7 @@ __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
 // OWN > 0: short tables, workgroup r of OWN waves takes request r (see decode_own).
 template <typename T, int D, int G, int MODE, int OWN>
 __global__ __launch_bounds__((64 * (OWN ? OWN : waves_of<T, D>())))
-    __attribute__((amdgpu_waves_per_eu(page_bytes_of<T, D>() <= 2048 && OWN && G <= 4 ? 8 : waves_of<T, D>() >= 8 ? 4 : 2))) void
+    __attribute__((amdgpu_waves_per_eu(decode_occupancy<T, D, OWN>()))) void
 decode_kernel(DecodeArgs a) {
     static_assert(!OWN || MODE != 2, "a shared-prefix call is always merged");
     constexpr bool STEP = MODE == 1, PREFIX = MODE == 2;
@@ -1447,10 +1458,11 @@ __global__ __launch_bounds__(NT) void merge_kernel(DecodeArgs a) {
             s_red[tid] = make_float4(M[0], Ls[0], Ox[0], Oy[0]);
             __syncthreads();
             if (tid < GD2) {
-#pragma unroll
-                for (int k = 1; k < NS; ++k) M[0] = fmaxf(M[0], s_red[tid + k * GD2].x);
+                // (sixteen at a time: all 32 of a small head at once do not fit the registers)
+#pragma unroll 16
+                for (int k = 0; k < NS; ++k) M[0] = fmaxf(M[0], s_red[tid + k * GD2].x);
                 Ls[0] = Ox[0] = Oy[0] = 0.0f;
-#pragma unroll
+#pragma unroll 16
                 for (int k = 0; k < NS; ++k) {
                     const float4 x = s_red[tid + k * GD2];
                     const float f = x.x == kNegInf ? 0.0f : exp2f(x.x - M[0]);
