@@ -326,7 +326,15 @@ struct Page<uint16_t, D, false> : PageBf16<D, false> {
     }
     // O^T += V^T.P^T; ntok: tokens of the page (slots past the last may hold
     // anything: 0 x inf would reach o, so they read as zero)
-    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&ot)[DT], int kg) {
+    static constexpr int VREGS = DT;
+    typedef u32x2_t v_t;
+    __device__ static inline void read_values(uint32_t va, int, v_t (&vx)[VREGS]) {
+#pragma unroll
+        for (int t = 0; t < DT; t += 4)
+            lds_read_tr(va ^ 32 * t, va ^ 32 * (t + 1), va ^ 32 * (t + 2), va ^ 32 * (t + 3), vx[t], vx[t + 1], vx[t + 2], vx[t + 3]);
+    }
+    __device__ static inline void weigh(uint32_t va, v_t (&vx)[VREGS], bool read, const float (&p)[4], int ntok,
+                                        f32x4_t (&ot)[DT], int kg) {
         bf16x4s_t phi, plo;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -336,18 +344,20 @@ struct Page<uint16_t, D, false> : PageBf16<D, false> {
         }
 #pragma unroll
         for (int t0 = 0; t0 < DT; t0 += 4) {
-            u32x2_t vx[4];
-            lds_read_tr(va ^ 32 * t0, va ^ 32 * (t0 + 1), va ^ 32 * (t0 + 2), va ^ 32 * (t0 + 3), vx[0], vx[1], vx[2], vx[3]);
+            if (!read) {
+                u32x2_t *x = vx + t0;
+                lds_read_tr(va ^ 32 * t0, va ^ 32 * (t0 + 1), va ^ 32 * (t0 + 2), va ^ 32 * (t0 + 3), x[0], x[1], x[2], x[3]);
+            }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                bf16x4s_t vt = __builtin_bit_cast(bf16x4s_t, vx[k]);
+            for (int t = t0; t < t0 + 4; ++t) {
+                bf16x4s_t vt = __builtin_bit_cast(bf16x4s_t, vx[t]);
                 if (ntok < kPage) {                       // wave-uniform
 #pragma unroll
                     for (int e = 0; e < 4; ++e)
                         if (4 * kg + e >= ntok) vt[e] = 0;
                 }
-                ot[t0 + k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t0 + k], 0, 0, 0);
-                ot[t0 + k] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t0 + k], 0, 0, 0);
+                ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, phi, ot[t], 0, 0, 0);
+                ot[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(vt, plo, ot[t], 0, 0, 0);
             }
         }
     }
@@ -377,12 +387,17 @@ struct Page<uint16_t, D, true> : PageBf16<D, true>, QuadOut<D> {
     __device__ static inline uint32_t vtoken(uint32_t va, int e, int kg) {
         return D == 64 ? va + (e ^ (kg & 1)) * UPR * 16 : va + e * UPR * 16;
     }
-    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&acc)[ACC], int kg) {
-        u32x2_t vx[4 * NU];
+    static constexpr int VREGS = 4 * NU;
+    typedef u32x2_t v_t;
+    __device__ static inline void read_values(uint32_t va, int kg, v_t (&vx)[VREGS]) {
 #pragma unroll
         for (int j = 0; j < NU; ++j)
             lds_read8(vtoken(va, 0, kg) ^ j * 128, vtoken(va, 1, kg) ^ j * 128, vtoken(va, 2, kg) ^ j * 128,
                       vtoken(va, 3, kg) ^ j * 128, vx[4 * j], vx[4 * j + 1], vx[4 * j + 2], vx[4 * j + 3]);
+    }
+    __device__ static inline void weigh(uint32_t va, v_t (&vx)[VREGS], bool read, const float (&p)[4], int ntok,
+                                        f32x4_t (&acc)[ACC], int kg) {
+        if (!read) read_values(va, kg, vx);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
 #pragma unroll
@@ -449,7 +464,11 @@ struct Page<float, D, false> {
         }
         return sum;
     }
-    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&ot)[DT], int kg) {
+    static constexpr int VREGS = 1;
+    typedef u32x2_t v_t;
+    __device__ static inline void read_values(uint32_t, int, v_t (&)[VREGS]) {}
+    __device__ static inline void weigh(uint32_t va, v_t (&)[VREGS], bool, const float (&p)[4], int ntok, f32x4_t (&ot)[DT],
+                                        int kg) {
         f32x4_t pv[DT];                               // the page's own sum, then added to the run's
 #pragma unroll
         for (int e0 = 0; e0 < 4; e0 += 8 / (D / 32)) {    // four reads at a time
@@ -542,7 +561,11 @@ struct Page<float, D, true> : QuadOut<D> {
         }
         return x;
     }
-    __device__ static inline void weigh(uint32_t va, const float (&p)[4], int ntok, f32x4_t (&acc)[ACC], int kg) {
+    static constexpr int VREGS = 1;
+    typedef u32x2_t v_t;
+    __device__ static inline void read_values(uint32_t, int, v_t (&)[VREGS]) {}
+    __device__ static inline void weigh(uint32_t va, v_t (&)[VREGS], bool, const float (&p)[4], int ntok, f32x4_t (&acc)[ACC],
+                                        int kg) {
         constexpr int NE = 4 / NU;                    // tokens per four reads
 #pragma unroll
         for (int e0 = 0; e0 < 4; e0 += NE) {
@@ -571,6 +594,14 @@ constexpr int page_bytes_of() { return kPage * D * (int)sizeof(T); }
 // as far as one product's columns go.
 template <typename T>
 constexpr bool quad_heads(int G) { return sizeof(T) == 2 ? G <= 2 : G <= 4; }
+
+// Calls whose values go to registers as soon as they are there (8 or 16 of them), so
+// that the next page is requested whole before this one's weights are formed: a
+// wave's pages follow each other 0.8 us apart instead of 0.95 (d = 64).  Not where
+// it would take the long batches of four and eight heads at d = 128 past the 96
+// registers that leave other kernels room beside them.
+template <typename T>
+constexpr bool early_values(int D, int G, int OWN) { return sizeof(T) == 2 && (D == 64 || OWN > 0 || G <= 2); }
 
 // One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
 // stage + 1024 q (the immediate offset moves source and destination).
@@ -649,6 +680,7 @@ decode_kernel(DecodeArgs a) {
     constexpr int NW = OWN ? OWN : waves_of<T, D>();
     constexpr int NT = 64 * NW;
     constexpr int LOADS = Pg::LOADS, ACC = Pg::ACC;
+    constexpr bool EARLY = early_values<T>(D, G, OWN);
     // per wave its pages (keys, values); when they are read, the wave's o goes
     // where the first keys were
     constexpr int STAGE = 2 * Pg::BYTES;
@@ -691,17 +723,20 @@ decode_kernel(DecodeArgs a) {
         // Thread t takes request base + t; the prefix sums meet in LDS.  (Rolled up:
         // the code before the first page is fetched cold by every CU.)
         __shared__ int s_sum[NW], s_incl[NT], s_len[NT], s_np[NT];
+        int any_long = 0;                                 // (sign) a request of the last block has too many pages for a workgroup
         auto scan_block = [&](int base, int acc) {        // inclusive sums of the block's requests; its end
             const int r = min(base + tid, R - 1), sl = a.seq_lens[r], np = a.num_pages[r];
             const int x = base + tid < R ? req_view<STEP, PREFIX>(a, r, sl, np).n : 0;
-            const int incl = wave_scan(x);
+            const int incl = wave_scan(x), mark = __ballot(x > kDecodeOwnRun * NW) ? 1 << 31 : 0;
             if (base > 0) __syncthreads();                // (the previous block has been read)
-            if (lane == 63) s_sum[wave] = incl;
+            if (lane == 63) s_sum[wave] = incl | mark;
             __syncthreads();
             int before = acc, all = acc;
+            any_long = 0;
 #pragma unroll
             for (int w = 0; w < NW; ++w) {
-                const int t = s_sum[w];
+                const int t = s_sum[w] & 0x7fffffff;
+                any_long |= s_sum[w];
                 if (w < wave) before += t;
                 all += t;
             }
@@ -714,6 +749,13 @@ decode_kernel(DecodeArgs a) {
         int U = 0;
         for (int base = 0; base < R; base += NT) U = uni(scan_block(base, U));
         const int L = max(max(a.min_run, cdiv(U, a.W * NW)), min(kDecodeShortRun, cdiv(U, a.W1 * NW)));
+        // Short requests in a wide table, few enough for a workgroup each, take one each,
+        // as OWN: nothing to merge, and the merge launch finds that at once.  Up to
+        // kDecodeOwnRun pages per wave; us a call at 512 table columns, equal runs and so:
+        // 4 requests of 100-250 tokens, 12/12 heads, d 64, 12.2 and 8.1; 16 of 60-120 at 8/1,
+        // d 128, 17.3 and 9.0; 64 of 100-500 at 32/8, d 128, 22.1 and 18.4; with eight pages per
+        // wave 16 of 100-1000 at 8/4, d 64, 11.9 and 13.7.
+        const bool own = R <= a.W && R <= NT && uni(any_long) >= 0;
         if (wg == a.W - 1) {                              // (the workgroup with the fewest pages)
             // for the merge pass, per request: tokens attended (-1: held), whether a
             // token went in, and the partial slots it folds (first, count; count 0:
@@ -728,7 +770,8 @@ decode_kernel(DecodeArgs a) {
                 if (h == 0) {
                     // (the lengths are read a second time here: should another stream be
                     // writing them, the slots named still lie in the workspace)
-                    const int ws = min(a0 / L / NW, a.W - 1), we = np > 0 ? min((a0 + np - 1) / L / NW, a.W - 1) : ws;
+                    const int ws = own ? r : min(a0 / L / NW, a.W - 1);
+                    const int we = own || np == 0 ? ws : min((a0 + np - 1) / L / NW, a.W - 1);
                     a.lens[r] = v.held ? -1 : v.m_attn;
                     a.lens[R + r] = v.room ? 1 : 0;
                     a.lens[2 * R + r] = ws + r;
@@ -741,11 +784,20 @@ decode_kernel(DecodeArgs a) {
                 }
             }
         }
-        if (wg * NW * L >= U) return;                     // (uniform over the workgroup)
+        if (own ? wg >= R : wg * NW * L >= U) return;     // (uniform over the workgroup)
 
         f0 = min((wg * NW + wave) * L, U);
         f1 = min(f0 + L, U);
-        for (int base = 0, acc = 0; base < R; base += NT) {
+        if (own) {
+            r = wg;
+            m_in = uni(s_len[r]);
+            P_in = uni(s_np[r]);
+            const int n_ = uni(req_view<STEP, PREFIX>(a, r, m_in, P_in).n), run = cdiv(n_, NW);
+            a0 = uni(s_incl[r]) - n_;
+            f0 = a0 + min(wave * run, n_);
+            f1 = a0 + min((wave + 1) * run, n_);
+        }
+        for (int base = 0, acc = 0; base < R && !own; base += NT) {
             if (R > NT) {                                 // (one block is still in LDS)
                 __syncthreads();
                 acc = uni(scan_block(base, acc));
@@ -954,6 +1006,7 @@ decode_kernel(DecodeArgs a) {
             const bool has = cur.phys >= 0, has1 = nxt.phys >= 0;
             const int ntok = min(kPage, cur.m_attn - (cur.base + cur.p) * kPage);
             f32x4_t sx = {0.0f, 0.0f, 0.0f, 0.0f};
+            typename Pg::v_t vx[Pg::VREGS];
             if (has) {                                // wave-uniform
                 // the keys: requested after them are the page's values
                 __builtin_amdgcn_sched_barrier(0);
@@ -962,8 +1015,16 @@ decode_kernel(DecodeArgs a) {
                 __asm__ volatile("" : "+v"(kr));
                 sx = Pg::scores(kr, q);
                 __builtin_amdgcn_sched_barrier(0);
+                if constexpr (EARLY) {
+                    __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    __asm__ volatile("" : "+v"(vr));
+                    Pg::read_values(vr, kg, vx);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
             }
             if (has1) request_keys(nxt.phys);
+            if (EARLY && has1) request_values(nxt.phys);
             if (has) {
                 // online softmax of the lane's head over tokens 4 kg + e
                 float sc[4], ml = kNegInf;
@@ -995,7 +1056,13 @@ decode_kernel(DecodeArgs a) {
                         sc[e] -= top;
                     lowest = fminf(lowest, sc[e]);
                 }
-                if (ntok < kPage || __any(lowest < -126.0f)) {
+                if (ntok < kPage) {                   // (not the slots past the last token)
+                    lowest = 0.0f;
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+                        if (4 * kg + e < ntok) lowest = fminf(lowest, sc[e]);
+                }
+                if (__any(lowest < -126.0f)) {
 #pragma unroll
                     for (int e = 0; e < 4; ++e) sc[e] = exp2f(sc[e]);
                 } else {
@@ -1003,16 +1070,18 @@ decode_kernel(DecodeArgs a) {
                     for (int e = 0; e < 4; ++e) sc[e] = __builtin_amdgcn_exp2f(sc[e]);
                 }
                 lrun += (sc[0] + sc[1]) + (sc[2] + sc[3]);
-                // the values: requested after them are the next page's keys
-                __builtin_amdgcn_sched_barrier(0);
-                if (has1) __builtin_amdgcn_s_waitcnt(wait_vm(LOADS));
-                else __builtin_amdgcn_s_waitcnt(kWaitVm0);
-                __builtin_amdgcn_sched_barrier(0);
-                __asm__ volatile("" : "+v"(vr));
-                Pg::weigh(vr, sc, ntok, ot, kg);
+                if constexpr (!EARLY) {
+                    // the values: requested after them are the next page's keys
+                    __builtin_amdgcn_sched_barrier(0);
+                    if (has1) __builtin_amdgcn_s_waitcnt(wait_vm(LOADS));
+                    else __builtin_amdgcn_s_waitcnt(kWaitVm0);
+                    __builtin_amdgcn_sched_barrier(0);
+                    __asm__ volatile("" : "+v"(vr));
+                }
+                Pg::weigh(vr, vx, EARLY, sc, ntok, ot, kg);
                 __builtin_amdgcn_sched_barrier(0);
             }
-            if (has1) request_values(nxt.phys);
+            if (!EARLY && has1) request_values(nxt.phys);
             if (cur.valid && cur.last) {
                 const bool all = cur.first_of && cur.ends;        // the wave has the whole request
                 if (!nxt.valid) {
@@ -1048,9 +1117,10 @@ decode_kernel(DecodeArgs a) {
         }
     }
     // the parts of waves [w0, w1) of request rr (m1, pt: and the partial that the
-    // wave after them wrote, folded last, as if it had left its part open).  All
-    // waves' values are requested at once, whichever count: a loop over the waves
-    // paid an LDS latency for each (1.5 us of a call).
+    // wave after them wrote, folded last, as if it had left its part open).  A
+    // workgroup of one request asks for all waves' values before it uses the first:
+    // a loop over them pays an LDS latency each (0.5-1 us of a call).  Among short
+    // requests, of two or three waves, the loop is the shorter one.
     auto fold = [&](int w0, int w1, int rr, bool more_, bool direct) {
         float *pt = part_of(rr);
         T *out = reinterpret_cast<T *>(a.out) + ((size_t)rr * Hq + (size_t)h * G) * D;
@@ -1061,26 +1131,33 @@ decode_kernel(DecodeArgs a) {
             const int i = min(tid + e * NT, G * D - 1), g = i / D, dd = i % D;
             const float *q = pt + (size_t)g * (D + 2);
             const float m1 = more_ ? q[D] : kNegInf;
-            float mw[NW], lw[NW], ow[NW];
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                mw[w] = s_ml[w][g][0];
-                lw[w] = s_ml[w][g][1];
-                ow[w] = reinterpret_cast<const float *>(s_wave[w])[i];
-            }
             M[e] = m1;
-#pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                if (w < w0 || w >= w1) mw[w] = kNegInf;
-                M[e] = fmaxf(M[e], mw[w]);
-            }
             Ls[e] = Os[e] = 0.0f;
+            auto add = [&](float mw, float lw, float ow) {
+                const float fw = mw == kNegInf ? 0.0f : exp2f(mw - M[e]);
+                Ls[e] += lw * fw;
+                Os[e] += ow * fw;
+            };
+            if (OWN || w1 - w0 == NW) {               // (uniform)
+                float mw[NW], lw[NW], ow[NW];
 #pragma unroll
-            for (int w = 0; w < NW; ++w) {
-                if (w < w0 || w >= w1) continue;      // (uniform)
-                const float fw = mw[w] == kNegInf ? 0.0f : exp2f(mw[w] - M[e]);
-                Ls[e] += lw[w] * fw;
-                Os[e] += ow[w] * fw;
+                for (int w = 0; w < NW; ++w) {
+                    mw[w] = s_ml[w][g][0];
+                    lw[w] = s_ml[w][g][1];
+                    ow[w] = reinterpret_cast<const float *>(s_wave[w])[i];
+                }
+#pragma unroll
+                for (int w = 0; w < NW; ++w) {
+                    if (w >= w1) mw[w] = kNegInf;
+                    M[e] = fmaxf(M[e], mw[w]);
+                }
+#pragma unroll
+                for (int w = 0; w < NW; ++w)
+                    if (w < w1) add(mw[w], lw[w], ow[w]);
+            } else {
+                for (int w = w0; w < w1; ++w) M[e] = fmaxf(M[e], s_ml[w][g][0]);
+                for (int w = w0; w < w1; ++w)
+                    add(s_ml[w][g][0], s_ml[w][g][1], reinterpret_cast<const float *>(s_wave[w])[i]);
             }
             const float f1_ = m1 == kNegInf ? 0.0f : exp2f(m1 - M[e]);
             if (more_) {
@@ -1509,7 +1586,7 @@ hipError_t launch_g(int G, const DecodeArgs &a, int stages, hipStream_t s) {
     // the merge pass also advances the lengths when a token went in, updates
     // the summaries of a step call, and folds the prefix partials of a
     // shared-prefix call; with a workgroup per request there is nothing to fold
-    const bool own = mode != 2 && decode_own(a.max_pages, a.R, a.Hkv);
+    const bool own = mode != 2 && decode_own(a.max_pages, a.R, a.Hkv, page_bytes_of<T, D>(), NW, quad_heads<T>(G));
     const bool narrow = own && decode_own_narrow(a.R, a.Hkv);
     const bool chunks = stages & GP_DECODE_CHUNKS, prefix = (stages & GP_DECODE_PREFIX) && mode == 2,
                merge = (stages & GP_DECODE_MERGE) &&

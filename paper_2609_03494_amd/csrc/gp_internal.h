@@ -24,6 +24,7 @@ constexpr int kDecodeWorkgroups = GP_DECODE_WORKGROUPS;    // decode workgroups 
 #endif
 constexpr int kDecodeMinRun = GP_DECODE_MIN_RUN;           // pages a decode wave takes at least
 constexpr int kDecodeShortRun = 8;        // runs up to this many pages: one round of workgroups only
+constexpr int kDecodeOwnRun = 6;          // pages per wave up to which all requests take a workgroup each (see decode_kernel)
 constexpr int kDecodeResident = 512;      // decode workgroups that 256 CUs hold at once
 #ifndef GP_WIDE_MERGE
 #define GP_WIDE_MERGE 64
@@ -57,19 +58,26 @@ __device__ inline float ema_step(float prev, float x, double beta, double one_mi
 }
 
 // Short tables: one workgroup per (KV head, request), so that no request spans
-// two and the merge launch falls away.  Up to 64 pages (1024 tokens) that saves
-// more than equal runs do (64 requests of up to 500 tokens, 32/8 heads, d 128:
-// 20.8 us against 26.3; 8/8 heads, d 64: 11.5 against 15.8), up to 128 where there
-// are two workgroups per CU (256 requests of up to 1000 tokens, 66 pages, 32/8
-// heads: 130 against 142; 64 requests of up to 1900: 63.1 against 64.6; but 4 of
-// them 21 against 13.9).
-__host__ __device__ inline bool decode_own(int max_pages, int R, int Hkv) {
-    return max_pages <= 64 || (max_pages <= 128 && (int64_t)R * Hkv >= 512);
+// two and the merge launch falls away.  Its time is that of the pages a wave takes
+// one after the other, 4 us and 0.8 per page (bf16, d 64) or 1.0 (d 128); equal runs
+// and their merge take 10 us or more at any length.  Up to nine pages per wave it is
+// always the shorter (4 requests of 366-1100 tokens, 12/12 heads, d 64: 9.7 us a
+// call against 12.5; one of 950, 32/8, d 128: 11.5 and 11.8), up to eight where P.V of
+// a 4 KB page runs in 4 x 4 products (16 of up to 1100 tokens, 4/4, d 128: 15.2 with
+// nine, 13.6 in equal runs).  With enough (KV head, request) pairs for half the chip
+// equal runs cost more: up to 16 pages (16 of 633-1900, 12/12, d 64: 15.7 against
+// 19.2), 10 of 4 KB or more (16 of 550-1100, 32/8, d 128: 14.5 and 16.7; at eleven 18.1
+// and 18.1).  With about two workgroups per CU up to 16 of any size (64 of up to 1900,
+// 32/8, d 128: 60.4 and 64.6).  waves: of a workgroup; quad: see Page in gp_decode.hip.
+__host__ __device__ inline bool decode_own(int max_pages, int R, int Hkv, int page_bytes, int waves, bool quad) {
+    const int per = cdiv(max_pages, waves);
+    const int64_t pairs = (int64_t)R * Hkv;
+    return per <= (quad && page_bytes > 2048 ? 8 : 9) || (pairs >= 128 && per <= (page_bytes <= 2048 ? 16 : 10)) || (pairs >= 448 && per <= 16);
 }
-// ... of four waves instead of eight where a wave holds 64 registers (pages of 2 KB)
-// and as many workgroups are there: more of them fit a CU, fewer waves have no page
-// (8/8 heads, d 64, up to 200 tokens: 256 requests 15.8 us against 20.3, 128 10.3
-// against 11.2; 16 requests of up to 500 tokens the other way round, 9.8 against 8.1).
+// ... of four waves instead of eight (pages of 2 KB) where as many workgroups are
+// there: more of them fit a CU, fewer waves have no page (8/8 heads, d 64, up to 200
+// tokens: 256 requests 15.8 us against 20.3, 128 10.3 against 11.2; 16 requests of up
+// to 500 tokens the other way round, 9.8 against 8.1).
 __host__ __device__ inline bool decode_own_narrow(int R, int Hkv) { return (int64_t)R * Hkv >= 512; }
 
 struct DecodeWs {

@@ -158,6 +158,9 @@ SPLITS = {
     "a_run_each": [32] * 40,
     "mixed": [0, 700, 3, 0, 0, 2500, 16, 48, 1, 1600, 0],
     "past_a_scan_block": [(r * 37) % 50 for r in range(1100)],
+    # a wide table: a workgroup each up to six pages per wave (48, or 24 with four waves), one page more, none
+    "short_in_wide_table": [0, 768, 5, 384, 0, 17, 383, 1],
+    "a_page_too_long": [769, 385, 40, 0, 3],
 }
 
 
