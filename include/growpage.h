@@ -227,8 +227,8 @@ gp_status_t gp_decode_attention(const gp_kv_layer_t *kv, const gp_page_state_t *
  * (not once per request), in a prefix pass on the matrix cores; each
  * request's private pages follow in the usual split pass, and the two
  * partial results are merged.  Whether a request reads the prefix pass is
- * decided on the device: it must not be held, hold at least prefix_pages
- * pages and prefix_pages * page_size tokens, and have the leader's page ids
+ * decided on the device: it must not be held, hold more than prefix_pages *
+ * page_size tokens (and the pages they take), and have the leader's page ids
  * on all prefix pages; any other member (e.g. one whose shared pages a
  * compaction has replaced by private copies, App. E.2) is served like a
  * request of no group, so the groups only decide the speed, never the
