@@ -545,43 +545,71 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
         for (int k = 0; k < 4; ++k) a.counters[k] += (long long)s_cnt[k];
     }
 
-    // Requests whose table row changes, one wave each: the old row is kept for
-    // the copy; a private page replaces each shared page that stays (ranked by
-    // logical page) and the old reference is dropped; a shrink also drops the
-    // last page.  Pages whose count reaches zero are listed.  (The whole
-    // workgroup on one request after the other, with a barrier per scan step,
-    // took 3 us per request: 64 us for the kernel at 18 compressing requests
-    // with a shared prefix.)
-    for (int i = wave; i < Rb; i += (int)(blockDim.x >> 6)) {
+    // Requests whose table row changes: the old row is kept for the copy; a private
+    // page replaces each shared page that stays (ranked by logical page) and the
+    // old reference is dropped; a shrink also drops the last page.  Pages whose
+    // count reaches zero are listed.  A wave takes up to 8 x 64 pages of a row, as
+    // many as keep all waves busy, their flags, ids, new ids and counts in flight
+    // together (the selection's counts and the flags before them give the rank of
+    // the first).  us for this
+    // call, 18 requests of 200 pages, 32 shared / one of 1500, 1300 shared / one of
+    // 4000, 3900 shared: the workgroup on one request after the other, with a
+    // barrier per scan step, 57 / 10.6 / 22; a wave per request, 64 pages at a time,
+    // 14 / 27 / 73; now 12 / 9.4 / 15.
+    constexpr int kSub = 8, kWaves = kDecideThreads / 64;
+    const int nsub = min(kSub, cdiv(Rb * cdiv(a.max_pages, 64), kWaves)), per_row = cdiv(a.max_pages, 64 * nsub);
+    for (int item = wave; item < Rb * per_row; item += kWaves) {
+        const int i = item / per_row, j0 = item % per_row * 64 * nsub;
         const int dec = s_rq[i].dec;
         const bool shrink = dec == GP_SHRINK;
         if (!(compressing(dec) && s_rq[i].nsh > 0) && !shrink) continue;      // wave-uniform
-        const int r = a.bnd[i], P = s_rq[i].P, pop = s_rq[i].pop;
+        const int P = s_rq[i].P, pop = s_rq[i].pop;
+        if (j0 >= P) continue;
+        const int r = a.bnd[i];
         const int keep = shrink ? P - 1 : P;
         int32_t *row = a.page_table + (size_t)r * a.max_pages;
-        int base = 0;
-        for (int j0 = 0; j0 < P; j0 += 64) {
-            const int j = j0 + lane;
-            const bool sh = j < keep && a.shflag[(size_t)i * a.max_pages + j] != 0;
-            const unsigned long long ms = __ballot(sh);
-            if (j < P) {
-                const int old = row[j];
-                a.old_table[(size_t)i * a.max_pages + j] = old;
-                if (sh) {
-                    const int k = base + __popcll(ms & ((1ull << lane) - 1));
-                    const int pid = a.free_list[fc0 - 1 - pop - k];
-                    row[j] = pid;
-                    if (pid >= 0 && pid < a.pool_pages) a.refcount[pid] = 1;
-                }
-                if (sh || (shrink && j == P - 1)) {
-                    if (shrink && j == P - 1) row[j] = -1;
-                    if (old >= 0 && old < a.pool_pages) {
-                        const int prev = atomicSub(&a.refcount[old], 1);
-                        if (prev == 1) a.released[atomicAdd(&a.hdr[HDR_NREL], 1)] = old;
-                    }
-                }
-            }
+        const uint8_t *shared = a.shflag + (size_t)i * a.max_pages;
+        int base = 0;                                 // shared pages before j0
+        for (int c = 0; c < j0 / kPageBlock; ++c) base += a.nshc[(size_t)i * a.npc + c];
+        for (int k0 = j0 / kPageBlock * kPageBlock; k0 < j0; k0 += 64 * kSub) {
+            uint8_t f[kSub];
+#pragma unroll
+            for (int u = 0; u < kSub; ++u) f[u] = shared[min(k0 + 64 * u, j0 - 64) + lane];
+#pragma unroll
+            for (int u = 0; u < kSub; ++u) base += k0 + 64 * u < j0 ? __popcll(__ballot(f[u] != 0)) : 0;
+        }
+        int old[kSub], pid[kSub], prev[kSub];
+        bool sh[kSub], drop[kSub];
+        const int end = min(P, j0 + 64 * nsub);       // of this wave's pages
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int j = min(j0 + 64 * u + lane, end - 1);
+            sh[u] = shared[j] != 0;
+            old[u] = row[j];
+        }
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int j = j0 + 64 * u + lane;
+            sh[u] = sh[u] && j < min(keep, end);
+            drop[u] = (sh[u] || (shrink && j == P - 1 && j < end)) && old[u] >= 0 && old[u] < a.pool_pages;
+            const unsigned long long ms = __ballot(sh[u]);
+            const int k = base + __popcll(ms & ((1ull << lane) - 1));
+            pid[u] = a.free_list[sh[u] ? fc0 - 1 - pop - k : 0];
+            prev[u] = drop[u] ? atomicSub(&a.refcount[old[u]], 1) : 0;
             base += __popcll(ms);
+        }
+#pragma unroll
+        for (int u = 0; u < kSub; ++u) {
+            const int j = j0 + 64 * u + lane;
+            if (j >= end) continue;
+            a.old_table[(size_t)i * a.max_pages + j] = old[u];
+            if (sh[u]) {
+                row[j] = pid[u];
+                if (pid[u] >= 0 && pid[u] < a.pool_pages) a.refcount[pid[u]] = 1;
+            } else if (shrink && j == P - 1) {
+                row[j] = -1;
+            }
+            if (drop[u] && prev[u] == 1) a.released[atomicAdd(&a.hdr[HDR_NREL], 1)] = old[u];
         }
     }
 }

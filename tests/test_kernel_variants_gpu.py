@@ -479,3 +479,72 @@ def test_decide_pages_in_list_order(events, stack):
     assert dec.cpu().tolist() == expect
     assert torch.equal(ps.page_table.cpu(), want_table)
     assert int(ps.free_count) == top and counters.cpu().tolist() == tally
+
+
+@pytest.mark.parametrize("policy", [gp.GP_POLICY_GROWPAGE, gp.GP_POLICY_SHRINK])
+@pytest.mark.parametrize("pages,shared", [(3, "all"), (65, "all"), (129, "prefix 128"), (130, "every 3rd"), (512, "all"),
+                                          (513, "every 3rd"), (600, "prefix 513"), (1025, "all"), (1600, "every 3rd"),
+                                          (2100, "prefix 1537")])
+def test_decide_long_shared_rows(pages, shared, policy):
+    """Shared pages over several blocks of a row (64 pages a ballot, 512 a wave,
+    1024 a selection count): private pages in order of the logical page, the old
+    references dropped, pages nobody holds any more back on the stack by id, and
+    a shrink's last page dropped; two requests of the same row, one beside them
+    that stays."""
+    _say(f"decide {pages} pages, shared: {shared}, policy {policy}")
+    gen = torch.Generator().manual_seed(pages)
+    hkv, d, R, shrink = 1, 64, 3, policy == gp.GP_POLICY_SHRINK
+    width = pages + 3
+    kind, _, num = shared.partition(" ")
+    is_shared = [kind == "all" or (kind == "prefix" and j < int(num)) or (kind == "every" and j % 3 == 1)
+                 for j in range(pages)]
+    pool = 6 * pages + 40
+    perm = torch.randperm(pool, generator=gen).to(torch.int32)
+    table = torch.full((R, width), -1, dtype=torch.int32)
+    refs = torch.zeros(pool, dtype=torch.int32)
+    at = 0
+    for j in range(pages):
+        for r in range(R):
+            if r and is_shared[j]:
+                table[r, j] = table[0, j]
+            else:
+                table[r, j], at = perm[at], at + 1
+            refs[int(table[r, j])] += 1
+    free = pool - at
+    free_list = torch.zeros(pool, dtype=torch.int32)
+    free_list[:free] = perm[at:]
+    i32 = lambda x: torch.as_tensor(x, dtype=torch.int32).to(DEV)
+    lens = [16 * pages, 16 * pages, 16 * pages - 5]           # the last one is not at a boundary
+    ps = gp.PageState(table.to(DEV), i32([pages] * R), i32(lens), refs.to(DEV), free_list.to(DEV), i32([free]))
+    kc = torch.randn(pool, hkv, 16, d, generator=gen).to(torch.bfloat16).to(DEV)
+    kv = gp.KVLayer(kc, kc.clone())
+    order = [1, 0]
+    counts = torch.tensor([[[[5, 60]]] * 2], dtype=torch.int32).to(DEV)
+    scores = torch.rand(1, 2, hkv, (width - 1) * 16, generator=gen).to(DEV)
+    dec, delta = torch.full((2,), -1, dtype=torch.int32, device=DEV), torch.zeros(2, device=DEV)
+    counters = torch.zeros(4, dtype=torch.int64, device=DEV)
+    ws = gp.workspace(gp.GP_OP_APPLY, R, 2, hkv, hkv, d, width, torch.bfloat16)
+    gp.gp_boundary_apply([kv], ps, i32(order), counts, scores,
+                         gp.Params(policy=policy, min_capacity_pages=2, shrink_threshold=0.0), dec, delta, counters, ws)
+    torch.cuda.synchronize()
+    want, want_refs, top = table.clone(), refs.clone(), free
+    keep = pages - 1 if shrink else pages
+    released = []
+    for r in order:
+        fresh = [j for j in range(keep) if is_shared[j]]
+        for j in fresh + ([pages - 1] if shrink else []):
+            old = int(table[r, j])
+            want_refs[old] -= 1
+            if want_refs[old] == 0:
+                released.append(old)
+        for k, j in enumerate(fresh):
+            want[r, j] = free_list[top - 1 - k]
+            want_refs[int(want[r, j])] = 1
+        top -= len(fresh)
+        if shrink:
+            want[r, pages - 1] = -1
+    assert dec.cpu().tolist() == [gp.GP_SHRINK if shrink else gp.GP_COMPRESS] * 2
+    assert torch.equal(ps.page_table.cpu(), want)
+    assert torch.equal(ps.refcount.cpu(), want_refs)
+    assert int(ps.free_count) == top + len(released)
+    assert ps.free_list.cpu()[top:top + len(released)].tolist() == sorted(released)
