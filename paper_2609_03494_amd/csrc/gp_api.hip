@@ -392,7 +392,7 @@ gp_status_t apply_call(const gp_kv_layer_t *layers, int32_t n_layers, const gp_p
         return GP_ERR_INVALID;
     if (params->policy == GP_POLICY_SHRINK && !isfinite(params->shrink_threshold)) return GP_ERR_INVALID;
     if (params->layout != GP_LAYOUT_SHIFT && params->layout != GP_LAYOUT_FILL) return GP_ERR_INVALID;
-    if (num_bnd > 2048 || ps->max_pages > kMaxBoundaryPages) return GP_ERR_UNSUPPORTED;
+    if (num_bnd > kMaxBnd || ps->max_pages > kMaxBoundaryPages) return GP_ERR_UNSUPPORTED;
     const gp_kv_layer_t &L0 = layers[0];
     const int E = elem_bytes(L0.dtype);
     const ApplyWs w = apply_ws(num_bnd, L0.num_kv_heads, L0.head_dim, E, ps->max_pages, n_layers);

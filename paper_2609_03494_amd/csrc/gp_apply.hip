@@ -38,8 +38,6 @@ namespace gp {
 
 namespace {
 
-constexpr int kMaxBnd = 2048;
-
 struct LayerTable {
     void *k[kMaxLayers];
     void *v[kMaxLayers];
@@ -349,17 +347,19 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_waves_per_eu(4))
 // ----------------------------------------------------------------- decide --
 // Flags per boundary request: bit 0 at a boundary, bit 1 wants to grow, bit 2
 // wants to shrink.
-enum { F_BOUNDARY = 1, F_GROW = 2, F_SHRINK = 4, F_SKIPPED = 8 };
+enum { F_BOUNDARY = 1, F_GROW = 2, F_SHRINK = 4, F_SKIPPED = 8, F_LAST_SHARED = 16 };
 
 // LDS per boundary request (dynamic: a few KB for the usual handful of events,
 // so that the kernel finds room beside decode attention's workgroups; sized for
 // kMaxBnd events it took 70 KB and had to wait for decode's drain).
 struct DecideReq {
     unsigned long long D;   // sum of K^S - K^L (two's complement)
-    int P, flags;
-    int nsh, nsh_last;      // shared pages to replace; whether the last page is one of them
-    int dec, pop;
+    int P;
+    int nsh;                // shared pages to replace
+    int pop;
+    short flags, dec;
 };
+static_assert(kMaxBnd * sizeof(DecideReq) + 1024 <= 64 << 10, "a launch's dynamic LDS stays below 64 KiB at any list length");
 
 constexpr int kDecideThreads = 512;   // (two waves per SIMD: it starts beside two decode workgroups)
 __global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
@@ -431,9 +431,8 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
         }
         a.delta[i] = dl;
         s_rq[i].P = P;
-        s_rq[i].flags = flags;
+        s_rq[i].flags = (short)(flags | (last_shared ? F_LAST_SHARED : 0));
         s_rq[i].nsh = nsh;
-        s_rq[i].nsh_last = last_shared;
     }
     __syncthreads();
 
@@ -444,7 +443,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
         if (!(q.flags & F_BOUNDARY)) return GP_NOT_BOUNDARY;
         const bool want = (q.flags & F_GROW) != 0, shrink = (q.flags & F_SHRINK) != 0;
         // a shrink keeps pages [0, P - 1) only: the last page needs no copy
-        const int nsh = shrink ? q.nsh - q.nsh_last : q.nsh;
+        const int nsh = shrink ? q.nsh - ((q.flags & F_LAST_SHARED) ? 1 : 0) : q.nsh;
         if (want && avail > a.reserve && q.P < a.max_pages) {
             pop = 1;
             return GP_GROW;
@@ -456,7 +455,7 @@ __global__ __launch_bounds__(kDecideThreads) void decide_kernel(ApplyArgs a) {
         return shrink ? GP_SHRINK : (want ? GP_FALLBACK : GP_COMPRESS);
     };
     auto settle = [&](int i, int dec, int pop, int popped) {
-        s_rq[i].dec = dec;
+        s_rq[i].dec = (short)dec;
         s_rq[i].pop = popped;
         if (dec != GP_GROW && dec != GP_PREEMPT && dec != GP_NOT_BOUNDARY) s_rq[i].nsh = pop;
         // (a shrink counts as a compression)

@@ -35,6 +35,7 @@ constexpr int kMaxPrefixSlotPages = 128;  // and at most (LDS id table)
 constexpr int kMaxDecodePages = 8192;     // table width the decode calls accept
 constexpr size_t kScratchBytes = size_t(8) << 20;   // static scratch of gp_decode_attention_noalloc
 constexpr int kMaxBoundaryPages = 4096;                    // table width the boundary calls accept
+constexpr int kMaxBnd = 2048;             // boundary requests one apply, select, decide or compact call takes
 constexpr int kStatBlock = 64;            // candidate tokens per softmax-statistics block (one wave)
 constexpr int kProbChunk = 1024;          // tokens per weight/score work item
 constexpr int kCompactChunk = 256;        // slots per compaction work item

@@ -423,7 +423,7 @@ def test_decode_shared_split(hq, hkv, d, prefix):
 
 # ------------------------------------------------------------------ decide --
 
-@pytest.mark.parametrize("events", [1, 7, 64, 513, 1500])
+@pytest.mark.parametrize("events", [1, 7, 64, 513, 1500, 2048])
 @pytest.mark.parametrize("stack", ["ample", "exact", "short", "none"])
 def test_decide_pages_in_list_order(events, stack):
     """Pages are handed out in list order, whether the stack covers everybody
