@@ -211,9 +211,9 @@ gp_status_t gp_update_summaries(const void *q_pre, gp_dtype_t dtype, int32_t num
  * out are not written, and gp_decode_step leaves its summaries alone).  Page slots at or beyond m_r are never used, whatever
  * they hold.  The work is split over the pages of the whole batch, so the
  * float32 sums of a request run in an order that depends on the lengths of the
- * others (held ones count with their length): its output is the same to
- * float32 rounding in any batch, bit for bit only in batches of the same
- * lengths.  out: [num_reqs][num_q_heads][head_dim]. */
+ * others (held ones count with their length), on num_reqs, num_kv_heads and
+ * max_pages: its output is the same to float32 rounding in any batch, bit for
+ * bit where all of these are the same.  out: [num_reqs][num_q_heads][head_dim]. */
 gp_status_t gp_decode_attention(const gp_kv_layer_t *kv, const gp_page_state_t *ps,
                                 const void *q_post, int32_t num_q_heads, float scale,
                                 void *out, void *ws, size_t ws_bytes, hipStream_t stream);
@@ -258,8 +258,12 @@ gp_status_t gp_decode_attention_shared(const gp_kv_layer_t *kv, const gp_page_st
  * harnesses that forbid hipMalloc).  Same arguments and results as
  * gp_decode_attention; the split partials go to a static device array of
  * 8 MiB (one per device, held until the process ends), so the call allocates
- * nothing.  A batch whose decode workspace (gp_workspace_bytes(GP_OP_DECODE,
- * ...)) exceeds 8 MiB returns GP_ERR_SCRATCH without launching.  `stream`
+ * nothing.  Batches up to a fixed size, whatever the kernels use of it: with
+ * c = ceil(max_pages / 64) and c' = ceil(max_pages / ceil(max_pages / c)),
+ *   up256(num_reqs * (c' + 1) * num_q_heads * (head_dim + 2) * 4) +
+ *   up256(num_reqs * 12) <= 8 MiB,   up256: rounded up to a multiple of 256;
+ * others return GP_ERR_SCRATCH without launching.  (gp_workspace_bytes, which
+ * covers the shared prefix too, does not tell.)  `stream`
  * must belong to the current device (else GP_ERR_INVALID).  Every call on a
  * device shares that device's array: calls that overlap on one device (on
  * different streams, or a later call before an earlier one has completed on

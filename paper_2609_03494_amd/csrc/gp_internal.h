@@ -87,9 +87,9 @@ struct DecodeWs {
     int W, slots, pslots;
 };
 
-// Bytes of a workspace with one (max, sum, o) partial per 64 pages of table
-// width and one more, and three words per request: what
-// gp_decode_attention_noalloc compares with its scratch.
+// What gp_decode_attention_noalloc compares with its scratch, as growpage.h states it:
+// one (max, sum, o) partial per 64 pages of table width and one more, and three words
+// per request.
 __host__ __device__ inline size_t decode_chunked_bytes(int R, int Hq, int D, int max_pages) {
     const int chunks = cdiv(max_pages, cdiv(max_pages, cdiv(max_pages, 64)));
     return align_up((size_t)R * (chunks + 1) * Hq * (D + 2) * sizeof(float)) + align_up((size_t)R * 3 * sizeof(int32_t));
@@ -115,7 +115,8 @@ __host__ __device__ inline DecodeWs decode_ws(int R, int Hq, int Hkv, int D, int
     w.W = cdiv(kDecodeWorkgroups, Hkv);
     const int64_t most = (int64_t)R * max_pages;
     if (most < (int64_t)w.W * waves * kDecodeMinRun) w.W = (int)((most + waves * kDecodeMinRun - 1) / (waves * kDecodeMinRun));
-    // a batch that the static scratch takes keeps fitting it
+    // a batch that the static scratch takes fits it (fewer workgroups from 673 KV heads of
+    // eight query heads on, where one request's partials are two slots of 4 MiB)
     const size_t lens = align_up((size_t)R * 5 * sizeof(int32_t));
     if (decode_chunked_bytes(R, Hq, D, max_pages) <= kScratchBytes) {
         const int64_t fit = (int64_t)((kScratchBytes - lens - kAlign) / unit) - R;

@@ -158,3 +158,33 @@ def test_stream_read_checksum(lib):
         gp.gp_stream_read(src, out)
         torch.cuda.synchronize()
         assert int(out.cpu().numpy().view(np.uint32)[0]) == int(np.bitwise_xor.reduce(host))
+
+
+def test_noalloc_limit_is_the_documented_one(lib):
+    """gp_decode_attention_noalloc refuses exactly the batches that the header's
+    formula says, on both sides of the limit; what it accepts goes on to the
+    device, which answers GP_ERR_HIP where there is none."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("the accepted side would launch on these addresses")
+    up = lambda x: -(-x // 256) * 256
+    fake, seen = 0x1000, set()
+    for hkv, G in ((1, 1), (2, 8), (8, 4), (8, 1), (40, 2), (256, 8), (700, 8)):
+        for d in (64, 128):
+            for dtype in (0, 1):
+                for pages in (1, 16, 64, 65, 128, 300, 2113, 4033, 8192):
+                    c = -(-pages // -(-pages // -(-pages // 64)))
+                    need = lambda R: up(R * (c + 1) * G * hkv * (d + 2) * 4) + up(R * 12)
+                    lo, hi = 0, 65535                                  # the largest R that fits
+                    while lo < hi:
+                        mid = (lo + hi + 1) // 2
+                        lo, hi = (mid, hi) if need(mid) <= 8 << 20 else (lo, mid - 1)
+                    for R in {1, 2, max(lo, 1), min(lo + 1, 65535)}:
+                        kv = _lib._KVLayer(fake, fake, 100, hkv, 16, d, dtype)
+                        ps = _lib._PageState(fake, fake, fake, fake, fake, fake, R, pages, 100)
+                        st = lib.gp_decode_attention_noalloc(ctypes.byref(kv), ctypes.byref(ps), fake, G * hkv, 0.1,
+                                                             fake, None)
+                        want = 5 if need(R) > 8 << 20 else 4
+                        assert st == want, (hkv, G, d, dtype, pages, R, st)
+                        seen.add(st)
+    assert seen == {4, 5}
