@@ -389,6 +389,82 @@ def test_decode_unaligned(dtype, hq, hkv, d, offset, spare):
     _check(results[1][0], _reference(kv.k, kv.v, table, lens, q, scale), dtype, "decode")
 
 
+# lengths whose new token opens a page (16 n): at a request's first page, at the first
+# page of a wave's run and of a workgroup, beside full (F), held (H) and empty requests
+STEPS = {
+    "opens_pages": [0, 16, 32, 256, 512, 768, 15, 31, 1, 480, "F48", "H64", 33],
+    "one_long": [2048],
+    "runs_of_two_pages": [32, "F32", 32, 32, "H32", 31, 32, 32, 0, 32] * 5,
+    "long_and_short": [1600, 5, "F16", 2047, "H700", 0, 1023, 16],
+}
+
+
+@pytest.mark.parametrize("name", list(STEPS))
+@pytest.mark.parametrize("spare", [2, 140])
+@pytest.mark.parametrize("repeat", [1, 9])
+@pytest.mark.parametrize("dtype,hq,hkv,d", [(torch.bfloat16, 3, 3, 64), (torch.bfloat16, 8, 4, 64), (torch.bfloat16, 16, 4, 64),
+                                            (torch.bfloat16, 16, 2, 64), (torch.bfloat16, 4, 4, 128), (torch.bfloat16, 8, 2, 128),
+                                            (torch.float32, 4, 2, 64), (torch.float32, 8, 1, 64), (torch.float32, 2, 2, 128),
+                                            (torch.float32, 8, 1, 128)])
+def test_step_token_split(name, spare, repeat, dtype, hq, hkv, d):
+    """gp_decode_step with a token in every form of the decode kernel (a workgroup of
+    four or eight waves per request, equal runs): the cache, lengths and summaries
+    of gp_append_step bit for bit, outputs of decode attention after it, and both
+    against float64."""
+    spec = STEPS[name] * (repeat if len(STEPS[name]) < 20 else 1)
+    full, held = ([str(m)[0] == c for m in spec] for c in "FH")
+    lens = [int(m[1:]) if isinstance(m, str) else m for m in spec]
+    if repeat > 1:                                             # (512 pairs: four waves per request at d 64)
+        spec_n = -(-512 // hkv)
+        while len(lens) < spec_n and max(lens) < 1000:
+            lens, full, held = lens + lens, full + full, held + held
+    _say(f"step {name} x{repeat} {dtype} heads {hq}/{hkv} d {d} spare {spare}: {len(lens)} requests")
+    R, scale = len(lens), d ** -0.5
+    gen = torch.Generator().manual_seed(R + d)
+    # a page for the token, but for the full ones
+    npages = [m // 16 if f else m // 16 + 1 for m, f in zip(lens, full)]
+    width = max(npages) + spare
+    pool, table = _paged(R, width, npages, gen)
+    kc = torch.full((pool, hkv, 16, d), float("nan"), dtype=dtype)
+    vc = kc.clone()
+    for r, m in enumerate(lens):
+        for p in range(-(-m // 16)):
+            t = min(16, m - 16 * p)
+            kc[table[r, p], :, :t] = torch.randn(hkv, t, d, generator=gen).to(dtype)
+            vc[table[r, p], :, :t] = torch.randn(hkv, t, d, generator=gen).to(dtype)
+    rand = lambda *s: torch.randn(*s, generator=gen).to(dtype).to(DEV)
+    q, q_pre, k_new, v_new = rand(R, hq, d), rand(R, hq, d), rand(R, hkv, d), rand(R, hkv, d)
+    qs = torch.randn(R + 3, 2, hq, d, generator=gen).to(DEV)
+    slots = torch.randperm(R + 3, generator=gen)[:R].to(torch.int32).to(DEV)
+    init = (torch.arange(R) % 5 == 4).to(torch.uint8).to(DEV)
+    dev_lens = [-m - 1 if h else m for m, h in zip(lens, held)]
+    n = gp.gp_workspace_bytes(gp.GP_OP_DECODE, R, 0, hq, hkv, d, width, dtype)
+    results = []
+    for fused in (True, False):
+        kv = gp.KVLayer(kc.to(DEV), vc.to(DEV))
+        ps, pos = _state(table, npages, dev_lens, pool), torch.arange(R, dtype=torch.int32, device=DEV)
+        out, qstate = torch.full_like(q, 7.0), qs.clone()
+        ws = torch.zeros(n, dtype=torch.uint8, device=DEV)
+        if fused:
+            gp.gp_decode_step(kv, ps, q, q_pre, scale, out, slots, init, qstate, 0.9, 0.999, ws, k_new, v_new, pos)
+        else:
+            gp.gp_append_step([kv], ps, pos, k_new.unsqueeze(0), v_new.unsqueeze(0), q_pre.unsqueeze(0), slots, init,
+                              qstate.unsqueeze(0), 0.9, 0.999)
+            gp.gp_decode_attention(kv, ps, q, scale, out, ws)
+        torch.cuda.synchronize()
+        results.append([kv.k, kv.v, qstate, pos, ps.seq_lens, out])
+    for what, a, b in zip(("keys", "values", "summaries", "positions", "lengths"), *results):
+        assert torch.equal(a.view(torch.uint8), b.view(torch.uint8)), what
+    k_, v_, _, _, new_lens, out = results[0]
+    assert new_lens.cpu().tolist() == [m if f or h else m + 1 for m, f, h in zip(dev_lens, full, held)]
+    assert bool((out[torch.tensor(held, device=DEV)] == 7.0).all())
+    ref_lens = [0 if h else max(m, 0) for m, h in zip(new_lens.cpu().tolist(), held)]
+    want = _reference(k_, v_, table, ref_lens, q, scale)
+    for got in (out, results[1][5]):
+        got[torch.tensor(held, device=DEV)] = 0.0
+        _check(got, want, dtype, "step")
+
+
 @pytest.mark.parametrize("hq,hkv,d", [(16, 2, 128), (4, 4, 64), (8, 2, 64)])
 @pytest.mark.parametrize("prefix", [1, 5, 70])
 def test_decode_shared_split(hq, hkv, d, prefix):
