@@ -6,8 +6,8 @@
 // every workgroup itself).  The waves take equal runs of L consecutive pages of
 // it, whatever requests they belong to, so all workgroups have the same amount
 // of work; the next page's keys and values are on their way across request
-// boundaries too.  A wave that meets the end of a
-// request writes that request's result (or its partial, if the request began
+// boundaries too.  (Short requests, few enough, take a workgroup each instead: see
+// decode_own and the split below.)  A wave that meets the end of a request writes that request's result (or its partial, if the request began
 // before the wave's run) and goes on with the next; at the end the workgroup
 // merges the runs its waves left open, and requests that span workgroups are
 // folded by merge_kernel from one (o, max, sum) partial per workgroup, at slot
@@ -664,7 +664,7 @@ constexpr int decode_occupancy() {
 // Per wave one LDS page of keys and one of values, filled by direct-to-LDS
 // loads, each instruction one contiguous 1 KiB of the head's slice; the keys
 // are refilled as soon as the scores are formed, the values once P.V has read
-// them, and each wait is for exactly the loads it needs.  Sixteen waves per CU
+// them (or the registers have: early_values), and each wait is for exactly the loads it needs.  Sixteen waves per CU
 // (bf16, d = 128) keep the memory busy while some of them compute: the copy of
 // the loads reads 6.7-6.8 TB/s whether or not a wave pauses for 1000 cycles
 // between a page's arrival and its refill; eight waves with two pages each read
@@ -752,7 +752,7 @@ decode_kernel(DecodeArgs a) {
         // Short requests in a wide table, few enough for a workgroup each, take one each,
         // as OWN: nothing to merge, and the merge launch finds that at once.  Up to
         // kDecodeOwnRun pages per wave; us a call at 512 table columns, equal runs and so:
-        // 4 requests of 100-250 tokens, 12/12 heads, d 64, 12.2 and 8.1; 16 of 60-120 at 8/1,
+        // 4 requests of 100-250 tokens, 12/12 heads, d 64, 12.2 and 8.5; 16 of 60-120 at 8/1,
         // d 128, 17.3 and 9.0; 64 of 100-500 at 32/8, d 128, 22.1 and 18.4; with eight pages per
         // wave 16 of 100-1000 at 8/4, d 64, 11.9 and 13.7.
         const bool own = R <= a.W && R <= NT && uni(any_long) >= 0;

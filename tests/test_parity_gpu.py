@@ -269,9 +269,9 @@ def test_decode_g8_prefix_shared():
 @pytest.mark.parametrize("hq", [8, 32, 64])
 def test_decode_ignores_slots_past_the_last_token(hq):
     """Slots of a request's last page past its last token hold anything -- here
-    NaN and +-inf in K and V -- and must not reach the output: the vector-ALU
-    P.V (G = 1) skips them, the matrix-core P.V (G = 4, 8) multiplies them by
-    zero weights, so it has to read them as zero first."""
+    NaN and +-inf in K and V -- and must not reach the output: P.V, on the matrix
+    cores, multiplies them by zero weights, so it has to read them as zero
+    first."""
     _say(f"decode: poisoned slots past the last token, {hq} q / 8 kv heads")
     rng = np.random.default_rng(hq)
     n = rng.integers(20, 1200, size=12)
