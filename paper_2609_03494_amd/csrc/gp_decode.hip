@@ -389,19 +389,21 @@ struct Page<uint16_t, D, true> : PageBf16<D, true>, QuadOut<D> {
     }
     static constexpr int VREGS = 4 * NU;
     typedef u32x2_t v_t;
+    __device__ static inline void read_group(uint32_t va, int kg, int j, v_t *x) {
+        lds_read8(vtoken(va, 0, kg) ^ j * 128, vtoken(va, 1, kg) ^ j * 128, vtoken(va, 2, kg) ^ j * 128,
+                  vtoken(va, 3, kg) ^ j * 128, x[0], x[1], x[2], x[3]);
+    }
     __device__ static inline void read_values(uint32_t va, int kg, v_t (&vx)[VREGS]) {
 #pragma unroll
-        for (int j = 0; j < NU; ++j)
-            lds_read8(vtoken(va, 0, kg) ^ j * 128, vtoken(va, 1, kg) ^ j * 128, vtoken(va, 2, kg) ^ j * 128,
-                      vtoken(va, 3, kg) ^ j * 128, vx[4 * j], vx[4 * j + 1], vx[4 * j + 2], vx[4 * j + 3]);
+        for (int j = 0; j < NU; ++j) read_group(va, kg, j, vx + 4 * j);
     }
     __device__ static inline void weigh(uint32_t va, v_t (&vx)[VREGS], bool read, const float (&p)[4], int ntok,
                                         f32x4_t (&acc)[ACC], int kg) {
-        if (!read) read_values(va, kg, vx);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
+        for (int j = 0; j < NU; ++j) {
+            if (!read) read_group(va, kg, j, vx + 4 * j);
 #pragma unroll
-            for (int j = 0; j < NU; ++j) {
+            for (int e = 0; e < 4; ++e) {
                 u32x2_t v = vx[4 * j + e];
                 if (ntok < kPage && 4 * kg + e >= ntok) v = u32x2_t{0u, 0u};
                 f32x4_t *o = acc + 4 * j;
@@ -597,11 +599,11 @@ constexpr bool quad_heads(int G) { return sizeof(T) == 2 ? G <= 2 : G <= 4; }
 
 // Calls whose values go to registers as soon as they are there (8 or 16 of them), so
 // that the next page is requested whole before this one's weights are formed: a
-// wave's pages follow each other 0.8 us apart instead of 0.95 (d = 64).  Not where
-// it would take the long batches of four and eight heads at d = 128 past the 96
-// registers that leave other kernels room beside them.
+// wave's pages follow each other 0.8 us apart instead of 0.95 (d = 64).  Not in the
+// equal runs of d = 128, which it would take past the 96 registers that leave other
+// kernels' waves room beside two workgroups (107 with one query head, for 1 %).
 template <typename T>
-constexpr bool early_values(int D, int G, int OWN) { return sizeof(T) == 2 && (D == 64 || OWN > 0 || G <= 2); }
+constexpr bool early_values(int D, int OWN) { return sizeof(T) == 2 && (D == 64 || OWN > 0); }
 
 // One page slice into LDS: instruction q takes at(q) (less 1024 (q % 4)) to
 // stage + 1024 q (the immediate offset moves source and destination).
@@ -653,8 +655,8 @@ __device__ inline void store_out(float *p, const f32x4_t &o, float l) {
 template <typename T, int D, int OWN>
 constexpr int decode_occupancy() {
     if (waves_of<T, D>() < 8) return 2;
-    if (OWN == 0 || page_bytes_of<T, D>() > 2048) return 4;
-    return OWN < waves_of<T, D>() ? 6 : 5;
+    if (OWN == 0) return 4;
+    return OWN < waves_of<T, D>() ? 6 : sizeof(T) == 2 ? 5 : 4;
 }
 
 // MODE 0: decode attention; 1: gp_decode_step with the step's new token (the
@@ -680,7 +682,7 @@ decode_kernel(DecodeArgs a) {
     constexpr int NW = OWN ? OWN : waves_of<T, D>();
     constexpr int NT = 64 * NW;
     constexpr int LOADS = Pg::LOADS, ACC = Pg::ACC;
-    constexpr bool EARLY = early_values<T>(D, G, OWN);
+    constexpr bool EARLY = early_values<T>(D, OWN);
     // per wave its pages (keys, values); when they are read, the wave's o goes
     // where the first keys were
     constexpr int STAGE = 2 * Pg::BYTES;
