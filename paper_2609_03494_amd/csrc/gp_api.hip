@@ -190,7 +190,7 @@ gp_status_t decode_call(const gp_kv_layer_t *kv, const gp_page_state_t *ps, cons
         const int rpb = kPrefixWaves * (16 / (num_q_heads / kv->num_kv_heads));
         for (int g = 0; g < num_groups; ++g) {
             const gp_prefix_group_t &gr = groups[g];
-            if (gr.first_req < end || gr.num_reqs < 1 || gr.first_req + gr.num_reqs > ps->num_reqs ||
+            if (gr.first_req < end || gr.num_reqs < 1 || gr.num_reqs > ps->num_reqs - gr.first_req ||
                 gr.prefix_pages < 1 || gr.prefix_pages > ps->max_pages)
                 return GP_ERR_INVALID;
             end = gr.first_req + gr.num_reqs;

@@ -188,3 +188,13 @@ def test_noalloc_limit_is_the_documented_one(lib):
                         assert st == want, (hkv, G, d, dtype, pages, R, st)
                         seen.add(st)
     assert seen == {4, 5}
+
+
+def test_prefix_group_beyond_int32_is_refused(lib):
+    """A group whose end does not fit an int32 is past the batch."""
+    fake = 0x1000
+    kv = _lib._KVLayer(fake, fake, 100, 8, 16, 128, 1)
+    ps = _lib._PageState(fake, fake, fake, fake, fake, fake, 4, 10, 100)
+    group = (_lib._PrefixGroup * 1)(_lib._PrefixGroup(1, 2 ** 31 - 1, 1))
+    assert lib.gp_decode_attention_shared(ctypes.byref(kv), ctypes.byref(ps), fake, 32, 0.1, fake, group, 1, 7, fake,
+                                          1 << 40, None) == 1
