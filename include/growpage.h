@@ -33,8 +33,10 @@
  *    zero-filled once after allocation; every call leaves its counters at
  *    zero on completion, so it can be reused without clearing.  Two calls
  *    that run concurrently must not share a workspace.
- *  - Buffers lie at any multiple of their element's size, bfloat16 pools (k, v)
- *    at a multiple of 16 bytes.
+ *  - Pools (k, v) and workspaces lie at multiples of 16 bytes, other buffers at
+ *    any multiple of their element's size.  gp_append_step takes pools, and the
+ *    decode calls float32 pools and workspaces, at any multiple of the element
+ *    as well.
  *  - Page size b is 16 tokens; head_dim is 64 or 128; num_q_heads is 1, 2, 4
  *    or 8 times num_kv_heads.  Decode attention takes page tables up to 8192
  *    pages wide (131072 tokens per request), the boundary calls up to 4096
